@@ -92,6 +92,40 @@ __device__ __forceinline__ int slot_in_row(int2 r, int x, int align) {
     }
 }
 
+// The same as a code that addresses every operand without a further test.
+// Inside: byte offset of the slot in a complex128 field (16 bytes a slot,
+// below 2^31); dead slot: that offset with the top bit set; outside:
+// CODE_OUT.  A field of w-byte values takes code / (16 / w) as its offset:
+// the top bit alone puts a dead slot at or past the end of every field
+// (fewer than 2^27 slots), and so does CODE_OUT with and without its top bit,
+// so loads read zero and the store of an outside point is dropped.
+constexpr unsigned CODE_DEAD = 0x80000000u;
+constexpr unsigned CODE_OUT = 0xfffffff0u;
+// Row entry of the march's LDS ring: byte offset of column 0 of the row (16
+// bytes a slot), first column, columns, and the widened range as first | count << 16.
+__device__ __forceinline__ int4 row_entry(int2 r, int align) {
+    const int x0 = r.y & 0xffff, x1 = (r.y >> 16) & 0xffff;
+    const int a0 = x0 & -align, a1 = (x1 + align - 1) & -align;
+    const int n = x1 - x0;
+    return make_int4((int)((unsigned)r.x * 16u), x0, n, n > 0 ? (int)((unsigned)a0 | (unsigned)(a1 - a0) << 16) : 0);
+}
+__device__ __forceinline__ unsigned code_in_row(int4 e, int x) {
+    const unsigned o = (unsigned)e.x + (unsigned)x * 16u;
+    const unsigned live = (unsigned)(x - e.y) < (unsigned)e.z ? o : o | CODE_DEAD;
+    return (unsigned)(x - (e.w & 0xffff)) < (unsigned)e.w >> 16 ? live : CODE_OUT;
+}
+// A halo point: inside or outside.
+__device__ __forceinline__ unsigned halo_code(int4 e, int x, bool on) {
+    return (unsigned)(x - e.y) < (unsigned)e.z && on ? (unsigned)e.x + (unsigned)x * 16u : CODE_OUT;
+}
+template <class T>
+__device__ __forceinline__ unsigned coff(unsigned code) {
+    return code / (16 / (unsigned)sizeof(T));
+}
+__device__ __forceinline__ unsigned code_of(int slot) {  // slot_in_row's value as a code
+    return slot >= 0 ? (unsigned)slot * 16u : (slot == -1 ? CODE_OUT : (unsigned)(-slot - 2) * 16u | CODE_DEAD);
+}
+
 // Buffer loads and stores (CDNA): a per-workgroup resource (base address,
 // size in bytes) in scalar registers and a 32-bit byte offset per lane.  An
 // offset at or beyond the size reads zero and drops a store, in hardware, so

@@ -78,38 +78,37 @@ struct Halo {
     }
 };
 
+// x_axis along the march: column-bound for axis 0 and 1 (xa), plane-bound for
+// axis 2 (hz = h there, else 0), zero without a field axis, and the field E
+// (zero without an axis), so that a step needs no test of the axis.
+struct FieldTerm {
+    double xa, hz, off, E;
+    __device__ __forceinline__ FieldTerm(const KParams &a, int x, int y) {
+        const int cc = a.axis == 0 ? x : y;
+        xa = a.axis == 0 || a.axis == 1 ? a.h * ((double)cc - a.off_axis) : 0.0;
+        hz = a.axis == 2 ? a.h : 0.0;
+        off = a.off_axis;
+        E = a.axis < 0 ? 0.0 : (a.field_dev ? *a.field_dev : a.field);
+    }
+    __device__ __forceinline__ double at(int z) const { return fma(hz, (double)z - off, xa); }
+};
+
 // The per-point epilogue shared by both marches: H value from the Laplacian
 // taps, then the stage combination (times the absorber mask m_c when MASK),
-// stored at idx (dropped when idx = -1; zero at the dead slot -idx - 2 when
-// idx <= -2).  PAIR (a first-type FP64 stage of the discrete adjoint): b_c
+// stored at the point's code (zero at a dead slot, dropped outside the box).
+// PAIR (a first-type FP64 stage of the discrete adjoint): b_c
 // holds the pair operand u at the point, and pacc gathers conj(in) x_axis u
 // (zero wherever the point is outside the box, since both loads read zero
 // there).
 template <bool NTS, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS, bool PAIR = false>
 __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0, Tc lr, Tc li, Tc v_c,
-                                       Tc vi_c, double2 b_c, double m_c, double E, int x, int y, int z,
-                                       int idx, __amdgpu_buffer_rsrc_t rout, double2 &pacc) {
-    Tc vloc = v_c;
-    if constexpr (PAIR || (!std::is_same<Tc, double>::value && FIRST)) {
-        // a branch here: in the FP32 first-type stages a select costs
-        // registers at the 4-wave occupancy limit, and the pair stages (which
-        // always have a field axis) measured the same either way
-        if (a.axis >= 0) {
-            const int cc = a.axis == 0 ? x : (a.axis == 1 ? y : z);
-            const double xc = a.h * ((double)cc - a.off_axis);
-            vloc += (Tc)(E * xc);
-            if constexpr (PAIR) {
-                pacc.x += xc * ((double)q0.x * b_c.x + (double)q0.y * b_c.y);
-                pacc.y += xc * ((double)q0.x * b_c.y - (double)q0.y * b_c.x);
-            }
-        }
-    } else {
-        // the field term as a select: a branch in the march's step costs
-        // more than the few operations it would skip
-        const int cc = a.axis == 0 ? x : (a.axis == 1 ? y : z);
-        const double xc = a.h * ((double)cc - a.off_axis);
-        const Tc vf = vloc + (Tc)(E * xc);
-        vloc = a.axis >= 0 ? vf : vloc;
+                                       Tc vi_c, double2 b_c, double m_c, const FieldTerm &f, int z,
+                                       unsigned code, __amdgpu_buffer_rsrc_t rout, double2 &pacc) {
+    const double xc = f.at(z);
+    const Tc vloc = v_c + (Tc)(f.E * xc);
+    if constexpr (PAIR) {
+        pacc.x += xc * ((double)q0.x * b_c.x + (double)q0.y * b_c.y);
+        pacc.y += xc * ((double)q0.x * b_c.y - (double)q0.y * b_c.x);
     }
     const Tc kin_h2 = (Tc)a.kin_h2;
     Tc hr, hi;
@@ -122,10 +121,10 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
         hr = kin_h2 * lr + vloc * q0.x;
         hi = kin_h2 * li + vloc * q0.y;
     }
-    const bool dead = idx < -1;
-    const unsigned o = boff<Tout>(dead ? -idx - 2 : idx);
+    const bool zero = (int)code < 0;
+    const unsigned o = coff<Tout>(code & ~CODE_DEAD);
     if (MODE == 0) {
-        store_c<NTS>(rout, o, (Tout *)nullptr, dead ? 0.0 : (double)hr, dead ? 0.0 : (double)hi);
+        store_c<NTS>(rout, o, (Tout *)nullptr, zero ? 0.0 : (double)hr, zero ? 0.0 : (double)hi);
     } else {
         const double2 bb = FIRST ? make_double2((double)q0.x, (double)q0.y) : b_c;
         double r = bb.x + (a.cre * (double)hr - a.cim * (double)hi);
@@ -134,17 +133,32 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
             r *= m_c;
             i *= m_c;
         }
-        store_c<NTS>(rout, o, (Tout *)nullptr, dead ? 0.0 : r, dead ? 0.0 : i);
+        store_c<NTS>(rout, o, (Tout *)nullptr, zero ? 0.0 : r, zero ? 0.0 : i);
     }
 }
+
+// Constants of the pipelined march: depth D, ring lengths, and the LDS ring
+// of row entries (segments of P planes, the unroll period).
+template <int TX, int TY, int D>
+struct Ring {
+    static_assert(D >= 1 && D <= 2, "pipeline depth 1..2");
+    static constexpr int NT = TX * TY;                            // threads
+    static constexpr int HPT = (8 * TX + 8 * TY + NT - 1) / NT;  // halo values per thread
+    static constexpr int Q = D == 1 ? 10 : 12;                   // own-column ring, >= 9 + D
+    static constexpr int HA = HPT == 1 ? 4 + D : D;              // planes ahead at which the halo is loaded
+    static constexpr int VD = D + 1;                             // V / base ring slots
+    static constexpr int P = clcm(clcm(clcm(clcm(Q, D), VD), 2), HA);
+    static constexpr int RY = TY + 8;                            // rows of a plane, halo included
+    static constexpr int SEG = HA == 4 + D ? 2 : 3;              // live segments of row entries
+    static constexpr int RPT = (P * RY + NT - 1) / NT;           // row entries a thread loads per segment
+    static constexpr int ROWS = SEG * P * RY;                    // int4 in LDS
+};
 
 // Software-pipelined march, depth D = 1..2, over the item's planes zs, zs +
 // dir, ... (dir = +1 upward, -1 downward; the stencil is symmetric in z).
 // At step k (output plane z = zs + dir k) a thread
-//   - issues the row-table reads for the loads of step k+1,
 //   - issues the data loads of plane k+4+D (own column), of the halo of plane
-//     k+HA and of V and base at plane k+D, from row entries read one step
-//     earlier,
+//     k+HA and of V and base at plane k+D,
 //   - computes plane k from data that arrived during earlier steps.
 // HA = 4+D when each thread carries one halo value (the halo of a plane is
 // then loaded in the same step as the plane's own columns, by this and by
@@ -152,23 +166,27 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
 // All rings are indexed by compile-time constants after unrolling the step
 // loop by a common period, so no register is moved while its load is in
 // flight.  FIRST: base == in, whose value at the point is the centre tap.
+//
+// Row entries come from LDS: the workgroup keeps the entries of its TY + 8
+// rows for one unroll period of planes ahead, loaded together once per
+// period.  Loaded by every thread for the next step, they sat in the vector
+// memory queue between the data loads; that queue completes in order, so
+// waiting for a row entry also waited for the data loads issued a step
+// before it, which cut the pipeline to one step whatever D said.  The ring
+// also takes two loads and about 40 of 118 vector instructions (table
+// addresses, range tests, offsets) out of every step, and 16-24 registers,
+// so depth-1 FP64 tiles run 3 waves per SIMD instead of 2.  Measured: a
+// Taylor stage of the 3.05 M-point sphere with 64 orbitals 1.88 -> 1.79 ms
+// (32 x 16, depth 2) and 1.81 -> 1.65 ms with the best tile of each form;
+// 96^3 cube, 8 orbitals 77 -> 64 us; 48 uneven spheres 2.6 -> 1.8 ms.
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
           bool PAIR>
 __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, const int n,
-                                           typename CT<Tc>::c2 *tile, double2 &pacc) {
+                                           typename CT<Tc>::c2 *tile, int4 *rowl, double2 &pacc) {
     using C2 = typename CT<Tc>::c2;
-    // selects instead of branches in the row lookups: the row index always,
-    // the slot in the row except in the FP32 stage that reads complex128
-    // (there that select costs registers at the 4-wave occupancy limit)
-    constexpr bool SEL = std::is_same<Tc, double>::value || std::is_same<Tin, float2>::value;
-    constexpr int NT = TX * TY, LX = TX + 8;
-    constexpr int HPT = (8 * TX + 8 * TY + NT - 1) / NT;
-    static_assert(D >= 1 && D <= 2, "pipeline depth 1..2");
-    constexpr int Q = D == 1 ? 10 : 12;        // own-column ring, >= 9 + D
-    constexpr int HA = HPT == 1 ? 4 + D : D;   // planes ahead at which the halo is loaded
-    constexpr int HQ = HA;                     // halo ring slots
-    constexpr int VD = D + 1;                  // V / base ring slots
-    constexpr int P = clcm(clcm(clcm(clcm(Q, D), VD), 2), HQ);
+    using R = Ring<TX, TY, D>;
+    constexpr int NT = R::NT, LX = TX + 8, HPT = R::HPT, Q = R::Q, HA = R::HA, HQ = R::HA, VD = R::VD, P = R::P;
+    constexpr int RY = R::RY, SEG = R::SEG, RPT = R::RPT;
     constexpr int PLANE = (TY + 8) * LX;       // one plane buffer; tile holds two
     const int t = threadIdx.x, lx = t % TX, ly = t / TX;
     const int x = it.x * TX + lx, y = it.y * TY + ly;
@@ -182,69 +200,64 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     const auto rvi = rsrc(CS ? a.Vim : a.V, CS && a.Vim ? np * 8 : 0);
     const Halo<TX, TY, HPT> hl(t, it);
 
-    auto fetch = [&](int idx, bool ok) -> C2 { return load_c<Tc, Tin>(rin, ok ? boff<Tin>(idx) : OOB); };
-    auto fetch_v = [&](int idx) -> Tc { return BL<Tc>::ld(rv, boff<Tc>(idx)); };
-    auto fetch_b = [&](int idx) -> double2 {
+    auto fetch = [&](unsigned c) -> C2 { return load_c<Tc, Tin>(rin, coff<Tin>(c)); };
+    auto fetch_v = [&](unsigned c) -> Tc { return BL<Tc>::ld(rv, coff<Tc>(c)); };
+    auto fetch_b = [&](unsigned c) -> double2 {
         if (MODE != 1 || (FIRST && !PAIR)) return make_double2(0.0, 0.0);
-        return BL<double2>::ld(rbase, boff<double2>(idx));
+        return BL<double2>::ld(rbase, coff<double2>(c));
     };
-    auto fetch_m = [&](int idx) -> double { return MASK ? BL<double>::ld(rm, boff<double>(idx)) : 1.0; };
-    auto fetch_vi = [&](int idx) -> Tc { return CS ? (Tc)BL<double>::ld(rvi, boff<double>(idx)) : (Tc)0; };
+    auto fetch_m = [&](unsigned c) -> double { return MASK ? BL<double>::ld(rm, coff<double>(c)) : 1.0; };
+    auto fetch_vi = [&](unsigned c) -> Tc { return CS ? (Tc)BL<double>::ld(rvi, coff<double>(c)) : (Tc)0; };
 
     const int zs = it.z, dir = it.w > it.z ? 1 : -1;
     const int nk = (it.w - it.z) * dir;  // planes to compute
+
+    // Row entries of segment b (planes bP + 4 + D ... bP + P + 3 + D of the
+    // march, b = -1 the prologue's), one per thread and pass; rows outside
+    // the tight box and planes past the last one read (nk + 3) are empty.
+    int2 seg[RPT];
+    auto seg_load = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int e = t + j * NT, pl = e / RY, r = e - pl * RY;
+            const int k = b * P + 4 + D + pl;
+            const int yy = it.y * TY + r - 4, zz = zs + dir * k;
+            const bool v = (unsigned)yy < (unsigned)a.ny && (unsigned)zz < (unsigned)a.nz && k < nk + 4 && pl < P;
+            seg[j] = a.rows[v ? zz * a.ny + yy : a.ny * a.nz];
+        }
+    };
+    auto seg_store = [&](int slot) {
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int e = t + j * NT;
+            if (P * RY % NT == 0 || e < P * RY) rowl[slot * (P * RY) + e] = row_entry(seg[j], a.align);
+        }
+    };
     // prologue: planes k = -4 .. 3+D into ring slots 0 .. Q-2 (slot of plane
-    // k is k + 4), halo of planes 0 .. HA-1, V/base of planes 0 .. D-1, rows
-    // for step 0.  Every row entry the prologue needs is requested before
-    // any is used, so that they arrive in one round trip (taking them one
-    // at a time chained a dozen L2 round trips ahead of the first plane);
-    // except in the FP32 stage that reads complex128, where holding them
-    // all costs registers at the 4-wave occupancy limit.
-    constexpr bool HOIST = !(std::is_same<Tc, float>::value && std::is_same<Tin, double2>::value);
-    int2 rw[Q - 1];
-    int2 rwh[HQ][HPT];
-    if constexpr (HOIST) {
+    // k is k + 4), halo of planes 0 .. HA-1, V/base of planes 0 .. D-1
+    seg_load(-1);
+    seg_store(SEG - 1);
+    seg_load(0);
+    seg_store(0);
+    int hrow[HPT];  // row of each halo value within a plane's entries
 #pragma unroll
-        for (int j = 0; j < Q - 1; ++j) rw[j] = row_of<true>(a, y, zs + dir * (j - 4));
-#pragma unroll
-        for (int d = 0; d < HQ; ++d)
-#pragma unroll
-            for (int k = 0; k < HPT; ++k) rwh[d][k] = row_of<true>(a, hl.y[k], zs + dir * d);
-    }
-    // step k reads row slot k % 2 and fills the other one
-    int2 rfr[2], rhl[2][HPT];
-    rfr[0] = row_of<true>(a, y, zs + dir * (4 + D));
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) rhl[0][k] = row_of<true>(a, hl.y[k], zs + dir * HA);
-    rfr[1] = make_int2(0, 0);
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) rhl[1][k] = make_int2(0, 0);
+    for (int j = 0; j < HPT; ++j) hrow[j] = hl.l[j] / LX;
+    __syncthreads();
+    const int4 *const pro = rowl + (SEG - 1) * (P * RY) + (P - 4 - D) * RY;  // entries of plane 0
     C2 cv[Q];
-    int oid[Q];
+    unsigned oid[Q];
 #pragma unroll
     for (int j = 0; j < Q - 1; ++j) {
-        int2 r;
-        if constexpr (HOIST)
-            r = rw[j];
-        else
-            r = row_of<true>(a, y, zs + dir * (j - 4));
-        oid[j] = slot_in_row<SEL>(r, x, a.align);
-        cv[j] = fetch(oid[j], true);
+        oid[j] = code_in_row(pro[(j - 4) * RY + ly + 4], x);
+        cv[j] = fetch(oid[j]);
     }
     cv[Q - 1] = C2{(Tc)0, (Tc)0};
-    oid[Q - 1] = -1;
+    oid[Q - 1] = CODE_OUT;
     C2 hal[HQ][HPT];
 #pragma unroll
     for (int d = 0; d < HQ; ++d)
 #pragma unroll
-        for (int k = 0; k < HPT; ++k) {
-            int2 r;
-            if constexpr (HOIST)
-                r = rwh[d][k];
-            else
-                r = row_of<true>(a, hl.y[k], zs + dir * d);
-            hal[d][k] = fetch(idx_in_row(r, hl.x[k]), hl.ok[k] && d < nk);
-        }
+        for (int j = 0; j < HPT; ++j) hal[d][j] = fetch(halo_code(pro[d * RY + hrow[j]], hl.x[j], hl.ok[j] && d < nk));
     Tc vr[VD], vir[VD];
     double2 br[VD];
     double mr[VD];
@@ -260,16 +273,19 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     br[D] = make_double2(0.0, 0.0);
     mr[D] = 0.0;
 
-    const double E = a.field_dev ? *a.field_dev : a.field;
+    const FieldTerm ft(a, x, y);
     const int own = (ly + 4) * LX + lx + 4;
+    int slot = 0;  // LDS segment of the current period
 
-    for (int kb = 0; kb < nk; kb += P) {
+    for (int kb = 0, b = 0; kb < nk; kb += P, ++b) {
+        const int next = slot + 1 == SEG ? 0 : slot + 1, prev = slot == 0 ? SEG - 1 : slot - 1;
+        const int4 *const rs = rowl + slot * (P * RY), *const rp = rowl + prev * (P * RY);
 #pragma unroll
         for (int s = 0; s < P; ++s) {
             const int k = kb + s;
             if (k >= nk) break;
             const int z = zs + dir * k;
-            const int sh = s % HQ, sr = s % 2, srp = (s + 1) % 2;
+            const int sh = s % HQ;
             const int shl = (s + HA) % HQ;              // halo slot of plane k + HA
             const int sv = s % VD, svn = (s + D) % VD;  // V/base: read slot, load slot
             // ring slot of plane k + m
@@ -279,36 +295,33 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
 #pragma unroll
             for (int j = 0; j < HPT; ++j)
                 if (hl.ok[j]) pl[hl.l[j]] = hal[sh][j];
-            const int idx_c = oid[SLOT(0)];
+            // next period's row entries: requested at the period's start,
+            // stored D + 2 steps later, when they have arrived with the data
+            // loads around them
+            if (s == 0) seg_load(b + 1);
+            if (s == D + 2) seg_store(next);
+            const unsigned code_c = oid[SLOT(0)];
             const Tc v_c = vr[sv];
             const Tc vi_c = vir[sv];
             const double2 b_c = br[sv];
             const double m_c = mr[sv];
             __syncthreads();
             {
-                // row entries for the next step first, then the loads that use
-                // the entries read last step
-                rfr[srp] = row_of<true>(a, y, z + dir * (5 + D));
-#pragma unroll
-                for (int j = 0; j < HPT; ++j) rhl[srp][j] = row_of<true>(a, hl.y[j], z + dir * (1 + HA));
-                int idf;
-                if constexpr (SEL) {
-                    const int sl = slot_in_row<true>(rfr[sr], x, a.align);
-                    idf = (k + 4 + D < nk + 4) ? sl : -1;
-                } else {
-                    idf = (k + 4 + D < nk + 4) ? slot_in_row<false>(rfr[sr], x, a.align) : -1;
-                }
-                oid[SLOT(4 + D)] = idf;
-                cv[SLOT(4 + D)] = fetch(idf, true);
+                const unsigned cf = code_in_row(rs[s * RY + ly + 4], x);
+                oid[SLOT(4 + D)] = cf;
+                cv[SLOT(4 + D)] = fetch(cf);
                 const bool hlive = k + HA < nk;
+                constexpr int back = 4 + D - HA;  // the halo's plane lies this far behind the own column's
 #pragma unroll
-                for (int j = 0; j < HPT; ++j)
-                    hal[shl][j] = fetch(idx_in_row(rhl[sr][j], hl.x[j]), hl.ok[j] && hlive);
-                const int idv = k + D < nk ? oid[SLOT(D)] : -1;
-                vr[svn] = fetch_v(idv);
-                vir[svn] = fetch_vi(idv);
-                br[svn] = fetch_b(idv);
-                mr[svn] = fetch_m(idv);
+                for (int j = 0; j < HPT; ++j) {
+                    const int4 e = s >= back ? rs[(s - back) * RY + hrow[j]] : rp[(P + s - back) * RY + hrow[j]];
+                    hal[shl][j] = fetch(halo_code(e, hl.x[j], hl.ok[j] && hlive));
+                }
+                const unsigned cd = k + D < nk ? oid[SLOT(D)] : CODE_OUT;
+                vr[svn] = fetch_v(cd);
+                vir[svn] = fetch_vi(cd);
+                br[svn] = fetch_b(cd);
+                mr[svn] = fetch_m(cd);
             }
             const C2 q0 = cv[SLOT(0)];
             Tc lr, li;
@@ -329,12 +342,13 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
                      FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (zm4.y + zp4.y));
             }
 #undef SLOT
-            finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, E, x, y, z, idx_c, rout,
+            finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, z, code_c, rout,
                                                        pacc);
             // no barrier here: the next step writes the other plane buffer,
             // and every wave has finished reading it once all have passed
             // this step's barrier
         }
+        slot = next;
     }
 }
 
@@ -403,7 +417,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     double2 b_c = fetch_b(idx_c);
     double m_c = fetch_m(idx_c);
 
-    const double E = a.field_dev ? *a.field_dev : a.field;
+    const FieldTerm ft(a, x, y);
     const int own = (ly + 4) * LX + lx + 4;
 
     for (int k = 0; k < nk; ++k) {
@@ -450,8 +464,8 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
                  FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (q[1].y + q[7].y)) +
                  FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (q[0].y + q[8].y));
         }
-        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, E, x, y, z, idx_c, rout,
-                                                       pacc);
+        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, z, code_of(idx_c),
+                                                       rout, pacc);
 #pragma unroll
         for (int j = 0; j < 8; ++j) q[j] = q[j + 1];
         idx_c = idx_n;
@@ -462,14 +476,23 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     }
 }
 
+// LDS row entries of a march (the lean one needs none).
+template <int TX, int TY, int D>
+constexpr int march_rows() {
+    if constexpr (D == 0)
+        return 1;
+    else
+        return Ring<TX, TY, D>::ROWS;
+}
+
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
           bool PAIR = false>
 __device__ __forceinline__ void march(const KParams &a, const int4 it, const int n, typename CT<Tc>::c2 *tile,
-                                      double2 &pacc) {
+                                      int4 *rowl, double2 &pacc) {
     if constexpr (D == 0)
         march_lean<NTS, TX, TY, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, pacc);
     else
-        march_ring<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, pacc);
+        march_ring<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, rowl, pacc);
 }
 
 // Sum of v over the workgroup (xor shuffles within each wave, then the wave
@@ -498,6 +521,7 @@ template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int 
           bool CS = false, bool PAIR = false>
 __global__ void __launch_bounds__(TX * TY) k_stencil(KParams a) {
     __shared__ typename CT<Tc>::c2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
+    __shared__ int4 rowl[march_rows<TX, TY, D>()];
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     int n, item;
     block_item(a, blk, &n, &item);
@@ -506,7 +530,7 @@ __global__ void __launch_bounds__(TX * TY) k_stencil(KParams a) {
     n = __builtin_amdgcn_readfirstlane(n);
     item = __builtin_amdgcn_readfirstlane(item);
     double2 pacc = make_double2(0.0, 0.0);
-    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, a.items[item], n, tile, pacc);
+    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, a.items[item], n, tile, rowl, pacc);
     if constexpr (PAIR) {
         // this workgroup's part of the pair sum, at its place in the launch
         // order (a fixed position, so the final sum has a fixed order)
@@ -534,6 +558,7 @@ __global__ void __launch_bounds__(TX * TY) k_stencil_batch(const KParams *__rest
                                                            const int32_t *__restrict__ seg, double cre,
                                                            double cim, int32_t *ctr) {
     __shared__ double2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
+    __shared__ int4 rowl[march_rows<TX, TY, D>()];
     __shared__ int32_t next;
     const int home = blockIdx.x % kBatchQueues;
     for (int j = 0; j < kBatchQueues; ++j) {
@@ -551,7 +576,7 @@ __global__ void __launch_bounds__(TX * TY) k_stencil_batch(const KParams *__rest
             a.cim = cim;
             double2 unused = make_double2(0.0, 0.0);
             march<NTS, TX, TY, D, double2, double, double2, 1, FIRST, false, false>(
-                a, bi.tile, __builtin_amdgcn_readfirstlane(bi.ob), tile, unused);
+                a, bi.tile, __builtin_amdgcn_readfirstlane(bi.ob), tile, rowl, unused);
             __syncthreads();  // the next item reuses the plane buffer
         }
     }
