@@ -49,12 +49,12 @@ namespace sk {
 // Halo assignment of a TX x TY tile (fixed for the whole march): halo value
 // j is a y-halo point for j < 8 TX (4 rows above, 4 below, x fastest) and an
 // x-halo point otherwise (4 left and 4 right of each tile row).
-template <int TX, int TY, int HPT>
+template <int TX, int TY, int NT, int HPT>
 struct Halo {
     int l[HPT], x[HPT], y[HPT];
     bool ok[HPT];
     __device__ __forceinline__ Halo(int t, int4 it) {
-        constexpr int NT = TX * TY, NHP = 8 * TX + 8 * TY, LX = TX + 8;
+        constexpr int NHP = 8 * TX + 8 * TY, LX = TX + 8;
 #pragma unroll
         for (int k = 0; k < HPT; ++k) {
             const int j = t + k * NT;
@@ -78,19 +78,19 @@ struct Halo {
     }
 };
 
-// x_axis along the march: column-bound for axis 0 and 1 (xa), plane-bound for
-// axis 2 (hz = h there, else 0), zero without a field axis, and the field E
-// (zero without an axis), so that a step needs no test of the axis.
+// x_axis along the march: bound to the thread's column for axis 0 (xa), to
+// the row or plane for axis 1 and 2 (hz = h there, else 0; at() takes that
+// row or plane), zero without a field axis, and the field E (zero without an
+// axis), so that a step needs no test of the axis.
 struct FieldTerm {
     double xa, hz, off, E;
-    __device__ __forceinline__ FieldTerm(const KParams &a, int x, int y) {
-        const int cc = a.axis == 0 ? x : y;
-        xa = a.axis == 0 || a.axis == 1 ? a.h * ((double)cc - a.off_axis) : 0.0;
-        hz = a.axis == 2 ? a.h : 0.0;
+    __device__ __forceinline__ FieldTerm(const KParams &a, int x) {
+        xa = a.axis == 0 ? a.h * ((double)x - a.off_axis) : 0.0;
+        hz = a.axis >= 1 ? a.h : 0.0;
         off = a.off_axis;
         E = a.axis < 0 ? 0.0 : (a.field_dev ? *a.field_dev : a.field);
     }
-    __device__ __forceinline__ double at(int z) const { return fma(hz, (double)z - off, xa); }
+    __device__ __forceinline__ double at(int i) const { return fma(hz, (double)i - off, xa); }
 };
 
 // The per-point epilogue shared by both marches: H value from the Laplacian
@@ -102,9 +102,9 @@ struct FieldTerm {
 // there).
 template <bool NTS, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS, bool PAIR = false>
 __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0, Tc lr, Tc li, Tc v_c,
-                                       Tc vi_c, double2 b_c, double m_c, const FieldTerm &f, int z,
+                                       Tc vi_c, double2 b_c, double m_c, const FieldTerm &f, int yz,
                                        unsigned code, __amdgpu_buffer_rsrc_t rout, double2 &pacc) {
-    const double xc = f.at(z);
+    const double xc = f.at(yz);
     const Tc vloc = v_c + (Tc)(f.E * xc);
     if constexpr (PAIR) {
         pacc.x += xc * ((double)q0.x * b_c.x + (double)q0.y * b_c.y);
@@ -137,15 +137,19 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
     }
 }
 
+// A stage that carries another operand per point (a base, a mask, an adjoint
+// pair).
+constexpr bool stage_heavy(int mode, bool first, bool pair) { return mode == 1 && (!first || pair); }
+
 // Constants of the pipelined march: depth D, ring lengths, and the LDS ring
 // of row entries (segments of P planes, the unroll period).
-template <int TX, int TY, int D>
+template <int TX, int TY, int D, int CY, bool HEAVY>
 struct Ring {
     static_assert(D >= 1 && D <= 2, "pipeline depth 1..2");
-    static constexpr int NT = TX * TY;                            // threads
+    static constexpr int NT = TX * TY / CY;                       // threads
     static constexpr int HPT = (8 * TX + 8 * TY + NT - 1) / NT;  // halo values per thread
     static constexpr int Q = D == 1 ? 10 : 12;                   // own-column ring, >= 9 + D
-    static constexpr int HA = HPT == 1 ? 4 + D : D;              // planes ahead at which the halo is loaded
+    static constexpr int HA = HPT <= CY && !HEAVY ? 4 + D : D;   // planes ahead at which the halo is loaded
     static constexpr int VD = D + 1;                             // V / base ring slots
     static constexpr int P = clcm(clcm(clcm(clcm(Q, D), VD), 2), HA);
     static constexpr int RY = TY + 8;                            // rows of a plane, halo included
@@ -160,9 +164,11 @@ struct Ring {
 //   - issues the data loads of plane k+4+D (own column), of the halo of plane
 //     k+HA and of V and base at plane k+D,
 //   - computes plane k from data that arrived during earlier steps.
-// HA = 4+D when each thread carries one halo value (the halo of a plane is
-// then loaded in the same step as the plane's own columns, by this and by
-// the neighbouring workgroups, while the lines are in L2), else HA = D.
+// HA = 4+D when each thread carries one halo value per column (the halo of a
+// plane is then loaded in the same step as the plane's own columns, by this
+// and by the neighbouring workgroups, while the lines are in L2), else HA = D;
+// the FP64 stages with another operand take HA = D too (16 registers, the
+// difference between 2 and 3 waves per SIMD at 16 x 16).
 // All rings are indexed by compile-time constants after unrolling the step
 // loop by a common period, so no register is moved while its load is in
 // flight.  FIRST: base == in, whose value at the point is the centre tap.
@@ -179,16 +185,16 @@ struct Ring {
 // Taylor stage of the 3.05 M-point sphere with 64 orbitals 1.88 -> 1.79 ms
 // (32 x 16, depth 2) and 1.81 -> 1.65 ms with the best tile of each form;
 // 96^3 cube, 8 orbitals 77 -> 64 us; 48 uneven spheres 2.6 -> 1.8 ms.
-template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
-          bool PAIR>
+template <bool NTS, int TX, int TY, int D, int CY, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK,
+          bool CS, bool PAIR>
 __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, const int n,
                                            typename CT<Tc>::c2 *tile, int4 *rowl, double2 &pacc) {
     using C2 = typename CT<Tc>::c2;
-    using R = Ring<TX, TY, D>;
+    using R = Ring<TX, TY, D, CY, std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, PAIR)>;
     constexpr int NT = R::NT, LX = TX + 8, HPT = R::HPT, Q = R::Q, HA = R::HA, HQ = R::HA, VD = R::VD, P = R::P;
     constexpr int RY = R::RY, SEG = R::SEG, RPT = R::RPT;
     constexpr int PLANE = (TY + 8) * LX;       // one plane buffer; tile holds two
-    const int t = threadIdx.x, lx = t % TX, ly = t / TX;
+    const int t = threadIdx.x, lx = t % TX, ly = t / TX * CY;
     const int x = it.x * TX + lx, y = it.y * TY + ly;
     const int64_t np = a.np;
     const auto rin = rsrc(static_cast<const Tin *>(a.in) + (int64_t)n * a.ldp, np * (int64_t)sizeof(Tin));
@@ -198,7 +204,7 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     const auto rv = rsrc(a.V, np * (int64_t)sizeof(Tc));
     const auto rm = rsrc(MASK ? a.mask : a.V, MASK ? np * 8 : 0);
     const auto rvi = rsrc(CS ? a.Vim : a.V, CS && a.Vim ? np * 8 : 0);
-    const Halo<TX, TY, HPT> hl(t, it);
+    const Halo<TX, TY, NT, HPT> hl(t, it);
 
     auto fetch = [&](unsigned c) -> C2 { return load_c<Tc, Tin>(rin, coff<Tin>(c)); };
     auto fetch_v = [&](unsigned c) -> Tc { return BL<Tc>::ld(rv, coff<Tc>(c)); };
@@ -244,36 +250,42 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     for (int j = 0; j < HPT; ++j) hrow[j] = hl.l[j] / LX;
     __syncthreads();
     const int4 *const pro = rowl + (SEG - 1) * (P * RY) + (P - 4 - D) * RY;  // entries of plane 0
-    C2 cv[Q];
-    unsigned oid[Q];
+    C2 cv[CY][Q];
+    unsigned oid[CY][Q];
 #pragma unroll
-    for (int j = 0; j < Q - 1; ++j) {
-        oid[j] = code_in_row(pro[(j - 4) * RY + ly + 4], x);
-        cv[j] = fetch(oid[j]);
+    for (int c = 0; c < CY; ++c) {
+#pragma unroll
+        for (int j = 0; j < Q - 1; ++j) {
+            oid[c][j] = code_in_row(pro[(j - 4) * RY + ly + 4 + c], x);
+            cv[c][j] = fetch(oid[c][j]);
+        }
+        cv[c][Q - 1] = C2{(Tc)0, (Tc)0};
+        oid[c][Q - 1] = CODE_OUT;
     }
-    cv[Q - 1] = C2{(Tc)0, (Tc)0};
-    oid[Q - 1] = CODE_OUT;
     C2 hal[HQ][HPT];
 #pragma unroll
     for (int d = 0; d < HQ; ++d)
 #pragma unroll
         for (int j = 0; j < HPT; ++j) hal[d][j] = fetch(halo_code(pro[d * RY + hrow[j]], hl.x[j], hl.ok[j] && d < nk));
-    Tc vr[VD], vir[VD];
-    double2 br[VD];
-    double mr[VD];
+    Tc vr[CY][VD], vir[CY][VD];
+    double2 br[CY][VD];
+    double mr[CY][VD];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        vr[d] = fetch_v(oid[4 + d]);
-        vir[d] = fetch_vi(oid[4 + d]);
-        br[d] = fetch_b(oid[4 + d]);
-        mr[d] = fetch_m(oid[4 + d]);
+    for (int c = 0; c < CY; ++c) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            vr[c][d] = fetch_v(oid[c][4 + d]);
+            vir[c][d] = fetch_vi(oid[c][4 + d]);
+            br[c][d] = fetch_b(oid[c][4 + d]);
+            mr[c][d] = fetch_m(oid[c][4 + d]);
+        }
+        vr[c][D] = (Tc)0;
+        vir[c][D] = (Tc)0;
+        br[c][D] = make_double2(0.0, 0.0);
+        mr[c][D] = 0.0;
     }
-    vr[D] = (Tc)0;
-    vir[D] = (Tc)0;
-    br[D] = make_double2(0.0, 0.0);
-    mr[D] = 0.0;
 
-    const FieldTerm ft(a, x, y);
+    const FieldTerm ft(a, x);
     const int own = (ly + 4) * LX + lx + 4;
     int slot = 0;  // LDS segment of the current period
 
@@ -291,7 +303,8 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
             // ring slot of plane k + m
 #define SLOT(m) ((s + (m) + 4 + Q) % Q)
             C2 *const pl = tile + (s % 2) * PLANE;  // plane buffer of this step
-            pl[own] = cv[SLOT(0)];
+#pragma unroll
+            for (int c = 0; c < CY; ++c) pl[own + c * LX] = cv[c][SLOT(0)];
 #pragma unroll
             for (int j = 0; j < HPT; ++j)
                 if (hl.ok[j]) pl[hl.l[j]] = hal[sh][j];
@@ -300,16 +313,26 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
             // loads around them
             if (s == 0) seg_load(b + 1);
             if (s == D + 2) seg_store(next);
-            const unsigned code_c = oid[SLOT(0)];
-            const Tc v_c = vr[sv];
-            const Tc vi_c = vir[sv];
-            const double2 b_c = br[sv];
-            const double m_c = mr[sv];
+            unsigned code_c[CY];
+            Tc v_c[CY], vi_c[CY];
+            double2 b_c[CY];
+            double m_c[CY];
+#pragma unroll
+            for (int c = 0; c < CY; ++c) {
+                code_c[c] = oid[c][SLOT(0)];
+                v_c[c] = vr[c][sv];
+                vi_c[c] = vir[c][sv];
+                b_c[c] = br[c][sv];
+                m_c[c] = mr[c][sv];
+            }
             __syncthreads();
             {
-                const unsigned cf = code_in_row(rs[s * RY + ly + 4], x);
-                oid[SLOT(4 + D)] = cf;
-                cv[SLOT(4 + D)] = fetch(cf);
+#pragma unroll
+                for (int c = 0; c < CY; ++c) {
+                    const unsigned cf = code_in_row(rs[s * RY + ly + 4 + c], x);
+                    oid[c][SLOT(4 + D)] = cf;
+                    cv[c][SLOT(4 + D)] = fetch(cf);
+                }
                 const bool hlive = k + HA < nk;
                 constexpr int back = 4 + D - HA;  // the halo's plane lies this far behind the own column's
 #pragma unroll
@@ -317,33 +340,46 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
                     const int4 e = s >= back ? rs[(s - back) * RY + hrow[j]] : rp[(P + s - back) * RY + hrow[j]];
                     hal[shl][j] = fetch(halo_code(e, hl.x[j], hl.ok[j] && hlive));
                 }
-                const unsigned cd = k + D < nk ? oid[SLOT(D)] : CODE_OUT;
-                vr[svn] = fetch_v(cd);
-                vir[svn] = fetch_vi(cd);
-                br[svn] = fetch_b(cd);
-                mr[svn] = fetch_m(cd);
+#pragma unroll
+                for (int c = 0; c < CY; ++c) {
+                    const unsigned cd = k + D < nk ? oid[c][SLOT(D)] : CODE_OUT;
+                    vr[c][svn] = fetch_v(cd);
+                    vir[c][svn] = fetch_vi(cd);
+                    br[c][svn] = fetch_b(cd);
+                    mr[c][svn] = fetch_m(cd);
+                }
             }
-            const C2 q0 = cv[SLOT(0)];
-            Tc lr, li;
-            {
-                const C2 xm1 = pl[own - 1], xp1 = pl[own + 1], xm2 = pl[own - 2], xp2 = pl[own + 2];
-                const C2 xm3 = pl[own - 3], xp3 = pl[own + 3], xm4 = pl[own - 4], xp4 = pl[own + 4];
-                const C2 ym1 = pl[own - LX], yp1 = pl[own + LX], ym2 = pl[own - 2 * LX], yp2 = pl[own + 2 * LX];
-                const C2 ym3 = pl[own - 3 * LX], yp3 = pl[own + 3 * LX], ym4 = pl[own - 4 * LX], yp4 = pl[own + 4 * LX];
-                const C2 zm1 = cv[SLOT(-1)], zp1 = cv[SLOT(1)], zm2 = cv[SLOT(-2)], zp2 = cv[SLOT(2)];
-                const C2 zm3 = cv[SLOT(-3)], zp3 = cv[SLOT(3)], zm4 = cv[SLOT(-4)], zp4 = cv[SLOT(4)];
-                lr = (Tc)3 * FD<Tc>::c0 * q0.x + FD<Tc>::c1 * ((xm1.x + xp1.x) + (ym1.x + yp1.x) + (zm1.x + zp1.x)) +
-                     FD<Tc>::c2 * ((xm2.x + xp2.x) + (ym2.x + yp2.x) + (zm2.x + zp2.x)) +
-                     FD<Tc>::c3 * ((xm3.x + xp3.x) + (ym3.x + yp3.x) + (zm3.x + zp3.x)) +
-                     FD<Tc>::c4 * ((xm4.x + xp4.x) + (ym4.x + yp4.x) + (zm4.x + zp4.x));
-                li = (Tc)3 * FD<Tc>::c0 * q0.y + FD<Tc>::c1 * ((xm1.y + xp1.y) + (ym1.y + yp1.y) + (zm1.y + zp1.y)) +
-                     FD<Tc>::c2 * ((xm2.y + xp2.y) + (ym2.y + yp2.y) + (zm2.y + zp2.y)) +
-                     FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (zm3.y + zp3.y)) +
-                     FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (zm4.y + zp4.y));
+            // rows y - 4 .. y + CY + 3 of this column: the thread's own rows
+            // from registers, the others from the plane
+            C2 yr[CY + 8];
+#pragma unroll
+            for (int r = 0; r < CY + 8; ++r)
+                yr[r] = r >= 4 && r < 4 + CY ? cv[r >= 4 && r < 4 + CY ? r - 4 : 0][SLOT(0)] : pl[own + (r - 4) * LX];
+#pragma unroll
+            for (int c = 0; c < CY; ++c) {
+                const C2 q0 = cv[c][SLOT(0)];
+                const C2 *const row = pl + own + c * LX;
+                Tc lr, li;
+                {
+                    const C2 xm1 = row[-1], xp1 = row[1], xm2 = row[-2], xp2 = row[2];
+                    const C2 xm3 = row[-3], xp3 = row[3], xm4 = row[-4], xp4 = row[4];
+                    const C2 ym1 = yr[c + 3], yp1 = yr[c + 5], ym2 = yr[c + 2], yp2 = yr[c + 6];
+                    const C2 ym3 = yr[c + 1], yp3 = yr[c + 7], ym4 = yr[c], yp4 = yr[c + 8];
+                    const C2 zm1 = cv[c][SLOT(-1)], zp1 = cv[c][SLOT(1)], zm2 = cv[c][SLOT(-2)], zp2 = cv[c][SLOT(2)];
+                    const C2 zm3 = cv[c][SLOT(-3)], zp3 = cv[c][SLOT(3)], zm4 = cv[c][SLOT(-4)], zp4 = cv[c][SLOT(4)];
+                    lr = (Tc)3 * FD<Tc>::c0 * q0.x + FD<Tc>::c1 * ((xm1.x + xp1.x) + (ym1.x + yp1.x) + (zm1.x + zp1.x)) +
+                         FD<Tc>::c2 * ((xm2.x + xp2.x) + (ym2.x + yp2.x) + (zm2.x + zp2.x)) +
+                         FD<Tc>::c3 * ((xm3.x + xp3.x) + (ym3.x + yp3.x) + (zm3.x + zp3.x)) +
+                         FD<Tc>::c4 * ((xm4.x + xp4.x) + (ym4.x + yp4.x) + (zm4.x + zp4.x));
+                    li = (Tc)3 * FD<Tc>::c0 * q0.y + FD<Tc>::c1 * ((xm1.y + xp1.y) + (ym1.y + yp1.y) + (zm1.y + zp1.y)) +
+                         FD<Tc>::c2 * ((xm2.y + xp2.y) + (ym2.y + yp2.y) + (zm2.y + zp2.y)) +
+                         FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (zm3.y + zp3.y)) +
+                         FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (zm4.y + zp4.y));
+                }
+                finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c[c], vi_c[c], b_c[c], m_c[c], ft,
+                                                                   a.axis == 1 ? y + c : z, code_c[c], rout, pacc);
             }
 #undef SLOT
-            finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, z, code_c, rout,
-                                                       pacc);
             // no barrier here: the next step writes the other plane buffer,
             // and every wave has finished reading it once all have passed
             // this step's barrier
@@ -378,7 +414,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     const auto rv = rsrc(a.V, np * (int64_t)sizeof(Tc));
     const auto rm = rsrc(MASK ? a.mask : a.V, MASK ? np * 8 : 0);
     const auto rvi = rsrc(CS ? a.Vim : a.V, CS && a.Vim ? np * 8 : 0);
-    const Halo<TX, TY, HPT> hl(t, it);
+    const Halo<TX, TY, NT, HPT> hl(t, it);
 
     auto fetch = [&](int idx, bool ok) -> C2 { return load_c<Tc, Tin>(rin, ok ? boff<Tin>(idx) : OOB); };
     auto fetch_v = [&](int idx) -> Tc { return BL<Tc>::ld(rv, boff<Tc>(idx)); };
@@ -417,7 +453,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     double2 b_c = fetch_b(idx_c);
     double m_c = fetch_m(idx_c);
 
-    const FieldTerm ft(a, x, y);
+    const FieldTerm ft(a, x);
     const int own = (ly + 4) * LX + lx + 4;
 
     for (int k = 0; k < nk; ++k) {
@@ -464,7 +500,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
                  FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (q[1].y + q[7].y)) +
                  FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (q[0].y + q[8].y));
         }
-        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, z, code_of(idx_c),
+        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, a.axis == 1 ? y : z, code_of(idx_c),
                                                        rout, pacc);
 #pragma unroll
         for (int j = 0; j < 8; ++j) q[j] = q[j + 1];
@@ -476,13 +512,30 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     }
 }
 
+// Columns per thread (in y) of a tile: two in the FP64 depth-1 march of the
+// widest tiles.  The thread's two rows share 8 of their 16 y taps and the
+// halo and address registers, so the 32 x 16 tile needs 256 threads of 242
+// VGPRs and two of them are resident per compute unit, 1024 columns in
+// flight instead of 768 (16 x 16 tiles) with half the x halo per column.
+// Stages that carry another operand (stage_heavy) would spill in that form;
+// they keep one column per thread at 32 x 16, and fit at 32 x 32 (512
+// threads, one halo value each).  Measured per stage:
+// 3.05 M-point sphere x 64 orbitals 1.65 (16 x 16) and 1.71 ms (32 x 16, one
+// column) -> 1.59 ms (32 x 16, two), 96^3 cube x 8 57 -> 52 us (32 x 32).
+constexpr int tile_cy(int TX, int TY, int D, bool fp64, bool heavy) {
+    return fp64 && D == 1 && (TX * TY == 1024 || (TX * TY == 512 && TX == 32 && !heavy)) ? 2 : 1;
+}
+template <int TX, int TY, int D, class Tc, int MODE, bool FIRST, bool PAIR>
+constexpr int stage_cy() {
+    return tile_cy(TX, TY, D, std::is_same<Tc, double>::value, stage_heavy(MODE, FIRST, PAIR));
+}
 // LDS row entries of a march (the lean one needs none).
-template <int TX, int TY, int D>
+template <int TX, int TY, int D, int CY, bool HEAVY>
 constexpr int march_rows() {
     if constexpr (D == 0)
         return 1;
     else
-        return Ring<TX, TY, D>::ROWS;
+        return Ring<TX, TY, D, CY, HEAVY>::ROWS;
 }
 
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
@@ -492,7 +545,8 @@ __device__ __forceinline__ void march(const KParams &a, const int4 it, const int
     if constexpr (D == 0)
         march_lean<NTS, TX, TY, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, pacc);
     else
-        march_ring<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, rowl, pacc);
+        march_ring<NTS, TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>(), Tin, Tc, Tout, MODE, FIRST, MASK, CS,
+                   PAIR>(a, it, n, tile, rowl, pacc);
 }
 
 // Sum of v over the workgroup (xor shuffles within each wave, then the wave
@@ -519,9 +573,10 @@ __device__ __forceinline__ double2 wg_sum(double2 v, double2 *lds) {
 
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK = false,
           bool CS = false, bool PAIR = false>
-__global__ void __launch_bounds__(TX * TY) k_stencil(KParams a) {
+__global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>()), 2) k_stencil(KParams a) {
     __shared__ typename CT<Tc>::c2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
-    __shared__ int4 rowl[march_rows<TX, TY, D>()];
+    __shared__ int4 rowl[march_rows<TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>(),
+                                    std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, PAIR)>()];
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     int n, item;
     block_item(a, blk, &n, &item);
@@ -534,7 +589,7 @@ __global__ void __launch_bounds__(TX * TY) k_stencil(KParams a) {
     if constexpr (PAIR) {
         // this workgroup's part of the pair sum, at its place in the launch
         // order (a fixed position, so the final sum has a fixed order)
-        const double2 s = wg_sum<TX * TY>(pacc, reinterpret_cast<double2 *>(tile));
+        const double2 s = wg_sum<TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>()>(pacc, reinterpret_cast<double2 *>(tile));
         if (threadIdx.x == 0) reinterpret_cast<double2 *>(a.pair_out)[blk] = s;
     }
 }
@@ -553,12 +608,13 @@ __global__ void __launch_bounds__(TX * TY) k_stencil(KParams a) {
 // the next launch (every workgroup has found every segment used up before
 // it counts itself done, so no item is taken after the reset).
 template <bool NTS, int TX, int TY, int D, bool FIRST>
-__global__ void __launch_bounds__(TX * TY) k_stencil_batch(const KParams *__restrict__ sysp,
+__global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, !FIRST)),
+                                         TX == 16 && TY == 16 && D == 1 && FIRST ? 3 : 2) k_stencil_batch(const KParams *__restrict__ sysp,
                                                            const BatchItem *__restrict__ items,
                                                            const int32_t *__restrict__ seg, double cre,
                                                            double cim, int32_t *ctr) {
     __shared__ double2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
-    __shared__ int4 rowl[march_rows<TX, TY, D>()];
+    __shared__ int4 rowl[march_rows<TX, TY, D, tile_cy(TX, TY, D, true, !FIRST), !FIRST>()];
     __shared__ int32_t next;
     const int home = blockIdx.x % kBatchQueues;
     for (int j = 0; j < kBatchQueues; ++j) {
@@ -592,32 +648,32 @@ __global__ void __launch_bounds__(TX * TY) k_stencil_batch(const KParams *__rest
 // shapes are mapped to these (see launch_stencil).
 template <bool NTS, int TX, int TY, int D>
 int launch_fp64_cs(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
-    constexpr int NT = TX * TY;
+    constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0 || a.mask || a.pair_y) return RSG_EUNSUPPORTED;
     if (a.mode == 0)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true><<<nb, N1, 0, s>>>(p);
     else if (a.first)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, true><<<nb, N1, 0, s>>>(p);
     else
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, false, true><<<nb, N2, 0, s>>>(p);
     return RSG_OK;
 }
 
 template <bool NTS, int TX, int TY, int D>
 int launch_fp64(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
-    constexpr int NT = TX * TY;
+    constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0) return RSG_EUNSUPPORTED;
     if (a.pair_y && !(a.mode == 1 && a.first && !a.mask)) return RSG_EUNSUPPORTED;
     if (a.mode == 0)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false><<<nb, N1, 0, s>>>(p);
     else if (a.pair_y)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, true><<<nb, N2, 0, s>>>(p);
     else if (a.first)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true><<<nb, N1, 0, s>>>(p);
     else if (a.mask)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, true><<<nb, N2, 0, s>>>(p);
     else
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false><<<nb, N2, 0, s>>>(p);
     return RSG_OK;
 }
 
@@ -647,7 +703,7 @@ int launch_fp32(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
 template <bool NTS, int TX, int TY, int D, bool FIRST>
 int launch_batch_inst(const KParams *sysp, const BatchItem *items, const int32_t *seg, int32_t nitems, double cre,
                       double cim, int32_t *ctr, int grid, hipStream_t s) {
-    constexpr int NT = TX * TY;
+    constexpr int NT = TX * TY / tile_cy(TX, TY, D, true, !FIRST);
     auto kern = k_stencil_batch<NTS, TX, TY, D, FIRST>;
     if (grid < 0) {
         int per_cu = 0, dev = 0;
@@ -675,9 +731,10 @@ int launch_batch_shape(bool first, const KParams *sysp, const BatchItem *items, 
 // tiles are not compiled: their rings spill past the register limit.)
 #define RSG_FP64_SHAPES(X) \
     X(8, 8, 1) X(8, 8, 2) X(16, 8, 1) X(16, 8, 2) X(32, 8, 1) X(32, 8, 2) X(16, 16, 1) \
-    X(16, 16, 2) X(32, 16, 1) X(32, 16, 2) X(64, 8, 1) X(64, 8, 2) X(32, 16, 0)
+    X(16, 16, 2) X(32, 16, 1) X(32, 16, 2) X(64, 8, 1) X(64, 8, 2) X(32, 16, 0) \
+    X(32, 32, 1)
 #define RSG_FP32_SHAPES(X) X(16, 8, 1) X(32, 8, 1) X(32, 8, 2) X(32, 16, 1) X(32, 16, 2) X(64, 8, 2)
-#define RSG_CS_SHAPES(X) X(8, 8, 1) X(16, 8, 1) X(16, 16, 1) X(32, 16, 1)
+#define RSG_CS_SHAPES(X) X(8, 8, 1) X(16, 8, 1) X(32, 8, 1) X(16, 16, 1) X(32, 16, 1)
 
 // One stencil stage over nb workgroups with the compiled kernel for the
 // tile shape and the stage's types (RSG_EUNSUPPORTED if there is none).
