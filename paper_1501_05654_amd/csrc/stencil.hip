@@ -26,30 +26,54 @@ std::vector<TileShape> tile_candidates(int compute) {
     return v;
 }
 
-// Measured on MI355X (sphere of 3.05 M points, 64 orbitals): 32 x 16 tiles,
-// depth 2, orbital-slowest order.  Smaller grids take the largest tile that
-// still gives every compute unit several workgroups, and z-chunks when even
-// the smallest tile does not.
+// Tile and z-chunk of a launch nobody tuned, by its points times orbitals.
+// A tile wants to be wide (halo lines per column: 32 x 8 1.5, 16 x 16 1.5,
+// 32 x 16 1.0) but a launch also wants enough workgroups: below 4 M values
+// the widest tiles leave compute units idle or pay for empty columns, and
+// z is cut so that about `items` workgroups start (each chunk re-reads 8
+// planes, which such batches find in cache) but no chunk is shorter than
+// `zmin` planes.  Chunks are cut equal, at the same planes for every tile
+// (ZM = 2), and two orbitals of a tile run side by side (BO = 2, V shared).
+// The lines come from timing every compiled tile with chunks of 1..96 planes
+// on 207 FP64 and 214 mixed systems (spheres 27 to 181 points across and
+// cubes of 20^3 to 120^3, 1..64 orbitals, both storages).  Time over that
+// system's best, geometric mean, FP64: this table 1.01-1.07 by size (worst
+// system 1.25), the fixed 32 x 16 / 32 x 8 / 16 x 8 choice before it
+// 1.03-1.26 (at 4-8 M values 16 x 8 tiles over the whole z-range 1.26); mixed
+// 1.01-1.05 against 1.02-1.39.
+namespace {
+struct ShapeRule {
+    double below;  // points x orbitals
+    int TX, TY, PD, items, zmin;
+};
+constexpr ShapeRule kRules64[] = {
+    {1e5, 32, 8, 1, 768, 1},    // latency: as many short marches as fit at once
+    {5e5, 32, 8, 1, 768, 2},
+    {4e6, 32, 8, 1, 1536, 6},   // enough chunks that the last round is full
+    {1e7, 16, 16, 1, 4096, 12}, // 3 workgroups a unit, still cache resident
+    {4e7, 32, 16, 1, 6144, 32}, // memory bound: least halo per column
+    {1e300, 32, 16, 1, 8192, 48},
+};
+constexpr ShapeRule kRules32[] = {
+    {5e5, 32, 8, 2, 768, 1},
+    {1e7, 16, 8, 1, 6144, 8},
+    {4e7, 32, 8, 2, 8192, 24},
+    {1e300, 32, 16, 1, 4096, 64},
+};
+}  // namespace
+
 TileShape default_shape(const Grid &g, int64_t nst, int compute) {
-    static const int pref[][3] = {{32, 16, 2}, {32, 8, 2}, {16, 8, 1}};
-    static const int pref32[][3] = {{32, 16, 2}, {32, 8, 2}, {16, 8, 1}};
-    TileShape sh{1, 16, 8, 0};
-    sh.PD = 1;
-    for (const auto &c : (compute == 0 ? pref : pref32)) {
-        const int64_t tiles = (int64_t)((g.n[0] + c[0] - 1) / c[0]) * ((g.n[1] + c[1] - 1) / c[1]);
-        sh.TX = c[0];
-        sh.TY = c[1];
-        sh.PD = c[2];
-        if (tiles * std::max<int64_t>(nst, 1) >= 2048) break;
-    }
-    sh.BO = 1;
-    sh.ZC = g.n[2];
-    // a grid with too few tiles to give every compute unit a few workgroups
-    // is also split along z, down to chunks of 2 planes (each chunk re-reads
-    // 8 planes, which such small batches find in cache)
-    const int64_t tiles = (int64_t)((g.n[0] + sh.TX - 1) / sh.TX) * ((g.n[1] + sh.TY - 1) / sh.TY);
-    const int64_t wgs = tiles * std::max<int64_t>(nst, 1);
-    if (wgs < 1024) sh.ZC = std::max<int>(2, (int)((int64_t)g.n[2] * wgs / 1024));
+    const double work = (double)g.npts * (double)std::max<int64_t>(nst, 1);
+    const ShapeRule *r = compute == 0 ? kRules64 : kRules32;
+    while (work >= r->below) ++r;
+    TileShape sh{1, r->TX, r->TY, 0};
+    sh.PD = r->PD;
+    sh.BO = 2;
+    const double tiles = (double)((g.n[0] + r->TX - 1) / r->TX) * ((g.n[1] + r->TY - 1) / r->TY) * (double)std::max<int64_t>(nst, 1);
+    const double zc = std::max<double>(r->zmin, g.n[2] * tiles / r->items);
+    const int chunks = std::max(1, (int)std::lround(g.n[2] / zc));
+    sh.ZC = (g.n[2] + chunks - 1) / chunks;
+    sh.ZM = chunks > 1 ? 2 : 0;
     return sh;
 }
 
