@@ -416,7 +416,7 @@ size_t rsg_batch_workspace_bytes(int32_t nsys, const rsg_system_desc *sys);
  * z-range, orbital) items (largest systems first; cut into one segment per
  * XCD, each workgroup taking items from its own XCD's segment first and
  * then from the others), with one projector
- * gather launch and one scatter launch per colour for all systems.  ws
+ * gather launch and one scatter launch for all systems.  ws
  * (rsg_batch_workspace_bytes) holds the work buffers and must outlive the
  * batch, as must every Hamiltonian and orbital array named in sys.  Results
  * are bitwise equal to propagating each system alone with its class's tile.

@@ -108,8 +108,7 @@ Ham::~Ham() {
     if (kb_p32) (void)hipFree(kb_p32);
     if (kb_E) (void)hipFree(kb_E);
     if (gather_items) (void)hipFree(gather_items);
-    for (auto *p : scatter_items)
-        if (p) (void)hipFree(p);
+    if (scatter_mem) (void)hipFree(scatter_mem);
 }
 
 namespace {
@@ -512,7 +511,7 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
                     mark[r] = a;
                 }
             // greedy colouring: atoms whose supports overlap get different
-            // colours, so one scatter launch never updates a point twice
+            // colours; a point adds its atoms in colour order
             std::vector<int> colour(natoms, -1);
             std::vector<std::vector<char>> used;
             for (int a = 0; a < natoms; ++a) {
@@ -528,12 +527,9 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
                 for (int64_t k = 0; k < H->kb_len[a]; ++k) used[c][idx_h[H->kb_off[a] + k]] = 1;
             }
             std::vector<int4> atoms(natoms);
-            std::vector<std::vector<int2>> sc(used.size());
             for (int a = 0; a < natoms; ++a) {
                 const int64_t padded = H->kb_off[a + 1] - H->kb_off[a];
                 atoms[a] = make_int4((int)H->kb_off[a], (int)padded, (int)H->kb_len[a], a);
-                for (int64_t k = 0; k < H->kb_len[a]; k += 16)
-                    sc[colour[a]].push_back(make_int2(a, (int)(H->kb_off[a] + k)));
             }
             if ((e = hipMalloc(&H->kb_idx, sizeof(int32_t) * total)) != hipSuccess) return fail("idx", e);
             if ((e = hipMalloc(&H->kb_p, sizeof(double) * 4 * total)) != hipSuccess) return fail("p", e);
@@ -549,18 +545,50 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
             if ((e = hipMemcpy(H->gather_items, atoms.data(), sizeof(int4) * natoms, hipMemcpyHostToDevice)) != hipSuccess)
                 return fail("atom upload", e);
             k_to_float<<<nblocks_for(4 * total), 256>>>(H->kb_p, H->kb_p32, 4 * total);
-            for (auto &v : sc) {
-                int2 *d = nullptr;
-                if (!v.empty()) {
-                    if ((e = hipMalloc(&d, sizeof(int2) * v.size())) != hipSuccess) return fail("scatter", e);
-                    if ((e = hipMemcpy(d, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice)) != hipSuccess) {
-                        (void)hipFree(d);
-                        return fail("scatter upload", e);
-                    }
+            ScatterHost sc;
+            for (int a = 0; a < natoms; ++a)
+                for (int64_t k = 0; k < H->kb_len[a]; ++k) mark[idx_h[H->kb_off[a] + k]] = -1;
+            build_scatter(idx_h, H->kb_off, H->kb_len, colour, mark, &sc);
+            // one allocation and one copy for all of its tables
+            const size_t nc = sc.entry.size();
+            size_t used_bytes = 0;
+            auto place_at = [&](size_t bytes) {
+                const size_t at = used_bytes;
+                used_bytes += rounded(bytes);
+                return at;
+            };
+            const size_t o_items = place_at(sizeof(int4) * sc.items.size()), o_pt = place_at(4 * sc.pt.size()),
+                         o_more = place_at(4 * sc.more.size()), o_place = place_at(4 * nc),
+                         o_atoms = place_at(4 * sc.atoms.size()), o_p = place_at(32 * nc), o_p32 = place_at(16 * nc);
+            std::vector<char> img(used_bytes, 0);
+            auto put = [&](size_t at, const auto &v) {
+                if (!v.empty()) std::memcpy(img.data() + at, v.data(), sizeof(v[0]) * v.size());
+            };
+            put(o_items, sc.items);
+            put(o_pt, sc.pt);
+            put(o_more, sc.more);
+            put(o_place, sc.place);
+            put(o_atoms, sc.atoms);
+            for (size_t k = 0; k < nc; ++k) {
+                const double *p = &p_h[4 * (size_t)sc.entry[k]];
+                double *d = reinterpret_cast<double *>(img.data() + o_p) + 4 * k;
+                float *f = reinterpret_cast<float *>(img.data() + o_p32) + 4 * k;
+                for (int i = 0; i < 4; ++i) {
+                    d[i] = p[i];
+                    f[i] = (float)p[i];
                 }
-                H->scatter_items.push_back(d);
-                H->scatter_counts.push_back((int32_t)v.size());
             }
+            if ((e = hipMalloc(&H->scatter_mem, used_bytes)) != hipSuccess) return fail("scatter", e);
+            if ((e = hipMemcpy(H->scatter_mem, img.data(), used_bytes, hipMemcpyHostToDevice)) != hipSuccess)
+                return fail("scatter upload", e);
+            H->scatter.items = (int4 *)(H->scatter_mem + o_items);
+            H->scatter.pt = (int32_t *)(H->scatter_mem + o_pt);
+            H->scatter.more = (int32_t *)(H->scatter_mem + o_more);
+            H->scatter.place = (int32_t *)(H->scatter_mem + o_place);
+            H->scatter.atoms = (int32_t *)(H->scatter_mem + o_atoms);
+            H->scatter_p = (double *)(H->scatter_mem + o_p);
+            H->scatter_p32 = (float *)(H->scatter_mem + o_p32);
+            H->scatter_n = (int32_t)sc.items.size();
         }
         if ((e = hipGetLastError()) != hipSuccess) return fail("conversion", e);
         if ((e = hipDeviceSynchronize()) != hipSuccess) return fail("sync", e);

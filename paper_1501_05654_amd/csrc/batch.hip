@@ -8,8 +8,7 @@
 // stencil launch over a list of (system, tile, z-range, orbital) items
 // (largest systems first, each sweeping its tiles orbital by orbital; the
 // list is cut into one contiguous segment per XCD, so that each XCD's L2
-// holds the halos its neighbouring tiles share), preceded by one projector gather launch and followed by one scatter launch
-// per colour, all systems at once.  A step sequence can be captured once into
+// holds the halos its neighbouring tiles share), preceded by one projector gather launch and followed by one scatter launch, all systems at once.  A step sequence can be captured once into
 // a HIP graph and replayed.  Each output point is computed by the same
 // arithmetic as the single-system path, so the results are bitwise equal to
 // propagating each system alone with its class's tile shape.
@@ -44,10 +43,8 @@ struct Batch {
     int32_t *ctr = nullptr;  // device work counters of the persistent stencil (zero between launches)
     int4 *gitems = nullptr;
     int32_t ngitems = 0;
-    int2 *sumitems = nullptr;  // projector chunk sums {system, block of 256 D entries}
-    int32_t nsumitems = 0;
-    std::vector<int4 *> sitems;  // scatter items per colour
-    std::vector<int32_t> nsitems;
+    int4 *sitems = nullptr;  // scatter items {system, its item, tile of 8 orbitals}
+    int32_t nsitems = 0;
     std::map<std::tuple<double, int64_t, hipStream_t>, hipGraphExec_t> graphs;
     void drop_graphs() {
         for (auto &kv : graphs) (void)hipGraphExecDestroy(kv.second);
@@ -70,14 +67,10 @@ struct Batch {
         if (ctr) (void)hipFree(ctr);
         ctr = nullptr;
         if (gitems) (void)hipFree(gitems);
-        if (sumitems) (void)hipFree(sumitems);
-        sumitems = nullptr;
-        nsumitems = 0;
-        for (auto *p : sitems)
-            if (p) (void)hipFree(p);
+        if (sitems) (void)hipFree(sitems);
         gitems = nullptr;
-        sitems.clear();
-        nsitems.clear();
+        sitems = nullptr;
+        nsitems = 0;
         drop_graphs();
     }
     ~Batch() { free_tables(); }
@@ -178,8 +171,7 @@ int build_class(Batch &b, size_t c, hipStream_t s) {
 int build_tables(Batch &b, hipStream_t s) {
     b.free_tables();
     std::vector<int4> gitems;
-    std::vector<int2> sumitems;
-    std::vector<std::vector<int4>> sitems;
+    std::vector<int4> sitems;
     std::vector<KParams> sp[4];
     std::vector<KbSys> kb[4];
     for (size_t i = 0; i < b.sys.size(); ++i) {
@@ -202,6 +194,8 @@ int build_tables(Batch &b, hipStream_t s) {
             ks.ncols = 2 * d.nst;
             ks.atoms = H.gather_items;
             ks.idx = H.kb_idx;
+            ks.tab = H.scatter;
+            ks.scatter_p = H.scatter_p;
             ks.p = H.kb_p;
             ks.E = H.kb_E;
             ks.D = (double *)b.D[i];
@@ -216,22 +210,8 @@ int build_tables(Batch &b, hipStream_t s) {
         for (int a = 0; a < H.natoms; ++a)
             for (int ct = 0; ct < nct; ++ct)
                 for (int ch = 0; ch < nchunk; ++ch) gitems.push_back(make_int4((int)i, a, ct, ch));
-        if (nchunk > 1) {
-            const int64_t nd = (int64_t)H.natoms * 4 * 2 * d.nst;
-            for (int64_t blk = 0; blk < (nd + 255) / 256; ++blk) sumitems.push_back(make_int2((int)i, (int)blk));
-        }
-        if (H.natoms > 0) {
-            // host copy of this system's scatter lists, per colour
-            for (size_t c = 0; c < H.scatter_items.size(); ++c) {
-                if (sitems.size() <= c) sitems.resize(c + 1);
-                std::vector<int2> v(H.scatter_counts[c]);
-                if (!v.empty())
-                    RSG_CHECK_HIP(hipMemcpy(v.data(), H.scatter_items[c], sizeof(int2) * v.size(),
-                                            hipMemcpyDeviceToHost));
-                for (const int2 &e : v)
-                    for (int ct = 0; ct < nct; ++ct) sitems[c].push_back(make_int4((int)i, e.x, e.y, ct));
-            }
-        }
+        for (int32_t j = 0; j < H.scatter_n; ++j)
+            for (int ot = 0; ot < (int)((d.nst + 7) / 8); ++ot) sitems.push_back(make_int4((int)i, j, ot, 0));
     }
     // the stage outputs of all systems together decide the store policy
     double out_bytes = 0;
@@ -245,15 +225,9 @@ int build_tables(Batch &b, hipStream_t s) {
     const std::vector<int32_t> ctr0(kBatchQueues + 1, 0);  // lives until the stream synchronisation below
     if ((rc = upload(&b.ctr, ctr0, s))) return rc;
     if ((rc = upload(&b.gitems, gitems, s))) return rc;
-    if ((rc = upload(&b.sumitems, sumitems, s))) return rc;
+    if ((rc = upload(&b.sitems, sitems, s))) return rc;
     b.ngitems = (int32_t)gitems.size();
-    b.nsumitems = (int32_t)sumitems.size();
-    for (auto &v : sitems) {
-        int4 *dptr = nullptr;
-        if ((rc = upload(&dptr, v, s))) return rc;
-        b.sitems.push_back(dptr);
-        b.nsitems.push_back((int32_t)v.size());
-    }
+    b.nsitems = (int32_t)sitems.size();
     RSG_CHECK_HIP(hipStreamSynchronize(s));
     for (size_t c = 0; c < b.cls.size(); ++c)
         if ((rc = build_class(b, c, s))) return rc;
@@ -277,15 +251,11 @@ int stage_launches(const Batch &b, int k, double dt, hipStream_t s) {
     const std::complex<double> c = std::complex<double>(0.0, dt) / taylor4_roots()[k];
     int rc;
     if ((rc = launch_kb_gather_batch(b.kb[k], b.gitems, b.ngitems, s))) return rc;
-    if ((rc = launch_kb_gather_sum_batch(b.kb[k], b.sumitems, b.nsumitems, s))) return rc;
     // the classes' launches share the work counters: they run one after the
     // other on this stream, and each leaves the counters zero
     for (const auto &cl : b.cls)
         if ((rc = class_launch(b, cl, k, c.real(), c.imag(), s))) return rc;
-    for (size_t ci = 0; ci < b.sitems.size(); ++ci)
-        if ((rc = launch_kb_scatter_batch(b.kb[k], b.sitems[ci], b.nsitems[ci], c.real(), c.imag(), s)))
-            return rc;
-    return RSG_OK;
+    return launch_kb_scatter_batch(b.kb[k], b.sitems, b.nsitems, c.real(), c.imag(), s);
 }
 
 int steps(const Batch &b, double dt, int64_t nsteps, hipStream_t s) {

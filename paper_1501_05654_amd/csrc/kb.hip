@@ -14,10 +14,12 @@
 // where cols are the 2*nst real columns (re and im of each orbital).  The
 // batch is orbital-major: real column col of point r sits at
 // (col / 2) * ldo + 2 r + col % 2 (in reals), ldo = 2 ldp.
-// Both run on v_mfma_{f64,f32}_16x16x4: the gather puts 16 columns on M,
-// 4 support points on K and the 4 projectors on N (zero-padded to 16); the
-// scatter puts 16 support points on M, the 4 projectors on K and 16
-// columns on N, which fills the instruction exactly.
+// The gather runs on v_mfma_{f64,f32}_16x16x4: 16 columns on M, 4 support
+// points on K and the 4 projectors on N (zero-padded to 16).  The scatter is
+// bound by the points it reads and writes (8 multiply-adds per 32 bytes), so
+// it goes by point, not by atom: every point of the union of all supports is
+// updated once, by one thread per orbital, with all the projectors that cover
+// it.
 //
 // MFMA operand layout (lane l of a wave of 64), measured on gfx950:
 //   A[i][k] in lane i + 16k, B[k][j] in lane j + 16k;
@@ -26,9 +28,9 @@
 //     i = 4(l/16) + r    for v_mfma_f32_16x16x4f32.
 //
 // Supports are padded to a multiple of 16 entries with p = 0 (and a valid
-// index); padded entries contribute zero and are never written.  Atoms whose
-// supports overlap are scattered in different launches (colours), so no two
-// lanes of one launch update the same point: the result is deterministic
+// index); padded entries contribute zero and are never written.  Atoms are
+// coloured so that supports of one colour are disjoint; a point covered by
+// several atoms adds them in colour order, so the result is deterministic
 // without atomics.
 #include "rsg_internal.h"
 
@@ -61,11 +63,14 @@ __device__ __forceinline__ f4_t mfma16(float a, float b, f4_t c) {
 // split its chunk (wave w takes groups w, w+GW, ... of the chunk; each wave
 // accumulates its groups in ascending order) and the partial products are
 // added in wave order.  With one chunk the result goes to D scaled by h^3;
-// with several, each chunk's sum goes to the partial buffer P and
-// k_kb_gather_sum adds the chunks in order.  Either way the result does not
+// with several, each chunk's sum goes to the partial buffer P and the
+// scatter adds the chunks in order.  Either way the result does not
 // depend on timing.  The group loop issues the index loads of GU groups,
 // then their data loads, then the MFMAs, so GU gathers are in flight per
 // wave.
+constexpr int SP = 32;              // lanes of a scatter workgroup along the points
+constexpr int SJ = kScatterPoints / SP;  // points per lane
+constexpr int SA = 16;              // atoms staged at a time
 constexpr int GW = 16;  // waves per gather workgroup
 constexpr int GU = 4;   // groups in flight per wave
 template <class Tin, class Tc>
@@ -141,101 +146,146 @@ __global__ void __launch_bounds__(GW * 64) k_kb_gather(const Tin *__restrict__ i
                          (int)blockIdx.z, (int)gridDim.z, P);
 }
 
-// D[a][i][c] = h3 * sum over chunks k = 0, 1, ... of P[a][i][k][c].
+// F[i] = c E_i D[a][i][n], D = h3 * (the chunk partials added in order).
 template <class Tc>
-__global__ void __launch_bounds__(256) k_kb_gather_sum(const Tc *__restrict__ P, Tc *__restrict__ D,
-                                                       int64_t nrows, int nchunk, int64_t ncols, Tc h3) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nrows * ncols) return;
-    const int64_t row = t / ncols, c = t - row * ncols;
-    const Tc *q = P + row * nchunk * ncols + c;
-    // loads of 8 chunks in flight, added in chunk order
-    Tc v = q[0];
-    int k = 1;
-    for (; k + 8 <= nchunk; k += 8) {
-        Tc x[8];
+__device__ __forceinline__ typename cpx<Tc>::type scatter_coef(const Tc *__restrict__ D, const Tc *__restrict__ P,
+                                                               int nchunk, Tc h3, const double *__restrict__ E,
+                                                               int64_t ncols, int a, int i, int64_t n, double cre,
+                                                               double cim) {
+    const int64_t row = (int64_t)a * 4 + i;
+    using C2 = typename cpx<Tc>::type;
+    C2 d;
+    if (nchunk == 1) {
+        d = *reinterpret_cast<const C2 *>(D + row * ncols + 2 * n);
+    } else {
+        // loads of 8 chunks in flight, added in chunk order
+        const Tc *q = P + row * nchunk * ncols + 2 * n;
+        d = *reinterpret_cast<const C2 *>(q);
+        int k = 1;
+        for (; k + 8 <= nchunk; k += 8) {
+            C2 x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = q[(int64_t)(k + u) * ncols];
+            for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const C2 *>(q + (int64_t)(k + u) * ncols);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += x[u];
+            for (int u = 0; u < 8; ++u) {
+                d.x += x[u].x;
+                d.y += x[u].y;
+            }
+        }
+        for (; k < nchunk; ++k) {
+            const C2 x = *reinterpret_cast<const C2 *>(q + (int64_t)k * ncols);
+            d.x += x.x;
+            d.y += x.y;
+        }
+        d.x = h3 * d.x;
+        d.y = h3 * d.y;
     }
-    for (; k < nchunk; ++k) v += q[(int64_t)k * ncols];
-    D[row * ncols + c] = h3 * v;
+    const double e = E[row];
+    C2 f;
+    f.x = (Tc)(e * (cre * (double)d.x - cim * (double)d.y));
+    f.y = (Tc)(e * (cre * (double)d.y + cim * (double)d.x));
+    return f;
 }
 
-
-// Scatter for one (16-entry support tile, 16-column tile), one wave.
+// Scatter for one item (up to SP points of one owner atom) and 8 orbitals:
+// lane e of 32 takes points e, e + 32, ..., so that a half-wave covers runs of
+// consecutive points of one orbital.  The coefficients of the item's atoms (its owner and
+// the atoms that overlap it there) are staged in LDS, SA atoms at a time.
+// Latency bound on small systems, where the chunk sums and every colour were
+// launches of their own: 2.0 + 2 x 3.6 us -> 5.0 us (2 atoms x 5 orbitals, 17 k
+// points), 4.8 + 2 x 4.9 -> 7.2 us (3 x 7, 500 k); 16 atoms x 64 orbitals
+// (3.05 M) 4.8 + 2 x 29.7 -> 49.9 us; 48 spheres 129 -> 110 us a stage.
+// 32 points an item: 6.6, 65 and 142 us; 128: 9.2, 49 and 104 us.
 template <class Tout, class Tc>
-__device__ __forceinline__ void scatter_tile(Tout *__restrict__ out, int64_t ldo, int64_t ncols,
-                                             const int2 itm, const int4 at, int ct,
-                                             const int32_t *__restrict__ idx,
-                                             const Tc *__restrict__ p,
-                                             const double *__restrict__ E,
-                                             const Tc *__restrict__ D, double cre, double cim,
-                                             const double *__restrict__ mask, Tc (*buf)[17]) {
-    using V = typename V4<Tc>::type;
-    const int l = threadIdx.x & 63;
-    const int lo = l & 15, hi = l >> 4;
-    const Tc av = p[((int64_t)itm.y + lo) * 4 + hi];
-    const int64_t col = (int64_t)ct * 16 + lo;
-    Tc bv = 0;
-    if (col < ncols) {
-        const int64_t n = col >> 1;
-        const double dre = (double)D[((int64_t)itm.x * 4 + hi) * ncols + 2 * n];
-        const double dim = (double)D[((int64_t)itm.x * 4 + hi) * ncols + 2 * n + 1];
-        const double e = E[itm.x * 4 + hi];
-        bv = (Tc)((col & 1) ? e * (cre * dim + cim * dre) : e * (cre * dre - cim * dim));
+__device__ __forceinline__ void scatter_points(Tout *__restrict__ out, int64_t ldo, int64_t ncols, const int4 it, int ct,
+                                               const ScatterTab &tab, const Tc *__restrict__ p,
+                                               const double *__restrict__ E, const Tc *__restrict__ D,
+                                               const Tc *__restrict__ P, int nchunk, Tc h3, double cre, double cim,
+                                               const double *__restrict__ mask,
+                                               typename cpx<Tc>::type (*sF)[4][8]) {
+    using O2 = typename cpx<Tout>::type;
+    const int t = threadIdx.x, o = t / SP;
+    const int64_t nst = ncols >> 1, n = (int64_t)ct * 8 + o;
+    O2 *const col = reinterpret_cast<O2 *>(out + (n < nst ? n : 0) * ldo);
+    // the owner's contribution (the first of every point) is requested with
+    // the point itself; only points under several atoms walk a list
+    int pt[SJ], c[SJ], c1[SJ];
+    Tc po[SJ][4];
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) {
+        const int e = (t & (SP - 1)) + j * SP;
+        const bool live = e < it.y && n < nst;
+        const int k = live ? it.x + e : it.x;
+        pt[j] = live ? tab.pt[k] : -1;
+        c[j] = tab.more[k];
+        c1[j] = live ? tab.more[k + 1] : c[j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) po[j][i] = p[(int64_t)k * 4 + i];
     }
-    V zero = {0, 0, 0, 0};
-    const V acc = mfma16(av, bv, zero);
-    // the 16 x 16 tile (support entry x column) through this wave's LDS
-    // slice, so that each lane then adds one complex value: a wave covers
-    // 16 consecutive entries of 4 orbitals per pass (256-byte runs where the
-    // support's points are consecutive)
+    O2 v[SJ];
+    double m[SJ];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) buf[acc_row(Tc(0), hi, r)][lo] = acc[r];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int64_t end = (int64_t)at.x + at.z;
-    const int el = l & 15;
-    const int64_t e = (int64_t)itm.y + el;
-    const int64_t pt = e < end ? idx[e] : 0;
-    const double m = (mask && e < end) ? mask[pt] : 1.0;
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int o = (l >> 4) + 4 * pass;  // orbital within the column tile
-        const int64_t c = (int64_t)ct * 16 + 2 * o;
-        if (e < end && c < ncols) {
-            Tout *dst = out + (c >> 1) * ldo + 2 * pt;
-            const double are = (double)buf[el][2 * o], aim = (double)buf[el][2 * o + 1];
-            const double addr = mask ? m * are : are, addi = mask ? m * aim : aim;
-            dst[0] = (Tout)((double)dst[0] + addr);
-            dst[1] = (Tout)((double)dst[1] + addi);
+    for (int j = 0; j < SJ; ++j) {
+        v[j] = O2{};
+        m[j] = 1.0;
+        if (pt[j] >= 0) {
+            v[j] = col[pt[j]];
+            if (mask) m[j] = mask[pt[j]];
         }
     }
+    auto add = [&](O2 &y, double mk, const Tc (&pv)[4], int slot) {
+        Tc re = 0, im = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            re += pv[i] * sF[slot][i][o].x;
+            im += pv[i] * sF[slot][i][o].y;
+        }
+        const double ar = mask ? mk * (double)re : (double)re, ai = mask ? mk * (double)im : (double)im;
+        y.x = (Tout)((double)y.x + ar);
+        y.y = (Tout)((double)y.y + ai);
+    };
+    for (int b0 = 0; b0 < it.w; b0 += SA) {
+        const int nb = min(SA, it.w - b0);
+        for (int j = t; j < nb * 32; j += SP * 8) {
+            const int64_t nn = (int64_t)ct * 8 + (j & 7);
+            if (nn < nst)
+                sF[j >> 5][(j >> 3) & 3][j & 7] = scatter_coef<Tc>(D, P, nchunk, h3, E, ncols, tab.atoms[it.z + b0 + (j >> 5)],
+                                                                   (j >> 3) & 3, nn, cre, cim);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SJ; ++j) {
+            if (b0 == 0) add(v[j], m[j], po[j], 0);
+            for (; c[j] < c1[j]; ++c[j]) {
+                const int q = tab.place[c[j]];
+                if (q >= b0 + nb) break;
+                Tc pv[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pv[i] = p[(int64_t)c[j] * 4 + i];
+                add(v[j], m[j], pv, q - b0);
+            }
+        }
+        if (b0 + SA < it.w) __syncthreads();  // the next atoms overwrite the coefficients
+    }
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+        if (pt[j] >= 0) col[pt[j]] = v[j];
 }
 
-// One wave per (16-entry support tile, 16-column tile).
+// blockIdx.x = item, blockIdx.y = tile of 8 orbitals.
 template <class Tout, class Tc>
-__global__ void __launch_bounds__(256) k_kb_scatter(Tout *__restrict__ out, int64_t ldo, int64_t ncols,
-                                                    const int2 *__restrict__ items, int32_t nitems,
-                                                    const int4 *__restrict__ atoms,
-                                                    const int32_t *__restrict__ idx,
-                                                    const Tc *__restrict__ p,
-                                                    const double *__restrict__ E,
-                                                    const Tc *__restrict__ D, double cre,
-                                                    double cim, const double *__restrict__ mask) {
-    __shared__ Tc buf[4][16][17];  // one 16 x 16 tile per wave (padded rows)
-    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (item >= nitems) return;
-    const int2 itm = items[item];  // {atom, first entry}
-    scatter_tile<Tout, Tc>(out, ldo, ncols, itm, atoms[itm.x], blockIdx.y, idx, p, E, D, cre, cim, mask,
-                           buf[threadIdx.x >> 6]);
+__global__ void __launch_bounds__(SP * 8) k_kb_scatter(Tout *__restrict__ out, int64_t ldo, int64_t ncols,
+                                                       ScatterTab tab, const Tc *__restrict__ p,
+                                                       const double *__restrict__ E, const Tc *__restrict__ D,
+                                                       const Tc *__restrict__ P, int nchunk, Tc h3, double cre,
+                                                       double cim, const double *__restrict__ mask) {
+    __shared__ typename cpx<Tc>::type sF[SA][4][8];
+    scatter_points<Tout, Tc>(out, ldo, ncols, tab.items[blockIdx.x], blockIdx.y, tab, p, E, D, P, nchunk, h3, cre, cim,
+                             mask, sF);
 }
 
 // Batched forms over many systems (FP64): item {system, atom, column tile}
-// for the gather, {system, atom, first entry, column tile} for the scatter.
+// for the gather, {system, scatter item, orbital tile} for the scatter.
 __global__ void __launch_bounds__(GW * 64) k_kb_gather_batch(const KbSys *__restrict__ sys,
                                                              const int4 *__restrict__ items) {
     __shared__ double red[GW][64][4];
@@ -245,41 +295,13 @@ __global__ void __launch_bounds__(GW * 64) k_kb_gather_batch(const KbSys *__rest
                                 red, it.w, s.nchunk, s.P);
 }
 
-// Same sum as k_kb_gather_sum, one workgroup per {system, block of 256 D
-// entries}.
-__global__ void __launch_bounds__(256) k_kb_gather_sum_batch(const KbSys *__restrict__ sys,
-                                                             const int2 *__restrict__ items) {
-    const int2 it = items[blockIdx.x];
+__global__ void __launch_bounds__(SP * 8) k_kb_scatter_batch(const KbSys *__restrict__ sys,
+                                                             const int4 *__restrict__ items, double cre, double cim) {
+    __shared__ double2 sF[SA][4][8];
+    const int4 it = items[blockIdx.x];
     const KbSys &s = sys[it.x];
-    const int64_t ncols = s.ncols, nrows = (int64_t)s.natoms * 4;
-    const int64_t t = (int64_t)it.y * 256 + threadIdx.x;
-    if (t >= nrows * ncols) return;
-    const int64_t row = t / ncols, c = t - row * ncols;
-    const int nchunk = s.nchunk;
-    const double *q = s.P + row * nchunk * ncols + c;
-    double v = q[0];
-    int k = 1;
-    for (; k + 8 <= nchunk; k += 8) {
-        double x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = q[(int64_t)(k + u) * ncols];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v += x[u];
-    }
-    for (; k < nchunk; ++k) v += q[(int64_t)k * ncols];
-    s.D[row * ncols + c] = s.h3 * v;
-}
-
-__global__ void __launch_bounds__(256) k_kb_scatter_batch(const KbSys *__restrict__ sys,
-                                                          const int4 *__restrict__ items, int32_t nitems,
-                                                          double cre, double cim) {
-    __shared__ double buf[4][16][17];  // one 16 x 16 tile per wave (padded rows)
-    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (item >= nitems) return;
-    const int4 it = items[item];
-    const KbSys &s = sys[it.x];
-    scatter_tile<double, double>(s.out, s.ldo, s.ncols, make_int2(it.y, it.z), s.atoms[it.y], it.w, s.idx,
-                                 s.p, s.E, s.D, cre, cim, nullptr, buf[threadIdx.x >> 6]);
+    scatter_points<double, double>(s.out, s.ldo, s.ncols, s.tab.items[it.y], it.z, s.tab, s.scatter_p, s.E, s.D, s.P, s.nchunk,
+                                   s.h3, cre, cim, nullptr, sF);
 }
 
 }  // namespace
@@ -322,15 +344,11 @@ int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_
     const double h3 = H.g->h * H.g->h * H.g->h;
     // the partials start at the first 256-byte boundary after D (FP64 size)
     void *P = nchunk > 1 ? (void *)((char *)D + gather_partials_offset(H, nst)) : nullptr;
-    const int64_t nrows = (int64_t)H.natoms * 4;
-    const unsigned sblk = (unsigned)((nrows * ncols + 255) / 256);
     if (compute == 0) {
         if (in_t != 0) return RSG_EUNSUPPORTED;
         k_kb_gather<double, double><<<grid, GW * 64, 0, s>>>((const double *)in, 2 * ldp, ncols,
                                                         H.gather_items, H.kb_idx, H.kb_p, h3,
                                                         (double *)D, (double *)P);
-        if (nchunk > 1)
-            k_kb_gather_sum<double><<<sblk, 256, 0, s>>>((const double *)P, (double *)D, nrows, nchunk, ncols, h3);
     } else {
         if (in_t == 0)
             k_kb_gather<double, float><<<grid, GW * 64, 0, s>>>((const double *)in, 2 * ldp, ncols,
@@ -340,9 +358,6 @@ int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_
             k_kb_gather<float, float><<<grid, GW * 64, 0, s>>>((const float *)in, 2 * ldp, ncols,
                                                           H.gather_items, H.kb_idx, H.kb_p32,
                                                           (float)h3, (float *)D, (float *)P);
-        if (nchunk > 1)
-            k_kb_gather_sum<float><<<sblk, 256, 0, s>>>((const float *)P, (float *)D, nrows, nchunk, ncols,
-                                                        (float)h3);
     }
     RSG_CHECK_HIP(hipGetLastError());
     return RSG_OK;
@@ -350,29 +365,89 @@ int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_
 
 int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t nst, int64_t ldp,
                       const void *D, double cre, double cim, const double *mask, hipStream_t s) {
-    if (H.natoms == 0 || nst == 0) return RSG_OK;
+    if (H.natoms == 0 || nst == 0 || H.scatter_n == 0) return RSG_OK;
     const int64_t ncols = 2 * nst;
-    for (size_t c = 0; c < H.scatter_items.size(); ++c) {
-        const int32_t n = H.scatter_counts[c];
-        if (n == 0) continue;
-        const dim3 grid((unsigned)((n + 3) / 4), (unsigned)((ncols + 15) / 16));
-        if (compute == 0) {
-            if (out_t != 0) return RSG_EUNSUPPORTED;
-            k_kb_scatter<double, double><<<grid, 256, 0, s>>>(
-                (double *)out, 2 * ldp, ncols, H.scatter_items[c], n, H.gather_items, H.kb_idx,
-                H.kb_p, H.kb_E, (const double *)D, cre, cim, mask);
-        } else if (out_t == 0) {
-            k_kb_scatter<double, float><<<grid, 256, 0, s>>>(
-                (double *)out, 2 * ldp, ncols, H.scatter_items[c], n, H.gather_items, H.kb_idx,
-                H.kb_p32, H.kb_E, (const float *)D, cre, cim, mask);
-        } else {
-            k_kb_scatter<float, float><<<grid, 256, 0, s>>>(
-                (float *)out, 2 * ldp, ncols, H.scatter_items[c], n, H.gather_items, H.kb_idx,
-                H.kb_p32, H.kb_E, (const float *)D, cre, cim, mask);
-        }
-        RSG_CHECK_HIP(hipGetLastError());
+    const int nchunk = gather_chunks(H, nst);
+    const double h3 = H.g->h * H.g->h * H.g->h;
+    const void *P = nchunk > 1 ? (const void *)((const char *)D + gather_partials_offset(H, nst)) : nullptr;
+    const dim3 grid((unsigned)H.scatter_n, (unsigned)((nst + 7) / 8));
+    if (compute == 0) {
+        if (out_t != 0) return RSG_EUNSUPPORTED;
+        k_kb_scatter<double, double><<<grid, SP * 8, 0, s>>>((double *)out, 2 * ldp, ncols, H.scatter, H.scatter_p, H.kb_E,
+                                                             (const double *)D, (const double *)P, nchunk, h3, cre,
+                                                             cim, mask);
+    } else if (out_t == 0) {
+        k_kb_scatter<double, float><<<grid, SP * 8, 0, s>>>((double *)out, 2 * ldp, ncols, H.scatter, H.scatter_p32, H.kb_E,
+                                                            (const float *)D, (const float *)P, nchunk, (float)h3, cre,
+                                                            cim, mask);
+    } else {
+        k_kb_scatter<float, float><<<grid, SP * 8, 0, s>>>((float *)out, 2 * ldp, ncols, H.scatter, H.scatter_p32, H.kb_E,
+                                                           (const float *)D, (const float *)P, nchunk, (float)h3, cre,
+                                                           cim, mask);
     }
+    RSG_CHECK_HIP(hipGetLastError());
     return RSG_OK;
+}
+
+// The scatter's tables (ScatterTab) from the padded supports and the atoms'
+// colours: the points of the union of all supports grouped by the first atom
+// in colour order that covers them, each with its atoms in colour order.
+// place: scratch of one entry per slot, all -1.
+void build_scatter(const std::vector<int32_t> &idx, const std::vector<int64_t> &off, const std::vector<int64_t> &len,
+                   const std::vector<int> &colour, std::vector<int32_t> &place, ScatterHost *t) {
+    const int natoms = (int)len.size();
+    std::vector<int> ord(natoms);
+    for (int a = 0; a < natoms; ++a) ord[a] = a;
+    std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return colour[a] < colour[b]; });
+    std::vector<int32_t> owner, extra;
+    for (auto *v : {&t->pt, &t->entry, &owner, &extra}) v->reserve(idx.size());
+    for (const int a : ord)
+        for (int64_t k = 0; k < len[a]; ++k) {
+            const int32_t r = idx[off[a] + k];
+            if (place[r] < 0) {
+                place[r] = (int32_t)t->pt.size();
+                t->pt.push_back(r);
+                owner.push_back(a);
+                extra.push_back(0);
+                t->entry.push_back((int32_t)(off[a] + k));
+            } else {
+                ++extra[place[r]];
+            }
+        }
+    const size_t n = t->pt.size();
+    t->more.assign(n + 1, (int32_t)n);
+    for (size_t u = 0; u < n; ++u) t->more[u + 1] = t->more[u] + extra[u];
+    t->entry.resize(t->more[n]);
+    t->place.assign(t->more[n], 0);
+    std::vector<int32_t> fill(t->more.begin(), t->more.end() - 1);
+    for (const int a : ord)
+        for (int64_t k = 0; k < len[a]; ++k) {
+            const int32_t u = place[idx[off[a] + k]];
+            if (owner[u] == a) continue;
+            t->entry[fill[u]] = (int32_t)(off[a] + k);
+            t->place[fill[u]++] = a;  // the atom for now
+        }
+    std::vector<int> rank(natoms), seen(natoms, -1);
+    for (int j = 0; j < natoms; ++j) rank[ord[j]] = j;
+    for (size_t u = 0; u < n;) {
+        size_t v = u + 1;
+        while (v < n && v - u < (size_t)kScatterPoints && owner[v] == owner[u]) ++v;
+        std::vector<int> list(1, owner[u]);  // the item's atoms in colour order, the owner first
+        seen[owner[u]] = (int)t->items.size();
+        for (int32_t c = t->more[u]; c < t->more[v]; ++c) {
+            const int a = t->place[c];
+            if (seen[a] != (int)t->items.size()) {
+                seen[a] = (int)t->items.size();
+                list.push_back(a);
+            }
+        }
+        std::sort(list.begin() + 1, list.end(), [&](int a, int b) { return rank[a] < rank[b]; });
+        for (int32_t c = t->more[u]; c < t->more[v]; ++c)
+            t->place[c] = (int32_t)(std::find(list.begin(), list.end(), t->place[c]) - list.begin());
+        t->items.push_back(make_int4((int)u, (int)(v - u), (int)t->atoms.size(), (int)list.size()));
+        t->atoms.insert(t->atoms.end(), list.begin(), list.end());
+        u = v;
+    }
 }
 
 int launch_kb_gather_batch(const KbSys *sys, const int4 *items, int32_t nitems, hipStream_t s) {
@@ -382,17 +457,10 @@ int launch_kb_gather_batch(const KbSys *sys, const int4 *items, int32_t nitems, 
     return RSG_OK;
 }
 
-int launch_kb_gather_sum_batch(const KbSys *sys, const int2 *items, int32_t nitems, hipStream_t s) {
-    if (nitems == 0) return RSG_OK;
-    k_kb_gather_sum_batch<<<(unsigned)nitems, 256, 0, s>>>(sys, items);
-    RSG_CHECK_HIP(hipGetLastError());
-    return RSG_OK;
-}
-
 int launch_kb_scatter_batch(const KbSys *sys, const int4 *items, int32_t nitems, double cre, double cim,
                             hipStream_t s) {
     if (nitems == 0) return RSG_OK;
-    k_kb_scatter_batch<<<(unsigned)((nitems + 3) / 4), 256, 0, s>>>(sys, items, nitems, cre, cim);
+    k_kb_scatter_batch<<<(unsigned)nitems, SP * 8, 0, s>>>(sys, items, cre, cim);
     RSG_CHECK_HIP(hipGetLastError());
     return RSG_OK;
 }

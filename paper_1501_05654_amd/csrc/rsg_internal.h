@@ -111,6 +111,26 @@ struct Grid {
 
 // ----------------------------------------------------------- Hamiltonian --
 
+// Projector scatter: the points of the union of all supports, each with the
+// atoms that cover it, in items of up to kScatterPoints points that share
+// their first atom.
+constexpr int kScatterPoints = 64;
+struct ScatterTab {
+    const int4 *items = nullptr;     // {first point, points, first of its atoms in `atoms`, atoms}
+    const int32_t *pt = nullptr;   // slot of each point
+    const int32_t *more = nullptr; // first contribution of each point beyond its owner's (points + 1 entries)
+    const int32_t *place = nullptr; // per contribution: its atom's place in the item's list (0 for an owner's)
+    const int32_t *atoms = nullptr; // the items' atoms in colour order, the owner first
+};
+// Contribution k < points is point k's owner's, the others follow by point in
+// colour order; entry: the support entry of each.
+struct ScatterHost {
+    std::vector<int4> items;
+    std::vector<int32_t> pt, more, place, atoms, entry;
+};
+void build_scatter(const std::vector<int32_t> &idx, const std::vector<int64_t> &off, const std::vector<int64_t> &len,
+                   const std::vector<int> &colour, std::vector<int32_t> &place, ScatterHost *t);
+
 struct Ham {
     Grid *g = nullptr;
     double kin = -0.5;
@@ -132,9 +152,11 @@ struct Ham {
     std::vector<int64_t> kb_off; // host [natoms+1] padded offsets
     std::vector<int64_t> kb_len; // host [natoms] true support sizes
     int4 *gather_items = nullptr;   // device: one per atom {offset, padded length, length, atom}
-    // scatter work: per colour a device list of {atom, entry0} (16 entries each)
-    std::vector<int2 *> scatter_items;
-    std::vector<int32_t> scatter_counts;
+    char *scatter_mem = nullptr;          // device tables of the projector scatter, one allocation:
+    ScatterTab scatter;
+    int32_t scatter_n = 0;                // its items
+    const double *scatter_p = nullptr;    // [contributions][4]: projector values in the scatter's order
+    const float *scatter_p32 = nullptr;   // FP32 copy
     // stencil tile shape per (nst, compute) chosen by rsg_autotune / rsg_set_tile
     std::map<std::pair<int64_t, int>, TileShape> tiles;
     TileShape tile_for(int64_t nst, int compute) const;
@@ -236,7 +258,8 @@ TileShape default_shape(const Grid &g, int64_t nst, int compute);
 std::vector<TileShape> tile_candidates(int compute);
 
 // KB projectors.  gather: D[a][i][col] = h^3 sum_e p[e][i] in(idx[e], col)
-// (col over the 2*nst real columns: re and im of each orbital); scatter:
+// (col over the 2*nst real columns: re and im of each orbital), or its
+// support-chunk partials, which the scatter adds; scatter:
 // out(idx[e], col) += sum_i p[e][i] (c E_i D[a][i][.])[col], times mask(idx[e])
 // when a mask is given.  Operands are orbital-major with ldp complex values
 // between orbitals.
@@ -253,6 +276,8 @@ struct KbSys {
     int64_t ldo, ncols; // 2*ldp (doubles between orbitals), 2*nst
     const int4 *atoms;  // {offset, padded length, length, atom}
     const int32_t *idx;
+    ScatterTab tab;
+    const double *scatter_p;
     const double *p;
     const double *E;
     double *D;          // [natoms][4][ncols]
@@ -267,8 +292,7 @@ int gather_chunks(const Ham &H, int64_t nst);
 size_t gather_partials_offset(const Ham &H, int64_t nst);
 // items {system, atom, column tile, chunk}
 int launch_kb_gather_batch(const KbSys *sys, const int4 *items, int32_t nitems, hipStream_t s);
-// items {system, block of 256 D entries}: D = h3 * sum of the chunk partials
-int launch_kb_gather_sum_batch(const KbSys *sys, const int2 *items, int32_t nitems, hipStream_t s);
+// items {system, scatter item, tile of 8 orbitals}
 int launch_kb_scatter_batch(const KbSys *sys, const int4 *items, int32_t nitems, double cre, double cim,
                             hipStream_t s);
 
