@@ -154,32 +154,7 @@ __device__ __forceinline__ typename cpx<Tc>::type scatter_coef(const Tc *__restr
                                                                double cim) {
     const int64_t row = (int64_t)a * 4 + i;
     using C2 = typename cpx<Tc>::type;
-    C2 d;
-    if (nchunk == 1) {
-        d = *reinterpret_cast<const C2 *>(D + row * ncols + 2 * n);
-    } else {
-        // loads of 8 chunks in flight, added in chunk order
-        const Tc *q = P + row * nchunk * ncols + 2 * n;
-        d = *reinterpret_cast<const C2 *>(q);
-        int k = 1;
-        for (; k + 8 <= nchunk; k += 8) {
-            C2 x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const C2 *>(q + (int64_t)(k + u) * ncols);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                d.x += x[u].x;
-                d.y += x[u].y;
-            }
-        }
-        for (; k < nchunk; ++k) {
-            const C2 x = *reinterpret_cast<const C2 *>(q + (int64_t)k * ncols);
-            d.x += x.x;
-            d.y += x.y;
-        }
-        d.x = h3 * d.x;
-        d.y = h3 * d.y;
-    }
+    const C2 d = kb_value<Tc>(D, P, nchunk, h3, ncols, row, n);
     const double e = E[row];
     C2 f;
     f.x = (Tc)(e * (cre * (double)d.x - cim * (double)d.y));
@@ -333,6 +308,19 @@ size_t kb_workspace_bytes(const Ham &H, int64_t nst) {
     const size_t d = (size_t)H.natoms * 4 * 2 * (size_t)nst * sizeof(double);
     const int nchunk = gather_chunks(H, nst);
     return nchunk > 1 ? 2 * ((d + 255) / 256 * 256) + (size_t)nchunk * d : d;
+}
+
+KbDot kb_dot(const Ham &H, int64_t nst, const void *D) {
+    KbDot k;
+    k.natoms = H.natoms;
+    if (H.natoms == 0) return k;
+    k.E = H.kb_E;
+    k.D = (const double *)D;
+    k.nchunk = gather_chunks(H, nst);
+    k.P = k.nchunk > 1 ? (const double *)((const char *)D + gather_partials_offset(H, nst)) : nullptr;
+    k.ncols = 2 * nst;
+    k.h3 = H.g->h * H.g->h * H.g->h;
+    return k;
 }
 
 int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_t nst, int64_t ldp,

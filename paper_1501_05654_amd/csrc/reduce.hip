@@ -154,6 +154,41 @@ __global__ void __launch_bounds__(RB) k_pair_final(const double2 *P, int64_t nb,
     if (t == 0) *g = 2.0 * h3 * acc;
 }
 
+// One workgroup per orbital: the stencil's partials of <psi|H_loc psi> by
+// strided sums and a fixed tree, then the projectors' E_i |D_i|^2 the same way
+// (h^3 <psi|p_i E_i D_i> = E_i |D_i|^2, so H psi itself is never written).
+__global__ void __launch_bounds__(RB) k_energy_final(const double2 *part, int64_t nitems, KbDot kb, double h3,
+                                                     double *out) {
+    __shared__ double red[RB][2];
+    const int64_t n = blockIdx.x;
+    const int t = threadIdx.x;
+    double re = 0.0, im = 0.0;
+    for (int64_t b = t; b < nitems; b += RB) {
+        re += part[n * nitems + b].x;
+        im += part[n * nitems + b].y;
+    }
+    re *= h3;
+    im *= h3;
+    for (int64_t r = t; r < (int64_t)kb.natoms * 4; r += RB) {
+        const double2 d = kb_value<double>(kb.D, kb.P, kb.nchunk, kb.h3, kb.ncols, r, n);
+        re += kb.E[r] * (d.x * d.x + d.y * d.y);
+    }
+    red[t][0] = re;
+    red[t][1] = im;
+    __syncthreads();
+    for (int w = RB / 2; w > 0; w >>= 1) {
+        if (t < w) {
+            red[t][0] += red[t + w][0];
+            red[t][1] += red[t + w][1];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        out[2 * n] = red[0][0];
+        out[2 * n + 1] = red[0][1];
+    }
+}
+
 struct PwArgs {
     const double2 *src[1];
     double2 *dst;
@@ -231,6 +266,13 @@ int launch_reduce(const Grid &g, int kind, int axis, const double2 *a, const dou
 
 int launch_pair_final(const double *P, int64_t nb, const double2 a[4], double h3, double *g, hipStream_t s) {
     k_pair_final<<<1, RB, 0, s>>>((const double2 *)P, nb, a[0], a[1], a[2], a[3], h3, g);
+    RSG_CHECK_HIP(hipGetLastError());
+    return RSG_OK;
+}
+
+int launch_energy_final(const double *part, int64_t nitems, int64_t nst, const KbDot &kb, double h3, double *out,
+                        hipStream_t s) {
+    k_energy_final<<<(unsigned)nst, RB, 0, s>>>((const double2 *)part, nitems, kb, h3, out);
     RSG_CHECK_HIP(hipGetLastError());
     return RSG_OK;
 }

@@ -176,6 +176,8 @@ template <> struct cpx<float> { using type = float2; };
 // in_t / out_t: 0 = complex128, 1 = complex64.  compute: 0 = FP64, 1 = FP32.
 // All operands are orbital-major with ldp complex values between orbitals;
 // base is always complex128.
+// DOT_T: no conjugation; DOT_H: conj(in) H in; DOT_ONLY: DOT_H, out not written.
+enum DotKind { DOT_NONE = 0, DOT_T = 1, DOT_H = 2, DOT_ONLY = 3 };
 struct StageArgs {
     const void *in = nullptr;
     const void *base = nullptr;
@@ -189,6 +191,10 @@ struct StageArgs {
     // place in the launch order (stencil_blocks entries).
     const void *pair_y = nullptr;
     double *pair_out = nullptr;
+    // H applications (mode 0, FP64): also sum in H in per orbital (DotKind)
+    // over the points, one complex partial per {orbital, item} in pair_out
+    // (stencil_blocks entries).
+    int dot = 0;
     int64_t nst = 0, ldp = 0;
     double field = 0;
     const double *field_dev = nullptr;
@@ -285,6 +291,14 @@ struct KbSys {
     int32_t nchunk, natoms;
     double h3;
 };
+// What a kernel needs to finish an orbital's <in|H in> from a gather's D.
+struct KbDot {
+    const double *E = nullptr, *D = nullptr, *P = nullptr;
+    int64_t ncols = 0;
+    int32_t natoms = 0, nchunk = 1;
+    double h3 = 0;
+};
+KbDot kb_dot(const Ham &H, int64_t nst, const void *D);
 // Support chunks of the projector gather for a batch of nst orbitals (the
 // single-system and batched paths use the same split, so they agree bit
 // for bit); the partials live in the projector workspace behind D.
@@ -336,6 +350,12 @@ int check_batch(const Ham *H, const void *p, int64_t nst, int64_t ldp, const cha
 // out = H(in) for an FP64 orbital-major batch; D: kb_workspace_bytes(H, nst).
 int hpsi_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp, double field,
               const double *field_dev, void *D, hipStream_t s);
+// The same without its projectors' scatter when kind is DOT_ONLY (out then is
+// not touched), and with the stencil's per-orbital sums of in H_loc in (kind;
+// H_loc: H without projectors) in part[nst][items], items = stencil_blocks / nst.
+// The projectors' part of the sums follows from their gather in D (kb_dot).
+int hdot_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp, double field, int kind, double *part,
+              void *D, hipStream_t s);
 // The four roots of the Taylor(4) polynomial sum_{k<=4} z^k/k!, largest
 // modulus first ({re, im} pairs), and whether a step of this handle in dtype
 // runs as the product of their linear factors (else as 1 + z times the
@@ -358,10 +378,43 @@ int launch_mul_axis(const Grid &g, int axis, const double2 *src, double2 *dst, i
 // P[4][nb] (complex) of the four adjoint stages, summed in a fixed order.
 int launch_pair_final(const double *P, int64_t nb, const double2 a[4], double h3, double *g, hipStream_t s);
 int launch_accumulate(const double *src, double *dst, hipStream_t s);
+// out[2n], out[2n+1] = h3 sum_k part[n][k] + sum_{a,i} E_i |D[a][i][n]|^2, in a fixed order.
+int launch_energy_final(const double *part, int64_t nitems, int64_t nst, const KbDot &kb, double h3, double *out,
+                        hipStream_t s);
 
 // Kernel timing hooks around stencil launches.
 void timing_before(hipStream_t s);
 void timing_after(hipStream_t s);
+
+// d = D[row][n] of a gather: the value itself, or h3 times its chunk partials
+// added in chunk order (loads of 8 chunks in flight).
+template <class Tc>
+__device__ __forceinline__ typename cpx<Tc>::type kb_value(const Tc *__restrict__ D, const Tc *__restrict__ P, int nchunk,
+                                                           Tc h3, int64_t ncols, int64_t row, int64_t n) {
+    using C2 = typename cpx<Tc>::type;
+    if (nchunk == 1) return *reinterpret_cast<const C2 *>(D + row * ncols + 2 * n);
+    const Tc *q = P + row * nchunk * ncols + 2 * n;
+    C2 d = *reinterpret_cast<const C2 *>(q);
+    int k = 1;
+    for (; k + 8 <= nchunk; k += 8) {
+        C2 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const C2 *>(q + (int64_t)(k + u) * ncols);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            d.x += x[u].x;
+            d.y += x[u].y;
+        }
+    }
+    for (; k < nchunk; ++k) {
+        const C2 x = *reinterpret_cast<const C2 *>(q + (int64_t)k * ncols);
+        d.x += x.x;
+        d.y += x.y;
+    }
+    d.x = h3 * d.x;
+    d.y = h3 * d.y;
+    return d;
+}
 
 }  // namespace rsg
 

@@ -46,6 +46,10 @@
 namespace rsg {
 namespace sk {
 
+// Sums a stage gathers on the way.
+enum { SUM_NONE = 0, SUM_PAIR = 1, SUM_TDOT = 2, SUM_HDOT = 3, SUM_ONLY = 4 };
+
+
 // Halo assignment of a TX x TY tile (fixed for the whole march): halo value
 // j is a y-halo point for j < 8 TX (4 rows above, 4 below, x fastest) and an
 // x-halo point otherwise (4 left and 4 right of each tile row).
@@ -96,17 +100,19 @@ struct FieldTerm {
 // The per-point epilogue shared by both marches: H value from the Laplacian
 // taps, then the stage combination (times the absorber mask m_c when MASK),
 // stored at the point's code (zero at a dead slot, dropped outside the box).
-// PAIR (a first-type FP64 stage of the discrete adjoint): b_c
+// SUM_PAIR (a first-type FP64 stage of the discrete adjoint): b_c
 // holds the pair operand u at the point, and pacc gathers conj(in) x_axis u
 // (zero wherever the point is outside the box, since both loads read zero
-// there).
-template <bool NTS, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS, bool PAIR = false>
+// there).  SUM_TDOT, SUM_HDOT (H applications): pacc gathers in H in without
+// and with conjugation of the first factor, over the box points; SUM_ONLY
+// does the second and stores nothing.
+template <bool NTS, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS, int SUM = 0>
 __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0, Tc lr, Tc li, Tc v_c,
                                        Tc vi_c, double2 b_c, double m_c, const FieldTerm &f, int yz,
                                        unsigned code, __amdgpu_buffer_rsrc_t rout, double2 &pacc) {
     const double xc = f.at(yz);
     const Tc vloc = v_c + (Tc)(f.E * xc);
-    if constexpr (PAIR) {
+    if constexpr (SUM == SUM_PAIR) {
         pacc.x += xc * ((double)q0.x * b_c.x + (double)q0.y * b_c.y);
         pacc.y += xc * ((double)q0.x * b_c.y - (double)q0.y * b_c.x);
     }
@@ -124,7 +130,15 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
     const bool zero = (int)code < 0;
     const unsigned o = coff<Tout>(code & ~CODE_DEAD);
     if (MODE == 0) {
-        store_c<NTS>(rout, o, (Tout *)nullptr, zero ? 0.0 : (double)hr, zero ? 0.0 : (double)hi);
+        const double sr = zero ? 0.0 : (double)hr, si = zero ? 0.0 : (double)hi;
+        if constexpr (SUM == SUM_TDOT) {
+            pacc.x += q0.x * sr - q0.y * si;
+            pacc.y += q0.x * si + q0.y * sr;
+        } else if constexpr (SUM == SUM_HDOT || SUM == SUM_ONLY) {
+            pacc.x += q0.x * sr + q0.y * si;
+            pacc.y += q0.x * si - q0.y * sr;
+        }
+        if constexpr (SUM != SUM_ONLY) store_c<NTS>(rout, o, (Tout *)nullptr, sr, si);
     } else {
         const double2 bb = FIRST ? make_double2((double)q0.x, (double)q0.y) : b_c;
         double r = bb.x + (a.cre * (double)hr - a.cim * (double)hi);
@@ -139,7 +153,7 @@ __device__ __forceinline__ void finish(const KParams &a, typename CT<Tc>::c2 q0,
 
 // A stage that carries another operand per point (a base, a mask, an adjoint
 // pair).
-constexpr bool stage_heavy(int mode, bool first, bool pair) { return mode == 1 && (!first || pair); }
+constexpr bool stage_heavy(int mode, bool first, int sum) { return mode == 1 && (!first || sum == SUM_PAIR); }
 
 // Constants of the pipelined march: depth D, ring lengths, and the LDS ring
 // of row entries (segments of P planes, the unroll period).
@@ -186,11 +200,11 @@ struct Ring {
 // (32 x 16, depth 2) and 1.81 -> 1.65 ms with the best tile of each form;
 // 96^3 cube, 8 orbitals 77 -> 64 us; 48 uneven spheres 2.6 -> 1.8 ms.
 template <bool NTS, int TX, int TY, int D, int CY, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK,
-          bool CS, bool PAIR>
+          bool CS, int SUM>
 __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, const int n,
                                            typename CT<Tc>::c2 *tile, int4 *rowl, double2 &pacc) {
     using C2 = typename CT<Tc>::c2;
-    using R = Ring<TX, TY, D, CY, std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, PAIR)>;
+    using R = Ring<TX, TY, D, CY, std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, SUM)>;
     constexpr int NT = R::NT, LX = TX + 8, HPT = R::HPT, Q = R::Q, HA = R::HA, HQ = R::HA, VD = R::VD, P = R::P;
     constexpr int RY = R::RY, SEG = R::SEG, RPT = R::RPT;
     constexpr int PLANE = (TY + 8) * LX;       // one plane buffer; tile holds two
@@ -199,7 +213,7 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     const int64_t np = a.np;
     const auto rin = rsrc(static_cast<const Tin *>(a.in) + (int64_t)n * a.ldp, np * (int64_t)sizeof(Tin));
     // the base operand (later stages), or the pair operand of an adjoint stage
-    const auto rbase = rsrc(static_cast<const double2 *>(PAIR ? a.pair_y : a.base) + (int64_t)n * a.ldp, np * 16);
+    const auto rbase = rsrc(static_cast<const double2 *>(SUM == SUM_PAIR ? a.pair_y : a.base) + (int64_t)n * a.ldp, np * 16);
     const auto rout = rsrc(static_cast<Tout *>(a.out) + (int64_t)n * a.ldp, np * (int64_t)sizeof(Tout));
     const auto rv = rsrc(a.V, np * (int64_t)sizeof(Tc));
     const auto rm = rsrc(MASK ? a.mask : a.V, MASK ? np * 8 : 0);
@@ -209,7 +223,7 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
     auto fetch = [&](unsigned c) -> C2 { return load_c<Tc, Tin>(rin, coff<Tin>(c)); };
     auto fetch_v = [&](unsigned c) -> Tc { return BL<Tc>::ld(rv, coff<Tc>(c)); };
     auto fetch_b = [&](unsigned c) -> double2 {
-        if (MODE != 1 || (FIRST && !PAIR)) return make_double2(0.0, 0.0);
+        if (MODE != 1 || (FIRST && SUM != SUM_PAIR)) return make_double2(0.0, 0.0);
         return BL<double2>::ld(rbase, coff<double2>(c));
     };
     auto fetch_m = [&](unsigned c) -> double { return MASK ? BL<double>::ld(rm, coff<double>(c)) : 1.0; };
@@ -376,7 +390,7 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
                          FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (zm3.y + zp3.y)) +
                          FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (zm4.y + zp4.y));
                 }
-                finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c[c], vi_c[c], b_c[c], m_c[c], ft,
+                finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, q0, lr, li, v_c[c], vi_c[c], b_c[c], m_c[c], ft,
                                                                    a.axis == 1 ? y + c : z, code_c[c], rout, pacc);
             }
 #undef SLOT
@@ -393,7 +407,7 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
 // issued one step ahead; a step starts by waiting for the previous step's
 // loads.  Planes run zs, zs + dir, ... as in the pipelined march.
 template <bool NTS, int TX, int TY, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
-          bool PAIR>
+          int SUM>
 __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, const int n,
                                            typename CT<Tc>::c2 *tile, double2 &pacc) {
     using C2 = typename CT<Tc>::c2;
@@ -409,7 +423,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     const int64_t np = a.np;
     const auto rin = rsrc(static_cast<const Tin *>(a.in) + (int64_t)n * a.ldp, np * (int64_t)sizeof(Tin));
     // the base operand (later stages), or the pair operand of an adjoint stage
-    const auto rbase = rsrc(static_cast<const double2 *>(PAIR ? a.pair_y : a.base) + (int64_t)n * a.ldp, np * 16);
+    const auto rbase = rsrc(static_cast<const double2 *>(SUM == SUM_PAIR ? a.pair_y : a.base) + (int64_t)n * a.ldp, np * 16);
     const auto rout = rsrc(static_cast<Tout *>(a.out) + (int64_t)n * a.ldp, np * (int64_t)sizeof(Tout));
     const auto rv = rsrc(a.V, np * (int64_t)sizeof(Tc));
     const auto rm = rsrc(MASK ? a.mask : a.V, MASK ? np * 8 : 0);
@@ -419,7 +433,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     auto fetch = [&](int idx, bool ok) -> C2 { return load_c<Tc, Tin>(rin, ok ? boff<Tin>(idx) : OOB); };
     auto fetch_v = [&](int idx) -> Tc { return BL<Tc>::ld(rv, boff<Tc>(idx)); };
     auto fetch_b = [&](int idx) -> double2 {
-        if (MODE != 1 || (FIRST && !PAIR)) return make_double2(0.0, 0.0);
+        if (MODE != 1 || (FIRST && SUM != SUM_PAIR)) return make_double2(0.0, 0.0);
         return BL<double2>::ld(rbase, boff<double2>(idx));
     };
     auto fetch_m = [&](int idx) -> double { return MASK ? BL<double>::ld(rm, boff<double>(idx)) : 1.0; };
@@ -500,7 +514,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
                  FD<Tc>::c3 * ((xm3.y + xp3.y) + (ym3.y + yp3.y) + (q[1].y + q[7].y)) +
                  FD<Tc>::c4 * ((xm4.y + xp4.y) + (ym4.y + yp4.y) + (q[0].y + q[8].y));
         }
-        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, a.axis == 1 ? y : z, code_of(idx_c),
+        finish<NTS, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, q0, lr, li, v_c, vi_c, b_c, m_c, ft, a.axis == 1 ? y : z, code_of(idx_c),
                                                        rout, pacc);
 #pragma unroll
         for (int j = 0; j < 8; ++j) q[j] = q[j + 1];
@@ -525,9 +539,9 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
 constexpr int tile_cy(int TX, int TY, int D, bool fp64, bool heavy) {
     return fp64 && D == 1 && (TX * TY == 1024 || (TX * TY == 512 && TX == 32 && !heavy)) ? 2 : 1;
 }
-template <int TX, int TY, int D, class Tc, int MODE, bool FIRST, bool PAIR>
+template <int TX, int TY, int D, class Tc, int MODE, bool FIRST, int SUM>
 constexpr int stage_cy() {
-    return tile_cy(TX, TY, D, std::is_same<Tc, double>::value, stage_heavy(MODE, FIRST, PAIR));
+    return tile_cy(TX, TY, D, std::is_same<Tc, double>::value, stage_heavy(MODE, FIRST, SUM));
 }
 // LDS row entries of a march (the lean one needs none).
 template <int TX, int TY, int D, int CY, bool HEAVY>
@@ -539,14 +553,14 @@ constexpr int march_rows() {
 }
 
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK, bool CS,
-          bool PAIR = false>
+          int SUM = 0>
 __device__ __forceinline__ void march(const KParams &a, const int4 it, const int n, typename CT<Tc>::c2 *tile,
                                       int4 *rowl, double2 &pacc) {
     if constexpr (D == 0)
-        march_lean<NTS, TX, TY, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, it, n, tile, pacc);
+        march_lean<NTS, TX, TY, Tin, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, it, n, tile, pacc);
     else
-        march_ring<NTS, TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>(), Tin, Tc, Tout, MODE, FIRST, MASK, CS,
-                   PAIR>(a, it, n, tile, rowl, pacc);
+        march_ring<NTS, TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>(), Tin, Tc, Tout, MODE, FIRST, MASK, CS,
+                   SUM>(a, it, n, tile, rowl, pacc);
 }
 
 // Sum of v over the workgroup (xor shuffles within each wave, then the wave
@@ -572,11 +586,11 @@ __device__ __forceinline__ double2 wg_sum(double2 v, double2 *lds) {
 }
 
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK = false,
-          bool CS = false, bool PAIR = false>
-__global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>()), 2) k_stencil(KParams a) {
+          bool CS = false, int SUM = 0>
+__global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>()), 2) k_stencil(KParams a) {
     __shared__ typename CT<Tc>::c2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
-    __shared__ int4 rowl[march_rows<TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>(),
-                                    std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, PAIR)>()];
+    __shared__ int4 rowl[march_rows<TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>(),
+                                    std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, SUM)>()];
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     int n, item;
     block_item(a, blk, &n, &item);
@@ -585,12 +599,14 @@ __global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST
     n = __builtin_amdgcn_readfirstlane(n);
     item = __builtin_amdgcn_readfirstlane(item);
     double2 pacc = make_double2(0.0, 0.0);
-    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, PAIR>(a, a.items[item], n, tile, rowl, pacc);
-    if constexpr (PAIR) {
-        // this workgroup's part of the pair sum, at its place in the launch
-        // order (a fixed position, so the final sum has a fixed order)
-        const double2 s = wg_sum<TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, PAIR>()>(pacc, reinterpret_cast<double2 *>(tile));
-        if (threadIdx.x == 0) reinterpret_cast<double2 *>(a.pair_out)[blk] = s;
+    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, a.items[item], n, tile, rowl, pacc);
+    if constexpr (SUM != 0) {
+        // this workgroup's part of the sum, at a fixed place (so the final
+        // sum has a fixed order): its place in the launch order for the pair
+        // sum over all orbitals, {orbital, item} for the per-orbital sums
+        const double2 s = wg_sum<TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>()>(pacc, reinterpret_cast<double2 *>(tile));
+        if (threadIdx.x == 0)
+            reinterpret_cast<double2 *>(a.pair_out)[SUM == SUM_PAIR ? blk : (int64_t)n * a.nitems + item] = s;
     }
 }
 
@@ -650,7 +666,13 @@ template <bool NTS, int TX, int TY, int D>
 int launch_fp64_cs(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
     constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0 || a.mask || a.pair_y) return RSG_EUNSUPPORTED;
-    if (a.mode == 0)
+    if (a.mode == 0 && a.dot == DOT_T)
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_TDOT><<<nb, N1, 0, s>>>(p);
+    else if (a.mode == 0 && a.dot == DOT_ONLY)
+        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_ONLY><<<nb, N1, 0, s>>>(p);
+    else if (a.dot)
+        return RSG_EUNSUPPORTED;
+    else if (a.mode == 0)
         k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true><<<nb, N1, 0, s>>>(p);
     else if (a.first)
         k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, true><<<nb, N1, 0, s>>>(p);
@@ -664,10 +686,18 @@ int launch_fp64(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
     constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0) return RSG_EUNSUPPORTED;
     if (a.pair_y && !(a.mode == 1 && a.first && !a.mask)) return RSG_EUNSUPPORTED;
-    if (a.mode == 0)
+    if (a.mode == 0 && a.dot == DOT_T)
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_TDOT><<<nb, N1, 0, s>>>(p);
+    else if (a.mode == 0 && a.dot == DOT_H)
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_HDOT><<<nb, N1, 0, s>>>(p);
+    else if (a.mode == 0 && a.dot == DOT_ONLY)
+        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_ONLY><<<nb, N1, 0, s>>>(p);
+    else if (a.dot)
+        return RSG_EUNSUPPORTED;
+    else if (a.mode == 0)
         k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false><<<nb, N1, 0, s>>>(p);
     else if (a.pair_y)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, true><<<nb, N2, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, SUM_PAIR><<<nb, N2, 0, s>>>(p);
     else if (a.first)
         k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true><<<nb, N1, 0, s>>>(p);
     else if (a.mask)
@@ -683,7 +713,7 @@ int launch_fp64(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
 template <bool NTS, int TX, int TY, int D>
 int launch_fp32(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
     constexpr int NT = TX * TY;
-    if (a.mode != 1 || a.pair_y) return RSG_EUNSUPPORTED;
+    if (a.mode != 1 || a.pair_y || a.dot) return RSG_EUNSUPPORTED;
     if (a.in_t == 0 && a.out_t == 1 && a.first)
         k_stencil<NTS, TX, TY, D, double2, float, float2, 1, true><<<nb, NT, 0, s>>>(p);
     else if (a.in_t == 1 && a.out_t == 1 && a.first)
