@@ -13,12 +13,22 @@
 // one H application per iteration suffices.
 //
 // Design: every per-orbital scalar of the recurrences stays on the device.
-// An iteration is the H application plus three passes over the batch, each
-// a pointwise update fused with the partial sums that the next scalar step
-// needs, and three small kernels (one workgroup per orbital) that add the
+// An iteration is the H application, whose stencil also sums p^T H p (the
+// projectors' part follows from their gather), plus two passes over the batch,
+// each a pointwise update fused with the partial sums that the next scalar
+// step needs, and small kernels (one workgroup per orbital) that add the
 // partial sums in a fixed order and advance the recurrences.  Converged
 // orbitals are frozen by a flag that every kernel reads first.  The host
 // looks at the flags only every few iterations.
+//
+// QMR's residual needs no recurrence of its own image: with A p_n = v~_{n+1}
+// + beta_n v_n the update r_n = r_{n-1} - s_n, s_n = eta_n A p_n +
+// (theta_{n-1} gamma_n)^2 s_{n-1}, is r_n = (1 - gamma_n^2) r_{n-1} - eta_n
+// v~_{n+1} (by induction: s_{n-1} and v_n both lie in the span of r_{n-1} and
+// r_{n-2}, whose terms in r_{n-2} cancel).  So s is not kept, the update does
+// not read H p, and v stays unnormalised (v~, its norm folded into beta):
+// 32 (H) + 64 + 144 = 240 B per point and orbital and iteration, 336 before.
+// 500 k points x 16 orbitals x 4 atoms: 654 -> 488 us an iteration.
 #include "rsg_internal.h"
 
 #include <algorithm>
@@ -44,7 +54,9 @@ struct SolveState {
     double2 alpha;       // CG: step length
     double rho;          // QMR: rho_i = ||v~_i||; CG: r^H r
     double theta, gamma; // QMR: theta_{i-1}, gamma_{i-1}
+    double2 pp;          // p^T p of the current p (QMR), p^H p (CG)
     double cd;           // QMR: (theta_{i-1} gamma_i)^2
+    double cr;           // QMR: 1 - gamma_i^2
     double inv;          // QMR: 1 / rho_{i+1}
     double bnorm, rnorm;
     double tol;
@@ -108,17 +120,19 @@ __device__ __forceinline__ void store_partials(double2 (&acc)[K], double2 *part)
 
 struct PassArgs {
     const double2 *b;
-    double2 *x, *r, *w, *v, *p, *d, *s;
+    double2 *x, *r, *w, *v, *p, *d;
     SolveState *st;
     double2 *part;  // [nst][nblk][NQ]
+    double2 *dot;   // [nst][ndot] the stencil's sums of p H_loc p, or null: k_sv_pw sums them
+    KbDot kb;
     int64_t np, ldp;
-    int32_t nblk;
+    int32_t nblk, ndot;
 };
 
 // ---------------------------------------------------------------- passes
 // Grid (nblk, nst): block b of orbital n handles a contiguous point range.
 
-// r = b - w - sigma x (w = H x); CG: p = r; QMR: d = s = 0.  Sums: |r|^2,
+// r = b - w - sigma x (w = H x); CG: p = r; QMR: d = 0.  Sums: |r|^2,
 // r^T r (QMR) , |b|^2.
 template <bool QMR>
 __global__ void __launch_bounds__(SB) k_sv_init(PassArgs a) {
@@ -135,7 +149,6 @@ __global__ void __launch_bounds__(SB) k_sv_init(PassArgs a) {
         a.r[o + i] = rr;
         if (QMR) {
             a.d[o + i] = make_double2(0, 0);
-            a.s[o + i] = make_double2(0, 0);
         } else {
             a.p[o + i] = rr;
         }
@@ -146,7 +159,7 @@ __global__ void __launch_bounds__(SB) k_sv_init(PassArgs a) {
     store_partials<NQ>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
-// QMR: v = r / rho_1, p = v.
+// QMR: v~ = r, p = v~ / rho_1.
 __global__ void __launch_bounds__(SB) k_sv_qmr_start(PassArgs a) {
     const int n = blockIdx.y, blk = blockIdx.x;
     if (!a.st[n].active) return;
@@ -157,12 +170,13 @@ __global__ void __launch_bounds__(SB) k_sv_qmr_start(PassArgs a) {
     for (int64_t i = lo + threadIdx.x; i < hi; i += SB) {
         const double2 rr = a.r[o + i];
         const double2 vv = make_double2(rr.x * inv, rr.y * inv);
-        a.v[o + i] = vv;
+        a.v[o + i] = rr;
         a.p[o + i] = vv;
     }
 }
 
-// Sums over p and w = H p: QMR p^T w, p^T p; CG p^H w, p^H p.
+// Sum over p and w = H p: QMR p^T w; CG p^H w (where the workspace has no
+// room for the stencil's own sums).
 template <bool QMR>
 __global__ void __launch_bounds__(SB) k_sv_pw(PassArgs a) {
     const int n = blockIdx.y, blk = blockIdx.x;
@@ -170,25 +184,22 @@ __global__ void __launch_bounds__(SB) k_sv_pw(PassArgs a) {
     const int64_t o = (int64_t)n * a.ldp;
     int64_t lo, hi;
     block_range(a.np, blk, a.nblk, &lo, &hi);
-    double2 acc[2] = {make_double2(0, 0), make_double2(0, 0)};
+    double2 acc[1] = {make_double2(0, 0)};
     for (int64_t i = lo + threadIdx.x; i < hi; i += SB) {
         const double2 pp = a.p[o + i], ww = a.w[o + i];
-        if (QMR) {
-            acc[0] = cadd(acc[0], tdot(pp, ww));
-            acc[1] = cadd(acc[1], tdot(pp, pp));
-        } else {
-            acc[0] = cadd(acc[0], hdot(pp, ww));
-            acc[1].x += cabs2(pp);
-        }
+        acc[0] = cadd(acc[0], QMR ? tdot(pp, ww) : hdot(pp, ww));
     }
-    store_partials<2>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
+    store_partials<1>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
-// QMR: v~ = w + sigma p - beta v, written over v.  Sums |v~|^2, v~^T v~.
+// QMR: v~ = w + sigma p - beta v, written over the last v~ (v = v~ / rho).
+// Sums |v~|^2, v~^T v~.
 __global__ void __launch_bounds__(SB) k_sv_qmr_vt(PassArgs a) {
     const int n = blockIdx.y, blk = blockIdx.x;
     if (!a.st[n].active) return;
-    const double2 sg = a.st[n].sigma, be = a.st[n].beta;
+    const double2 sg = a.st[n].sigma, bs = a.st[n].beta;
+    const double vs = a.st[n].inv;
+    const double2 be = make_double2(bs.x * vs, bs.y * vs);
     const int64_t o = (int64_t)n * a.ldp;
     int64_t lo, hi;
     block_range(a.np, blk, a.nblk, &lo, &hi);
@@ -204,39 +215,35 @@ __global__ void __launch_bounds__(SB) k_sv_qmr_vt(PassArgs a) {
     store_partials<2>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
-// QMR: d = eta p + cd d; s = eta (w + sigma p) + cd s; x += d; r -= s;
-// v = v~ / rho_{i+1}; p = v - cp p.  Sum |r|^2.
+// QMR: d = eta p + cd d; x += d; r = cr r - eta v~; p = v~ / rho_{i+1} - cp p.
+// Sums |r|^2, p^T p (of the new p).
 __global__ void __launch_bounds__(SB) k_sv_qmr_update(PassArgs a) {
     const int n = blockIdx.y, blk = blockIdx.x;
     if (!a.st[n].active) return;
     const SolveState &q = a.st[n];
-    const double2 sg = q.sigma, et = q.eta, cp = q.cp;
-    const double cd = q.cd, inv = q.inv;
+    const double2 et = q.eta, cp = q.cp;
+    const double cd = q.cd, cr = q.cr, inv = q.inv;
     const int64_t o = (int64_t)n * a.ldp;
     int64_t lo, hi;
     block_range(a.np, blk, a.nblk, &lo, &hi);
-    double2 acc[1] = {make_double2(0, 0)};
+    double2 acc[2] = {make_double2(0, 0), make_double2(0, 0)};
     for (int64_t i = lo + threadIdx.x; i < hi; i += SB) {
-        const double2 pp = a.p[o + i], ww = a.w[o + i], vt = a.v[o + i];
-        double2 dd = a.d[o + i], ss = a.s[o + i], xx = a.x[o + i], rr = a.r[o + i];
-        const double2 ep = cmul(et, pp);
-        const double2 ap = cadd(ww, cmul(sg, pp));
-        const double2 ea = cmul(et, ap);
+        const double2 pp = a.p[o + i], vt = a.v[o + i];
+        double2 dd = a.d[o + i], xx = a.x[o + i], rr = a.r[o + i];
+        const double2 ep = cmul(et, pp), ev = cmul(et, vt);
         dd = make_double2(ep.x + cd * dd.x, ep.y + cd * dd.y);
-        ss = make_double2(ea.x + cd * ss.x, ea.y + cd * ss.y);
         xx = cadd(xx, dd);
-        rr = make_double2(rr.x - ss.x, rr.y - ss.y);
-        const double2 vn = make_double2(vt.x * inv, vt.y * inv);
+        rr = make_double2(cr * rr.x - ev.x, cr * rr.y - ev.y);
         const double2 cpp = cmul(cp, pp);
+        const double2 pn = make_double2(vt.x * inv - cpp.x, vt.y * inv - cpp.y);
         a.d[o + i] = dd;
-        a.s[o + i] = ss;
         a.x[o + i] = xx;
         a.r[o + i] = rr;
-        a.v[o + i] = vn;
-        a.p[o + i] = make_double2(vn.x - cpp.x, vn.y - cpp.y);
+        a.p[o + i] = pn;
         acc[0].x += cabs2(rr);
+        acc[1] = cadd(acc[1], tdot(pn, pn));
     }
-    store_partials<1>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
+    store_partials<2>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
 // CG: x += alpha p; r -= alpha (w + sigma p).  Sum |r|^2.
@@ -262,7 +269,7 @@ __global__ void __launch_bounds__(SB) k_sv_cg_update(PassArgs a) {
     store_partials<1>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
-// CG: p = r + beta p.
+// CG: p = r + beta p.  Sum |p|^2.
 __global__ void __launch_bounds__(SB) k_sv_cg_dir(PassArgs a) {
     const int n = blockIdx.y, blk = blockIdx.x;
     if (!a.st[n].active) return;
@@ -270,18 +277,49 @@ __global__ void __launch_bounds__(SB) k_sv_cg_dir(PassArgs a) {
     const int64_t o = (int64_t)n * a.ldp;
     int64_t lo, hi;
     block_range(a.np, blk, a.nblk, &lo, &hi);
+    double2 acc[1] = {make_double2(0, 0)};
     for (int64_t i = lo + threadIdx.x; i < hi; i += SB) {
         const double2 rr = a.r[o + i], pp = a.p[o + i];
         const double2 bp = cmul(be, pp);
-        a.p[o + i] = make_double2(rr.x + bp.x, rr.y + bp.y);
+        const double2 pn = make_double2(rr.x + bp.x, rr.y + bp.y);
+        a.p[o + i] = pn;
+        acc[0].x += cabs2(pn);
     }
+    store_partials<1>(acc, a.part + ((int64_t)n * a.nblk + blk) * NQ);
 }
 
 // ---------------------------------------------------------------- scalars
 // One workgroup per orbital: the K partial sums of the orbital's nblk
 // blocks, added in a fixed order, then one thread advances the recurrence.
 
-enum ScalStep { SC_INIT_QMR, SC_INIT_CG, SC_EPS, SC_RHO, SC_RES_QMR, SC_ALPHA, SC_RES_CG };
+enum ScalStep { SC_INIT_QMR, SC_INIT_CG, SC_EPS, SC_RHO, SC_RES_QMR, SC_ALPHA, SC_RES_CG, SC_PP };
+
+// p H p of orbital n: the stencil's partials (or k_sv_pw's) in a fixed order,
+// and for the former the projectors' part, sum_{a,i} E_i D_i^2 / h^3 with D_i =
+// h^3 p_i^T p (|D_i|^2 for CG's conjugated product).
+template <bool QMR>
+__device__ __forceinline__ double2 sum_dot(const PassArgs &a, int n) {
+    __shared__ double2 red[SB];
+    double2 t = make_double2(0, 0);
+    if (a.dot) {
+        for (int b = threadIdx.x; b < a.ndot; b += SB) t = cadd(t, a.dot[(int64_t)n * a.ndot + b]);
+        for (int r = threadIdx.x; r < a.kb.natoms * 4; r += SB) {
+            const double2 d = kb_value<double>(a.kb.D, a.kb.P, a.kb.nchunk, a.kb.h3, a.kb.ncols, r, n);
+            const double f = a.kb.E[r] / a.kb.h3;
+            const double2 dd = QMR ? tdot(d, d) : make_double2(cabs2(d), 0.0);
+            t = make_double2(t.x + f * dd.x, t.y + f * dd.y);
+        }
+    } else {
+        for (int b = threadIdx.x; b < a.nblk; b += SB) t = cadd(t, a.part[((int64_t)n * a.nblk + b) * NQ]);
+    }
+    red[threadIdx.x] = t;
+    __syncthreads();
+    for (int w = SB / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + w]);
+        __syncthreads();
+    }
+    return red[0];
+}
 
 template <int K>
 __device__ __forceinline__ void sum_partials(const double2 *part, int nblk, double2 (&out)[K]) {
@@ -311,12 +349,19 @@ constexpr double TINY = 1e-290;
 constexpr double DELTA_MIN = 1e-13;
 
 template <int STEP>
-__global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *part, int nblk) {
+__global__ void __launch_bounds__(SB) k_sv_scal(PassArgs a) {
     const int n = blockIdx.x;
-    SolveState &q = st[n];
+    SolveState &q = a.st[n];
     if (STEP != SC_INIT_QMR && STEP != SC_INIT_CG && !q.active) return;
+    constexpr int K = STEP == SC_INIT_QMR || STEP == SC_INIT_CG ? 3 : (STEP == SC_RES_CG || STEP == SC_PP ? 1 : 2);
     double2 s[NQ];
-    sum_partials<NQ>(part + (int64_t)n * nblk * NQ, nblk, s);
+    if constexpr (STEP == SC_EPS || STEP == SC_ALPHA) {
+        s[0] = sum_dot<STEP == SC_EPS>(a, n);
+    } else {
+        double2 k[K];
+        sum_partials<K>(a.part + (int64_t)n * a.nblk * NQ, a.nblk, k);
+        for (int j = 0; j < K; ++j) s[j] = k[j];
+    }
     if (threadIdx.x != 0) return;
     if (STEP == SC_INIT_QMR || STEP == SC_INIT_CG) {
         q.bnorm = std::sqrt(s[2].x);
@@ -334,6 +379,7 @@ __global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *p
             q.rho = rho;
             q.inv = 1.0 / rho;
             q.delta = make_double2(s[1].x / (rho * rho), s[1].y / (rho * rho));
+            q.pp = q.delta;  // p_1 = v_1
             q.gamma = 1.0;
             q.theta = 0.0;
             q.eta = make_double2(-1.0, 0.0);
@@ -343,10 +389,11 @@ __global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *p
             }
         } else {
             q.rho = s[0].x;  // r^H r
+            q.pp = make_double2(s[0].x, 0.0);
         }
     } else if (STEP == SC_EPS) {
         // eps_i = p^T (H + sigma) p, beta_i = eps_i / delta_i
-        const double2 e = cadd(s[0], cmul(q.sigma, s[1]));
+        const double2 e = cadd(s[0], cmul(q.sigma, q.pp));
         q.eps = e;
         if (std::sqrt(cabs2(e)) < TINY) {
             q.active = 0;
@@ -365,6 +412,7 @@ __global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *p
         const double2 num = make_double2(-q.eta.x * f, -q.eta.y * f);
         q.eta = cdiv(num, q.beta);
         q.cd = (q.theta * ga) * (q.theta * ga);
+        q.cr = (th * ga) * (th * ga);  // 1 - gamma^2 without cancellation
         q.theta = th;
         q.gamma = ga;
         if (rho1 > 0) {
@@ -383,6 +431,7 @@ __global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *p
     } else if (STEP == SC_RES_QMR || STEP == SC_RES_CG) {
         q.rnorm = std::sqrt(s[0].x);
         q.iters += 1;
+        if (STEP == SC_RES_QMR) q.pp = s[1];
         const double target = q.tol * (q.bnorm > 0 ? q.bnorm : 1.0);
         if (q.rnorm <= target) {
             q.active = 0;
@@ -402,13 +451,15 @@ __global__ void __launch_bounds__(SB) k_sv_scal(SolveState *st, const double2 *p
         }
     } else if (STEP == SC_ALPHA) {
         // alpha = r^H r / p^H (H + sigma) p (real for a real shift)
-        const double pap = s[0].x + q.sigma.x * s[1].x;
+        const double pap = s[0].x + q.sigma.x * q.pp.x;
         if (std::fabs(pap) < TINY) {
             q.active = 0;
             q.status = 2;
             return;
         }
         q.alpha = make_double2(q.rho / pap, 0.0);
+    } else if (STEP == SC_PP) {
+        q.pp = make_double2(s[0].x, 0.0);
     }
 }
 
@@ -420,6 +471,7 @@ using namespace rsg;
 
 extern "C" size_t rsg_solve_workspace_bytes(rsg_ham_t H, int32_t method, int64_t nst, int64_t ldp) {
     if (!H || nst < 0 || ldp < 1) return 0;
+    // (QMR: five batches, and one for the stencil's partial sums)
     const int nb = method == RSG_SOLVE_QMR ? 6 : 3;
     const int64_t nblk = solve_blocks(H->g->np);
     return nb * rounded(batch_bytes(nst, ldp, 16)) + rounded(kb_workspace_bytes(*H, nst)) +
@@ -464,7 +516,7 @@ extern "C" int rsg_shifted_solve(rsg_ham_t H, const double *shift, const void *b
     a.p = static_cast<double2 *>(c.take(bytes));
     a.v = qmr ? static_cast<double2 *>(c.take(bytes)) : nullptr;
     a.d = qmr ? static_cast<double2 *>(c.take(bytes)) : nullptr;
-    a.s = qmr ? static_cast<double2 *>(c.take(bytes)) : nullptr;
+    double2 *const spare = qmr ? static_cast<double2 *>(c.take(bytes)) : nullptr;
     void *D = c.take(kb_workspace_bytes(*H, nst));
     a.part = static_cast<double2 *>(c.take(sizeof(double2) * NQ * nblk * nst));
     a.st = static_cast<SolveState *>(c.take(sizeof(SolveState) * nst));
@@ -473,7 +525,18 @@ extern "C" int rsg_shifted_solve(rsg_ham_t H, const double *shift, const void *b
     a.np = H->g->np;
     a.ldp = ldp;
     a.nblk = (int32_t)nblk;
+    a.kb = kb_dot(*H, nst, D);
     hipStream_t s = (hipStream_t)stream;
+    // The stencil's partials, one per work item, go where there is room for
+    // them: QMR's spare batch, CG's partial sums (free at that point of an
+    // iteration; enough from a few hundred points per item on).  Without room
+    // a pass of its own reads p and w again.
+    const int64_t ndot = a.np > 0 ? stencil_blocks(*H, nst, 0, s) : 0;
+    if (ndot < 0) return (int)ndot;
+    a.ndot = (int32_t)(ndot / nst);
+    a.dot = nullptr;
+    if (ndot > 0 && qmr && sizeof(double2) * (size_t)ndot <= bytes) a.dot = spare;
+    if (ndot > 0 && !qmr && ndot <= NQ * nblk * nst) a.dot = a.part;
     return guarded([&]() -> int {
         std::vector<SolveState> hs(nst);
         for (int64_t n = 0; n < nst; ++n) {
@@ -491,11 +554,11 @@ extern "C" int rsg_shifted_solve(rsg_ham_t H, const double *shift, const void *b
         if ((r = hpsi_impl(*H, a.x, a.w, nst, ldp, 0.0, nullptr, D, s))) return r;
         if (qmr) {
             k_sv_init<true><<<pg, SB, 0, s>>>(a);
-            k_sv_scal<SC_INIT_QMR><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+            k_sv_scal<SC_INIT_QMR><<<on, SB, 0, s>>>(a);
             k_sv_qmr_start<<<pg, SB, 0, s>>>(a);
         } else {
             k_sv_init<false><<<pg, SB, 0, s>>>(a);
-            k_sv_scal<SC_INIT_CG><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+            k_sv_scal<SC_INIT_CG><<<on, SB, 0, s>>>(a);
         }
         RSG_CHECK_HIP(hipGetLastError());
         for (int it = 0; it < maxiter; ++it) {
@@ -506,20 +569,25 @@ extern "C" int rsg_shifted_solve(rsg_ham_t H, const double *shift, const void *b
                 for (int64_t n = 0; n < nst && !any; ++n) any = hs[n].active != 0;
                 if (!any) break;
             }
-            if ((r = hpsi_impl(*H, a.p, a.w, nst, ldp, 0.0, nullptr, D, s))) return r;
+            if (a.dot) {
+                if ((r = hdot_impl(*H, a.p, a.w, nst, ldp, 0.0, qmr ? DOT_T : DOT_H, (double *)a.dot, D, s))) return r;
+            } else if ((r = hpsi_impl(*H, a.p, a.w, nst, ldp, 0.0, nullptr, D, s))) {
+                return r;
+            }
             if (qmr) {
-                k_sv_pw<true><<<pg, SB, 0, s>>>(a);
-                k_sv_scal<SC_EPS><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+                if (!a.dot) k_sv_pw<true><<<pg, SB, 0, s>>>(a);
+                k_sv_scal<SC_EPS><<<on, SB, 0, s>>>(a);
                 k_sv_qmr_vt<<<pg, SB, 0, s>>>(a);
-                k_sv_scal<SC_RHO><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+                k_sv_scal<SC_RHO><<<on, SB, 0, s>>>(a);
                 k_sv_qmr_update<<<pg, SB, 0, s>>>(a);
-                k_sv_scal<SC_RES_QMR><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+                k_sv_scal<SC_RES_QMR><<<on, SB, 0, s>>>(a);
             } else {
-                k_sv_pw<false><<<pg, SB, 0, s>>>(a);
-                k_sv_scal<SC_ALPHA><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+                if (!a.dot) k_sv_pw<false><<<pg, SB, 0, s>>>(a);
+                k_sv_scal<SC_ALPHA><<<on, SB, 0, s>>>(a);
                 k_sv_cg_update<<<pg, SB, 0, s>>>(a);
-                k_sv_scal<SC_RES_CG><<<on, SB, 0, s>>>(a.st, a.part, a.nblk);
+                k_sv_scal<SC_RES_CG><<<on, SB, 0, s>>>(a);
                 k_sv_cg_dir<<<pg, SB, 0, s>>>(a);
+                k_sv_scal<SC_PP><<<on, SB, 0, s>>>(a);
             }
             RSG_CHECK_HIP(hipGetLastError());
         }
