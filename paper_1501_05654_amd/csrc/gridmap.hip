@@ -39,6 +39,15 @@ constexpr int MB = 256;  // threads per workgroup
 // One thread per (point, orbital), orbital fastest: a wave reads whole rows
 // of nst orbitals of each neighbour.  Taps of equal |m| are summed first
 // (x, y, z pairs), then weighted.
+//
+// Bound by the latency of its gathers: all 24 table entries are requested,
+// then all 24 neighbours (a point without one reads itself and adds zero, so
+// no load hides behind a branch; with a branch each, the loads ran one after
+// another, 48 round trips deep).  500,199 points in Hilbert order: 16 orbitals
+// 277 -> 196 us, 64 orbitals 1.03 -> 0.88 ms, 4 orbitals 62 -> 51 us.  What is
+// left is the L1's rate (25 values of 16 B in for one out).  Workgroups of 1024
+// threads (265 us) and orbitals in groups of 4, 8 or 32 per workgroup
+// (200-211 us) were slower.
 __global__ void __launch_bounds__(MB) k_map_lap(const double2 *__restrict__ psi, double2 *__restrict__ out,
                                                 const int32_t *__restrict__ nbr, int32_t np, int32_t nst,
                                                 int64_t ld, double scale) {
@@ -47,20 +56,19 @@ __global__ void __launch_bounds__(MB) k_map_lap(const double2 *__restrict__ psi,
     const int p = g / nst;
     if (p >= np) return;
     const int n = g - p * nst;
+    int q[24];
+#pragma unroll
+    for (int j = 0; j < 24; ++j) q[j] = nbr[(int64_t)j * np + p];
     const double2 c = psi[(int64_t)p * ld + n];
+    double2 v[24];
+#pragma unroll
+    for (int j = 0; j < 24; ++j) v[j] = psi[(int64_t)(q[j] >= 0 ? q[j] : p) * ld + n];
     double sr[4] = {0, 0, 0, 0}, si[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = nbr[(int64_t)(8 * a + k) * np + p];
-            const int dm = k < 4 ? 3 - k : k - 4;  // |m| - 1
-            if (q >= 0) {
-                const double2 v = psi[(int64_t)q * ld + n];
-                sr[dm] += v.x;
-                si[dm] += v.y;
-            }
-        }
+    for (int j = 0; j < 24; ++j) {
+        const int k = j & 7, dm = k < 4 ? 3 - k : k - 4;  // |m| - 1
+        sr[dm] += q[j] >= 0 ? v[j].x : 0.0;
+        si[dm] += q[j] >= 0 ? v[j].y : 0.0;
     }
     const double c0 = -205.0 / 72.0, c1 = 8.0 / 5.0, c2 = -1.0 / 5.0, c3 = 8.0 / 315.0, c4 = -1.0 / 560.0;
     const double lr = 3.0 * c0 * c.x + c1 * sr[0] + c2 * sr[1] + c3 * sr[2] + c4 * sr[3];
