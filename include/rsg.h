@@ -411,8 +411,9 @@ size_t rsg_batch_workspace_bytes(int32_t nsys, const rsg_system_desc *sys);
  * across systems).  The systems fall into size classes by the width of their
  * tight box (narrower than 48 points, 48 to 79, 80 or more; empty classes
  * are dropped), and each class has its own stencil tile shape (initially
- * 32 x 8, depth 2).  Each stage of a Taylor(4) step of all systems runs as
- * one persistent stencil launch per class over a list of (system, tile,
+ * 32 x 16, depth 1, z in aligned chunks of 48 planes).  Each stage of a
+ * Taylor(4) step of all systems runs as one persistent stencil launch per
+ * tile shape in use over a list of (system, tile,
  * z-range, orbital) items (largest systems first; cut into one segment per
  * XCD, each workgroup taking items from its own XCD's segment first and
  * then from the others), with one projector
@@ -432,7 +433,7 @@ int rsg_batch_destroy(rsg_batch_t b);
 /* Size classes: *nclass, and (if class_of_sys is not NULL) the class of
  * every system.  rsg_batch_set_classes replaces the classes: class_of_sys[i]
  * in 0..nclass-1 for every system, every class non-empty (RSG_EINVAL
- * otherwise); every class restarts with the 32 x 8 depth-2 tile. */
+ * otherwise); every class restarts with the initial tile. */
 int rsg_batch_classes(rsg_batch_t b, int32_t *nclass, int32_t *class_of_sys);
 int rsg_batch_set_classes(rsg_batch_t b, const int32_t *class_of_sys, void *stream);
 

@@ -4,7 +4,7 @@
 // (section "Parallelization, optimizations and graphics processing units");
 // here the group extends across systems.  The systems are grouped into size
 // classes (by the width of their box), each class with its own stencil tile
-// shape; every stage of a Taylor(4) step runs, per class, as one persistent
+// shape; every stage of a Taylor(4) step runs, per tile shape in use, as one persistent
 // stencil launch over a list of (system, tile, z-range, orbital) items
 // (largest systems first, each sweeping its tiles orbital by orbital; the
 // list is cut into one contiguous segment per XCD, so that each XCD's L2
@@ -24,18 +24,42 @@ namespace rsg {
 // Systems of one size class share a tile shape and a persistent launch per
 // stage; the classes of a stage run back to back on the caller's stream.
 struct BatchClass {
-    TileShape tile{1, 32, 8, 0};
+    TileShape tile{1, 32, 16, 48};
     std::vector<int32_t> sys;    // member systems
     BatchItem *items = nullptr;  // device work list of this class
     int32_t *seg = nullptr;      // device bounds of the list's per-XCD segments
     int32_t nitems = 0;
     int grid = 0;                // resident workgroups of the class's kernel
+    void free_list() {
+        if (items) (void)hipFree(items);
+        if (seg) (void)hipFree(seg);
+        items = nullptr;
+        seg = nullptr;
+        nitems = 0;
+    }
 };
+
+// Tile every class starts with: 32 x 16, two columns per thread, z in chunks
+// of 48 planes at common planes.  Of ten shapes x five chunk lengths per class
+// on four sets of systems (48 spheres of 1..32 and 1..5 orbitals on both
+// storages, 6 spheres) it is within 3 % of the best in every class; the 32 x 8
+// depth-2 tile over the whole z-range before it took 9-13 % longer a stage
+// (48 spheres, 1.6e8 values: 1.98 -> 1.75 ms).
+static TileShape start_tile() {
+    TileShape t{1, 32, 16, 48};
+    t.PD = 1;
+    t.ZM = 2;
+    return t;
+}
+static bool same_tile(const TileShape &a, const TileShape &b) { return !(a < b) && !(b < a); }
 
 struct Batch {
     std::vector<rsg_system_desc> sys;
     std::vector<void *> w1, w2, D;  // per-system work buffers inside the caller's workspace
     std::vector<BatchClass> cls;
+    // Classes on one tile run as one launch (its list over all their systems),
+    // so a stage drains the chip once, not once per class.
+    std::vector<BatchClass> launches;
     int32_t grid_cap = 0;  // at most this many persistent workgroups per launch (0: no cap)
     bool nt = false;       // stage outputs written with non-temporal stores
     KParams *sp[4] = {nullptr, nullptr, nullptr, nullptr};  // device, per stage, one per system
@@ -57,13 +81,9 @@ struct Batch {
             sp[k] = nullptr;
             kb[k] = nullptr;
         }
-        for (auto &c : cls) {
-            if (c.items) (void)hipFree(c.items);
-            if (c.seg) (void)hipFree(c.seg);
-            c.items = nullptr;
-            c.seg = nullptr;
-            c.nitems = 0;
-        }
+        for (auto &c : cls) c.free_list();
+        for (auto &c : launches) c.free_list();
+        launches.clear();
         if (ctr) (void)hipFree(ctr);
         ctr = nullptr;
         if (gitems) (void)hipFree(gitems);
@@ -113,18 +133,12 @@ void stage_buffers(const Batch &b, size_t i, int k, const void **in, const void 
     *base = *in;
 }
 
-// Stencil items of class c for its tile: its systems with the most work
+// Stencil items of cl's systems for its tile: the systems with the most work
 // first (the small ones fill the tail of the persistent grid), each system
 // sweeping its tiles one orbital at a time so that neighbouring tiles are
-// resident together.  Replaces the class's device list.
-int build_class(Batch &b, size_t c, hipStream_t s) {
-    BatchClass &cl = b.cls[c];
-    if (cl.items) (void)hipFree(cl.items);
-    if (cl.seg) (void)hipFree(cl.seg);
-    cl.items = nullptr;
-    cl.seg = nullptr;
-    cl.nitems = 0;
-    b.drop_graphs();
+// resident together.  Replaces the device list.
+int build_list(Batch &b, BatchClass &cl, hipStream_t s) {
+    cl.free_list();
     std::vector<int32_t> by_work = cl.sys;
     std::stable_sort(by_work.begin(), by_work.end(), [&](int32_t p, int32_t q) {
         return b.sys[p].ham->g->np * b.sys[p].nst > b.sys[q].ham->g->np * b.sys[q].nst;
@@ -163,6 +177,36 @@ int build_class(Batch &b, size_t c, hipStream_t s) {
     if ((rc = upload(&cl.seg, seg, s))) return rc;
     cl.nitems = (int32_t)items.size();
     RSG_CHECK_HIP(hipStreamSynchronize(s));
+    return RSG_OK;
+}
+
+// The device list of class c, after its tile changed.  The merged launches
+// are rebuilt by merge_classes.
+int build_class(Batch &b, size_t c, hipStream_t s) {
+    b.drop_graphs();
+    return build_list(b, b.cls[c], s);
+}
+
+// The launches of a stage from the classes' tiles.
+int merge_classes(Batch &b, hipStream_t s) {
+    b.drop_graphs();
+    for (auto &l : b.launches) l.free_list();
+    b.launches.clear();
+    for (const auto &c : b.cls) {
+        BatchClass *l = nullptr;
+        for (auto &k : b.launches)
+            if (same_tile(k.tile, c.tile)) l = &k;
+        if (!l) {
+            b.launches.emplace_back();
+            l = &b.launches.back();
+            l->tile = c.tile;
+        }
+        l->sys.insert(l->sys.end(), c.sys.begin(), c.sys.end());
+    }
+    for (auto &l : b.launches) {
+        const int rc = build_list(b, l, s);
+        if (rc) return rc;
+    }
     return RSG_OK;
 }
 
@@ -231,7 +275,7 @@ int build_tables(Batch &b, hipStream_t s) {
     RSG_CHECK_HIP(hipStreamSynchronize(s));
     for (size_t c = 0; c < b.cls.size(); ++c)
         if ((rc = build_class(b, c, s))) return rc;
-    return RSG_OK;
+    return merge_classes(b, s);
 }
 
 int class_grid(const Batch &b, const BatchClass &c) {
@@ -251,10 +295,10 @@ int stage_launches(const Batch &b, int k, double dt, hipStream_t s) {
     const std::complex<double> c = std::complex<double>(0.0, dt) / taylor4_roots()[k];
     int rc;
     if ((rc = launch_kb_gather_batch(b.kb[k], b.gitems, b.ngitems, s))) return rc;
-    // the classes' launches share the work counters: they run one after the
-    // other on this stream, and each leaves the counters zero
-    for (const auto &cl : b.cls)
-        if ((rc = class_launch(b, cl, k, c.real(), c.imag(), s))) return rc;
+    // the launches share the work counters: they run one after the other on
+    // this stream, and each leaves the counters zero
+    for (const auto &l : b.launches)
+        if ((rc = class_launch(b, l, k, c.real(), c.imag(), s))) return rc;
     return launch_kb_scatter_batch(b.kb[k], b.sitems, b.nsitems, c.real(), c.imag(), s);
 }
 
@@ -303,7 +347,7 @@ extern "C" size_t rsg_batch_workspace_bytes(int32_t nsys, const rsg_system_desc 
 }
 
 // Systems -> size classes by tight-box width (kClassEdges), empty classes
-// dropped; every class starts with the 32 x 8 depth-2 tile.
+// dropped; every class starts with start_tile().
 static void default_classes(Batch &b) {
     constexpr int ncl = (int)(sizeof(kClassEdges) / sizeof(kClassEdges[0])) + 1;
     std::vector<BatchClass> cls(ncl);
@@ -316,8 +360,7 @@ static void default_classes(Batch &b) {
     b.cls.clear();
     for (auto &c : cls)
         if (!c.sys.empty()) {
-            c.tile = TileShape{1, 32, 8, 0};
-            c.tile.PD = 2;
+            c.tile = start_tile();
             b.cls.push_back(c);
         }
 }
@@ -402,10 +445,7 @@ extern "C" int rsg_batch_set_classes(rsg_batch_t b, const int32_t *class_of_sys,
         for (int32_t i = 0; i < nsys; ++i) cls[class_of_sys[i]].sys.push_back(i);
         for (int32_t c = 0; c < ncl; ++c)
             RSG_REQUIRE(!cls[c].sys.empty(), RSG_EINVAL, "rsg_batch_set_classes: class %d has no system", c);
-        for (auto &c : cls) {
-            c.tile = TileShape{1, 32, 8, 0};
-            c.tile.PD = 2;
-        }
+        for (auto &c : cls) c.tile = start_tile();
         b->free_tables();
         b->cls = cls;
         return build_tables(*b, (hipStream_t)stream);
@@ -438,7 +478,7 @@ extern "C" int rsg_batch_set_tile(rsg_batch_t b, const rsg_tile *t, void *stream
             const int r = build_class(*b, (size_t)c, (hipStream_t)stream);
             if (r) return r;
         }
-        return RSG_OK;
+        return merge_classes(*b, (hipStream_t)stream);
     });
 }
 
@@ -449,7 +489,10 @@ extern "C" int rsg_batch_set_class_tile(rsg_batch_t b, int32_t c, const rsg_tile
     int rc = check_batch_tile(t, "rsg_batch_set_class_tile");
     if (rc) return rc;
     set_class_tile(b, c, t);
-    return guarded([&]() { return build_class(*b, (size_t)c, (hipStream_t)stream); });
+    return guarded([&]() {
+        const int r = build_class(*b, (size_t)c, (hipStream_t)stream);
+        return r ? r : merge_classes(*b, (hipStream_t)stream);
+    });
 }
 
 static rsg_tile tile_out(const TileShape &s) { return rsg_tile{s.B, s.TX, s.TY, s.ZC, s.PD, 0, 0, s.ZM}; }
@@ -547,6 +590,7 @@ extern "C" int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, d
             total += bt;
             if (!rc) rc = build_class(*b, ci, s);
         }
+        if (!rc) rc = merge_classes(*b, s);
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (rc) {
