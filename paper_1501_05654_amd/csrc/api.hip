@@ -162,9 +162,8 @@ int check_batch(const Ham *H, const void *p, int64_t nst, int64_t ldp, const cha
 // out = H(in), FP64.
 int hpsi_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp, double field,
               const double *field_dev, void *D, hipStream_t s) {
-    int rc = launch_kb_gather(H, in, 0, 0, nst, ldp, D, s);
-    if (rc) return rc;
     StageArgs a;
+    a.D = D;
     a.in = in;
     a.out = out;
     a.mode = 0;
@@ -172,16 +171,15 @@ int hpsi_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp,
     a.ldp = ldp;
     a.field = field;
     a.field_dev = field_dev;
-    rc = launch_stencil(H, a, H.tile_for(nst, 0), s);
+    int rc = launch_stencil(H, a, H.tile_for(nst, 0), s);
     if (rc) return rc;
     return launch_kb_scatter(H, out, 0, 0, nst, ldp, D, 1.0, 0.0, nullptr, s);
 }
 
 int hdot_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp, double field, int kind, double *part,
               void *D, hipStream_t s) {
-    int rc = launch_kb_gather(H, in, 0, 0, nst, ldp, D, s);
-    if (rc) return rc;
     StageArgs a;
+    a.D = D;
     a.in = in;
     a.out = out;
     a.mode = 0;
@@ -190,7 +188,7 @@ int hdot_impl(const Ham &H, const void *in, void *out, int64_t nst, int64_t ldp,
     a.field = field;
     a.dot = kind;
     a.pair_out = part;
-    rc = launch_stencil(H, a, H.tile_for(nst, 0), s);
+    int rc = launch_stencil(H, a, H.tile_for(nst, 0), s);
     if (rc || kind == DOT_ONLY) return rc;
     return launch_kb_scatter(H, out, 0, 0, nst, ldp, D, 1.0, 0.0, nullptr, s);
 }
@@ -202,9 +200,8 @@ int stage_impl(const Ham &H, const void *in, int in_t, const void *base, void *o
                int compute, int64_t nst, int64_t ldp, double cre, double cim, double field,
                const double *field_dev, void *D, hipStream_t s, const double *mask = nullptr,
                const void *pair_y = nullptr, double *pair_out = nullptr) {
-    int rc = launch_kb_gather(H, in, in_t, compute, nst, ldp, D, s);
-    if (rc) return rc;
     StageArgs a;
+    a.D = D;
     a.in = in;
     a.base = base;
     a.out = out;
@@ -222,7 +219,7 @@ int stage_impl(const Ham &H, const void *in, int in_t, const void *base, void *o
     a.mask = mask;
     a.pair_y = pair_y;
     a.pair_out = pair_out;
-    rc = launch_stencil(H, a, H.tile_for(nst, compute), s);
+    int rc = launch_stencil(H, a, H.tile_for(nst, compute), s);
     if (rc) return rc;
     return launch_kb_scatter(H, out, out_t, compute, nst, ldp, D, cre, cim, mask, s);
 }

@@ -32,6 +32,7 @@
 // coloured so that supports of one colour are disjoint; a point covered by
 // several atoms adds them in colour order, so the result is deterministic
 // without atomics.
+#include "kb_gather.h"
 #include "rsg_internal.h"
 
 #include <algorithm>
@@ -40,111 +41,9 @@ namespace rsg {
 
 namespace {
 
-typedef double d4_t __attribute__((ext_vector_type(4)));
-typedef float f4_t __attribute__((ext_vector_type(4)));
-
-template <class T> struct V4;
-template <> struct V4<double> { using type = d4_t; };
-template <> struct V4<float> { using type = f4_t; };
-
-// Row of the accumulator element r held by lane group hi = l / 16.
-__device__ __forceinline__ int acc_row(double, int hi, int r) { return hi + 4 * r; }
-__device__ __forceinline__ int acc_row(float, int hi, int r) { return 4 * hi + r; }
-
-__device__ __forceinline__ d4_t mfma16(double a, double b, d4_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4_t mfma16(float a, float b, f4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Gather for one (atom, 16-column tile, support chunk): the support of 4-entry
-// groups is cut into nchunk contiguous chunks; the GW waves of the workgroup
-// split its chunk (wave w takes groups w, w+GW, ... of the chunk; each wave
-// accumulates its groups in ascending order) and the partial products are
-// added in wave order.  With one chunk the result goes to D scaled by h^3;
-// with several, each chunk's sum goes to the partial buffer P and the
-// scatter adds the chunks in order.  Either way the result does not
-// depend on timing.  The group loop issues the index loads of GU groups,
-// then their data loads, then the MFMAs, so GU gathers are in flight per
-// wave.
-constexpr int SP = 32;              // lanes of a scatter workgroup along the points
+constexpr int SP = 32;                   // lanes of a scatter workgroup along the points
 constexpr int SJ = kScatterPoints / SP;  // points per lane
-constexpr int SA = 16;              // atoms staged at a time
-constexpr int GW = 16;  // waves per gather workgroup
-constexpr int GU = 4;   // groups in flight per wave
-template <class Tin, class Tc>
-__device__ __forceinline__ void gather_tile(const Tin *__restrict__ in, int64_t ldo, int64_t ncols,
-                                            const int4 at, int a, int ct,
-                                            const int32_t *__restrict__ idx,
-                                            const Tc *__restrict__ p, Tc h3, Tc *__restrict__ D,
-                                            Tc (*red)[64][4], int chunk = 0, int nchunk = 1,
-                                            Tc *__restrict__ P = nullptr) {
-    using V = typename V4<Tc>::type;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int lo = l & 15, hi = l >> 4;
-    const int64_t col = (int64_t)ct * 16 + lo;
-    const bool cok = col < ncols;
-    const Tin *inc = in + (cok ? (col >> 1) * ldo + (col & 1) : 0);
-    V acc = {0, 0, 0, 0};
-    const int ngall = at.y >> 2;
-    const int per = (ngall + nchunk - 1) / nchunk;
-    const int g0 = min(ngall, chunk * per);
-    const int ngroups = min(ngall, g0 + per);
-    int gq = g0 + w;
-    for (; gq + (GU - 1) * GW < ngroups; gq += GU * GW) {
-        int64_t e[GU];
-        int32_t ix[GU];
-        Tc bv[GU], av[GU];
-#pragma unroll
-        for (int u = 0; u < GU; ++u) {
-            e[u] = (int64_t)at.x + 4 * (gq + u * GW) + hi;
-            ix[u] = idx[e[u]];
-            bv[u] = lo < 4 ? p[e[u] * 4 + lo] : (Tc)0;
-        }
-#pragma unroll
-        for (int u = 0; u < GU; ++u) av[u] = cok ? (Tc)inc[2 * (int64_t)ix[u]] : (Tc)0;
-#pragma unroll
-        for (int u = 0; u < GU; ++u) acc = mfma16(av[u], bv[u], acc);
-    }
-    for (; gq < ngroups; gq += GW) {
-        const int64_t e = (int64_t)at.x + 4 * gq + hi;
-        const Tc av = cok ? (Tc)inc[2 * (int64_t)idx[e]] : (Tc)0;
-        const Tc bv = lo < 4 ? p[e * 4 + lo] : (Tc)0;
-        acc = mfma16(av, bv, acc);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[w][l][r] = acc[r];
-    __syncthreads();
-    if (w == 0 && lo < 4) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            Tc v = red[0][l][r];
-#pragma unroll
-            for (int k = 1; k < GW; ++k) v += red[k][l][r];
-            const int64_t c = (int64_t)ct * 16 + acc_row(Tc(0), hi, r);
-            if (c < ncols) {
-                if (nchunk == 1)
-                    D[((int64_t)a * 4 + lo) * ncols + c] = h3 * v;
-                else
-                    P[(((int64_t)a * 4 + lo) * nchunk + chunk) * ncols + c] = v;
-            }
-        }
-    }
-}
-
-// blockIdx.x = atom, blockIdx.y = tile of 16 real columns, blockIdx.z =
-// support chunk (gridDim.z chunks).
-template <class Tin, class Tc>
-__global__ void __launch_bounds__(GW * 64) k_kb_gather(const Tin *__restrict__ in, int64_t ldo,
-                                                       int64_t ncols, const int4 *__restrict__ atoms,
-                                                       const int32_t *__restrict__ idx,
-                                                       const Tc *__restrict__ p, Tc h3,
-                                                       Tc *__restrict__ D, Tc *__restrict__ P) {
-    __shared__ Tc red[GW][64][4];
-    gather_tile<Tin, Tc>(in, ldo, ncols, atoms[blockIdx.x], blockIdx.x, blockIdx.y, idx, p, h3, D, red,
-                         (int)blockIdx.z, (int)gridDim.z, P);
-}
+constexpr int SA = 16;                   // atoms staged at a time
 
 // F[i] = c E_i D[a][i][n], D = h3 * (the chunk partials added in order).
 template <class Tc>
@@ -259,15 +158,17 @@ __global__ void __launch_bounds__(SP * 8) k_kb_scatter(Tout *__restrict__ out, i
                              mask, sF);
 }
 
+constexpr int GW = 16;  // waves of a batched gather workgroup
+
 // Batched forms over many systems (FP64): item {system, atom, column tile}
 // for the gather, {system, scatter item, orbital tile} for the scatter.
 __global__ void __launch_bounds__(GW * 64) k_kb_gather_batch(const KbSys *__restrict__ sys,
                                                              const int4 *__restrict__ items) {
-    __shared__ double red[GW][64][4];
+    __shared__ double red[kGatherSlots * 64];
     const int4 it = items[blockIdx.x];
     const KbSys &s = sys[it.x];
-    gather_tile<double, double>(s.in, s.ldo, s.ncols, s.atoms[it.y], it.y, it.z, s.idx, s.p, s.h3, s.D,
-                                red, it.w, s.nchunk, s.P);
+    gather_tile<GW, double, double>(s.in, s.ldo, s.ncols, s.atoms[it.y], it.y, it.z, s.idx, s.p, s.h3, s.D,
+                                    red, it.w, s.nchunk, s.P);
 }
 
 __global__ void __launch_bounds__(SP * 8) k_kb_scatter_batch(const KbSys *__restrict__ sys,
@@ -282,7 +183,7 @@ __global__ void __launch_bounds__(SP * 8) k_kb_scatter_batch(const KbSys *__rest
 }  // namespace
 
 // Support chunks per (atom, column tile): enough workgroups to fill the chip
-// when there are few atoms or few orbitals, each chunk at least 8 GW groups
+// when there are few atoms or few orbitals, each chunk at least 8 groups a slot
 // of 4 support entries of the smallest support (8 groups per wave: with
 // fewer, a batch of many small systems ran tens of thousands of nearly
 // empty gather workgroups).  The count depends on the system alone, so a
@@ -293,7 +194,7 @@ int gather_chunks(const Ham &H, int64_t nst) {
     for (int32_t a = 0; a < H.natoms; ++a) min_groups = std::min(min_groups, (H.kb_off[a + 1] - H.kb_off[a]) / 4);
     const int64_t tiles = (int64_t)H.natoms * ((2 * nst + 15) / 16);
     const int64_t want = (512 + tiles - 1) / tiles;
-    const int64_t cap = std::max<int64_t>(1, min_groups / (8 * GW));
+    const int64_t cap = std::max<int64_t>(1, min_groups / (8 * kGatherSlots));
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(want, cap), 64));
 }
 
@@ -323,32 +224,22 @@ KbDot kb_dot(const Ham &H, int64_t nst, const void *D) {
     return k;
 }
 
-int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_t nst, int64_t ldp,
-                     void *D, hipStream_t s) {
-    if (H.natoms == 0 || nst == 0) return RSG_OK;
-    const int64_t ncols = 2 * nst;
-    const int nchunk = gather_chunks(H, nst);
-    const dim3 grid((unsigned)H.natoms, (unsigned)((ncols + 15) / 16), (unsigned)nchunk);
-    const double h3 = H.g->h * H.g->h * H.g->h;
+GatherArgs gather_args(const Ham &H, int compute, int64_t nst, int64_t ldp, void *D) {
+    GatherArgs g;
+    if (!D || H.natoms == 0 || nst == 0) return g;
+    g.atoms = H.gather_items;
+    g.idx = H.kb_idx;
+    g.p = compute == 0 ? (const void *)H.kb_p : (const void *)H.kb_p32;
+    g.D = D;
+    g.ncols = 2 * nst;
+    g.ldo = 2 * ldp;
+    g.nct = (int32_t)((g.ncols + 15) / 16);
+    g.nchunk = gather_chunks(H, nst);
     // the partials start at the first 256-byte boundary after D (FP64 size)
-    void *P = nchunk > 1 ? (void *)((char *)D + gather_partials_offset(H, nst)) : nullptr;
-    if (compute == 0) {
-        if (in_t != 0) return RSG_EUNSUPPORTED;
-        k_kb_gather<double, double><<<grid, GW * 64, 0, s>>>((const double *)in, 2 * ldp, ncols,
-                                                        H.gather_items, H.kb_idx, H.kb_p, h3,
-                                                        (double *)D, (double *)P);
-    } else {
-        if (in_t == 0)
-            k_kb_gather<double, float><<<grid, GW * 64, 0, s>>>((const double *)in, 2 * ldp, ncols,
-                                                           H.gather_items, H.kb_idx, H.kb_p32,
-                                                           (float)h3, (float *)D, (float *)P);
-        else
-            k_kb_gather<float, float><<<grid, GW * 64, 0, s>>>((const float *)in, 2 * ldp, ncols,
-                                                          H.gather_items, H.kb_idx, H.kb_p32,
-                                                          (float)h3, (float *)D, (float *)P);
-    }
-    RSG_CHECK_HIP(hipGetLastError());
-    return RSG_OK;
+    g.P = g.nchunk > 1 ? (void *)((char *)D + gather_partials_offset(H, nst)) : nullptr;
+    g.nblk = H.natoms * g.nct * g.nchunk;
+    g.h3 = H.g->h * H.g->h * H.g->h;
+    return g;
 }
 
 int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t nst, int64_t ldp,

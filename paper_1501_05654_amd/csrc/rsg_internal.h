@@ -195,6 +195,7 @@ struct StageArgs {
     // over the points, one complex partial per {orbital, item} in pair_out
     // (stencil_blocks entries).
     int dot = 0;
+    void *D = nullptr;  // projector workspace: with it the launch also gathers `in` there
     int64_t nst = 0, ldp = 0;
     double field = 0;
     const double *field_dev = nullptr;
@@ -269,8 +270,19 @@ std::vector<TileShape> tile_candidates(int compute);
 // out(idx[e], col) += sum_i p[e][i] (c E_i D[a][i][.])[col], times mask(idx[e])
 // when a mask is given.  Operands are orbital-major with ldp complex values
 // between orbitals.
-int launch_kb_gather(const Ham &H, const void *in, int in_t, int compute, int64_t nst, int64_t ldp,
-                     void *D, hipStream_t s);
+// The gather of a stage's input runs as extra workgroups of the stencil launch
+// that reads the same input (StageArgs::D).
+struct GatherArgs {
+    const int4 *atoms = nullptr;
+    const int32_t *idx = nullptr;
+    const void *p = nullptr;
+    void *D = nullptr, *P = nullptr;
+    int64_t ncols = 0, ldo = 0;
+    int32_t nct = 0, nchunk = 1, nblk = 0;
+    int32_t at = 0;  // first of its nblk workgroups in the launch: 0, or after the stencil's
+    double h3 = 0;
+};
+GatherArgs gather_args(const Ham &H, int compute, int64_t nst, int64_t ldp, void *D);
 int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t nst, int64_t ldp,
                       const void *D, double cre, double cim, const double *mask, hipStream_t s);
 size_t kb_workspace_bytes(const Ham &H, int64_t nst);

@@ -174,9 +174,18 @@ int launch_stencil(const Ham &H, const StageArgs &a, const TileShape &tile, hipS
     const int nb = (int)nb64;
     // an output that no cache level holds is streamed past L2
     const bool nt = (double)a.nst * (double)g.np * (a.out_t == 0 ? 16.0 : 8.0) >= kNtStoreBytes;
+    // the projector gather's workgroups: first in a launch that is resident at
+    // once (they take as long as a short march), last in a larger one, where
+    // they fill compute units that the last marches leave idle
+    GatherArgs ga = gather_args(H, a.compute, a.nst, a.ldp, a.D);
+    ga.at = nb > 4096 ? nb : 0;
+    if ((int64_t)nb + ga.nblk > INT32_MAX) {
+        set_error("stencil launch too large");
+        return RSG_EUNSUPPORTED;
+    }
     timing_before(s);
     const int rc =
-        nt ? stencil_dispatch<true>(a, p, shape, cs, nb, s) : stencil_dispatch<false>(a, p, shape, cs, nb, s);
+        nt ? stencil_dispatch<true>(a, p, ga, shape, cs, nb, s) : stencil_dispatch<false>(a, p, ga, shape, cs, nb, s);
     timing_after(s);
     if (rc == RSG_EUNSUPPORTED) {
         set_error("stencil: unsupported tile %dx%dx%d depth %d for this precision", shape.B, shape.TX,

@@ -36,6 +36,7 @@
 // caches); each set is instantiated in a source file of its own.
 #pragma once
 
+#include "kb_gather.h"
 #include "rsg_internal.h"
 #include "stencil_common.h"
 
@@ -587,11 +588,26 @@ __device__ __forceinline__ double2 wg_sum(double2 v, double2 *lds) {
 
 template <bool NTS, int TX, int TY, int D, class Tin, class Tc, class Tout, int MODE, bool FIRST, bool MASK = false,
           bool CS = false, int SUM = 0>
-__global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>()), 2) k_stencil(KParams a) {
+__global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>()), 2)
+    k_stencil(KParams a, GatherArgs g) {
     __shared__ typename CT<Tc>::c2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
     __shared__ int4 rowl[march_rows<TX, TY, D, stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>(),
                                     std::is_same<Tc, double>::value && stage_heavy(MODE, FIRST, SUM)>()];
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    constexpr int NW = TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST, SUM>() / 64;
+    using Real = decltype(Tin{}.x);
+    if ((unsigned)((int)blockIdx.x - g.at) < (unsigned)g.nblk) {
+        // the projector gather of the same input, with the plane buffer as
+        // its LDS.  A launch of its own before the stencil cost 6-7 us on
+        // small and middle systems and 20 us on 16 atoms x 64 orbitals, all
+        // latency; here it hides under the stencil (GATHER_US).
+        static_assert(sizeof(tile) >= kGatherSlots * 64 * sizeof(Tc), "gather sums fit the plane buffer");
+        const int j = (int)blockIdx.x - g.at, chunk = j % g.nchunk, q = j / g.nchunk, atom = q / g.nct;
+        gather_tile<NW, Real, Tc>(static_cast<const Real *>(a.in), g.ldo, g.ncols, g.atoms[atom], atom, q - atom * g.nct,
+                                  g.idx, static_cast<const Tc *>(g.p), (Tc)g.h3, static_cast<Tc *>(g.D),
+                                  reinterpret_cast<Tc *>(tile), chunk, g.nchunk, static_cast<Tc *>(g.P));
+        return;
+    }
+    const int blk = xcd_remap((int)blockIdx.x - (g.at == 0 ? g.nblk : 0), (int)gridDim.x - g.nblk);
     int n, item;
     block_item(a, blk, &n, &item);
     // uniform by construction; saying so keeps the buffer resources in
@@ -663,47 +679,47 @@ __global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, !FIRST)),
 // Complex-scaled Hamiltonians use the depth-1 pipelined march; other tile
 // shapes are mapped to these (see launch_stencil).
 template <bool NTS, int TX, int TY, int D>
-int launch_fp64_cs(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
+int launch_fp64_cs(const StageArgs &a, const KParams &p, const GatherArgs &g, int nb, hipStream_t s) {
     constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0 || a.mask || a.pair_y) return RSG_EUNSUPPORTED;
     if (a.mode == 0 && a.dot == DOT_T)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_TDOT><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_TDOT><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.mode == 0 && a.dot == DOT_ONLY)
-        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_ONLY><<<nb, N1, 0, s>>>(p);
+        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, true, SUM_ONLY><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.dot)
         return RSG_EUNSUPPORTED;
     else if (a.mode == 0)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, true><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.first)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, true><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, true><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, false, true><<<nb, N2, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, false, true><<<nb + g.nblk, N2, 0, s>>>(p, g);
     return RSG_OK;
 }
 
 template <bool NTS, int TX, int TY, int D>
-int launch_fp64(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
+int launch_fp64(const StageArgs &a, const KParams &p, const GatherArgs &g, int nb, hipStream_t s) {
     constexpr int N1 = TX * TY / tile_cy(TX, TY, D, true, false), N2 = TX * TY / tile_cy(TX, TY, D, true, true);
     if (a.in_t != 0 || a.out_t != 0) return RSG_EUNSUPPORTED;
     if (a.pair_y && !(a.mode == 1 && a.first && !a.mask)) return RSG_EUNSUPPORTED;
     if (a.mode == 0 && a.dot == DOT_T)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_TDOT><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_TDOT><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.mode == 0 && a.dot == DOT_H)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_HDOT><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_HDOT><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.mode == 0 && a.dot == DOT_ONLY)
-        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_ONLY><<<nb, N1, 0, s>>>(p);
+        k_stencil<false, TX, TY, D, double2, double, double2, 0, false, false, false, SUM_ONLY><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.dot)
         return RSG_EUNSUPPORTED;
     else if (a.mode == 0)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 0, false><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.pair_y)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, SUM_PAIR><<<nb, N2, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true, false, false, SUM_PAIR><<<nb + g.nblk, N2, 0, s>>>(p, g);
     else if (a.first)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true><<<nb, N1, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, true><<<nb + g.nblk, N1, 0, s>>>(p, g);
     else if (a.mask)
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, true><<<nb, N2, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false, true><<<nb + g.nblk, N2, 0, s>>>(p, g);
     else
-        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false><<<nb, N2, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, double, double2, 1, false><<<nb + g.nblk, N2, 0, s>>>(p, g);
     return RSG_OK;
 }
 
@@ -711,17 +727,17 @@ int launch_fp64(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
 // writes complex64, the middle stages complex64 to complex64 (each its own
 // base), the last complex64 to complex128 with the complex128 base psi.
 template <bool NTS, int TX, int TY, int D>
-int launch_fp32(const StageArgs &a, const KParams &p, int nb, hipStream_t s) {
+int launch_fp32(const StageArgs &a, const KParams &p, const GatherArgs &g, int nb, hipStream_t s) {
     constexpr int NT = TX * TY;
     if (a.mode != 1 || a.pair_y || a.dot) return RSG_EUNSUPPORTED;
     if (a.in_t == 0 && a.out_t == 1 && a.first)
-        k_stencil<NTS, TX, TY, D, double2, float, float2, 1, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, double2, float, float2, 1, true><<<nb + g.nblk, NT, 0, s>>>(p, g);
     else if (a.in_t == 1 && a.out_t == 1 && a.first)
-        k_stencil<NTS, TX, TY, D, float2, float, float2, 1, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, float2, float, float2, 1, true><<<nb + g.nblk, NT, 0, s>>>(p, g);
     else if (a.in_t == 1 && a.out_t == 0 && !a.first && a.mask)
-        k_stencil<NTS, TX, TY, D, float2, float, double2, 1, false, true><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, float2, float, double2, 1, false, true><<<nb + g.nblk, NT, 0, s>>>(p, g);
     else if (a.in_t == 1 && a.out_t == 0 && !a.first)
-        k_stencil<NTS, TX, TY, D, float2, float, double2, 1, false><<<nb, NT, 0, s>>>(p);
+        k_stencil<NTS, TX, TY, D, float2, float, double2, 1, false><<<nb + g.nblk, NT, 0, s>>>(p, g);
     else
         return RSG_EUNSUPPORTED;
     return RSG_OK;
@@ -769,13 +785,14 @@ int launch_batch_shape(bool first, const KParams *sysp, const BatchItem *items, 
 // One stencil stage over nb workgroups with the compiled kernel for the
 // tile shape and the stage's types (RSG_EUNSUPPORTED if there is none).
 template <bool NTS>
-int stencil_dispatch(const StageArgs &a, const KParams &p, const TileShape &shape, bool cs, int nb, hipStream_t s) {
+int stencil_dispatch(const StageArgs &a, const KParams &p, const GatherArgs &g, const TileShape &shape, bool cs, int nb,
+                     hipStream_t s) {
     int rc = RSG_EUNSUPPORTED;
     bool found = false;
 #define RSG_TRY(X_, Y_, D_, FN)                                         \
     if (!found && shape.TX == X_ && shape.TY == Y_ && shape.PD == D_) { \
         found = true;                                                   \
-        rc = sk::FN<NTS, X_, Y_, D_>(a, p, nb, s);                      \
+        rc = sk::FN<NTS, X_, Y_, D_>(a, p, g, nb, s);                   \
     }
 #define RSG_TRY64(X_, Y_, D_) RSG_TRY(X_, Y_, D_, launch_fp64)
 #define RSG_TRY32(X_, Y_, D_) RSG_TRY(X_, Y_, D_, launch_fp32)
@@ -816,8 +833,8 @@ int batch_dispatch(const TileShape &shape, bool first, const KParams *sysp, cons
 
 // instantiated in stencil_inst.hip (false) and stencil_inst_nt.hip (true)
 #define RSG_STENCIL_INST(EXT, NTS_)                                                                           \
-    EXT template int stencil_dispatch<NTS_>(const StageArgs &, const KParams &, const TileShape &, bool, int,  \
-                                             hipStream_t);                                                    \
+    EXT template int stencil_dispatch<NTS_>(const StageArgs &, const KParams &, const GatherArgs &,            \
+                                            const TileShape &, bool, int, hipStream_t);                       \
     EXT template int batch_dispatch<NTS_>(const TileShape &, bool, const KParams *, const BatchItem *,         \
                                           const int32_t *, int32_t, double, double, int32_t *, int, hipStream_t);
 RSG_STENCIL_INST(extern, false)
