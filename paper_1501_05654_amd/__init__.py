@@ -401,8 +401,16 @@ def _nst(t, nst):
 def hpsi(ham: Hamiltonian, psi: torch.Tensor, field: float = 0.0, out: torch.Tensor | None = None,
          nst: int | None = None) -> torch.Tensor:
     _batch(psi, "psi", ham.grid.np)
-    out = torch.zeros_like(psi) if out is None else _batch(out, "out", ham.grid.np)
     n = _nst(psi, nst)
+    if out is not None:
+        _batch(out, "out", ham.grid.np)
+    elif n == psi.shape[0]:
+        # H writes every slot of every orbital: only padding is left to clear
+        out = torch.empty_like(psi)
+        if psi.shape[1] > ham.grid.np:
+            out[:, ham.grid.np:].zero_()
+    else:
+        out = torch.zeros_like(psi)
     ws = _ws(ham.workspace_bytes("hpsi", n, psi.shape[1]), psi.device)
     _check(_lib.rsg_hpsi(ham._h, _ptr(psi), _ptr(out), n, psi.shape[1], C128, float(field),
                          _ptr(ws), ws.numel(), _stream()))
