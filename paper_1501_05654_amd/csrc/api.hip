@@ -526,21 +526,30 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
                     mark[r] = a;
                 }
             // greedy colouring: atoms whose supports overlap get different
-            // colours; a point adds its atoms in colour order
+            // colours; a point adds its atoms in colour order.  mark[r]
+            // heads the list of the entries at point r so far.
+            auto unmark = [&] {
+                for (int a = 0; a < natoms; ++a)
+                    for (int64_t k = 0; k < H->kb_len[a]; ++k) mark[idx_h[H->kb_off[a] + k]] = -1;
+            };
+            unmark();
             std::vector<int> colour(natoms, -1);
-            std::vector<std::vector<char>> used;
+            std::vector<int32_t> before(total, -1), atom_of(total, 0);
             for (int a = 0; a < natoms; ++a) {
+                std::vector<char> taken(a + 1, 0);
+                for (int64_t k = 0; k < H->kb_len[a]; ++k)
+                    for (int32_t e = mark[idx_h[H->kb_off[a] + k]]; e >= 0; e = before[e]) taken[colour[atom_of[e]]] = 1;
                 int c = 0;
-                for (;; ++c) {
-                    if (c == (int)used.size()) used.emplace_back(np > 0 ? np : 1, 0);
-                    bool clash = false;
-                    for (int64_t k = 0; k < H->kb_len[a] && !clash; ++k)
-                        clash = used[c][idx_h[H->kb_off[a] + k]] != 0;
-                    if (!clash) break;
-                }
+                while (taken[c]) ++c;
                 colour[a] = c;
-                for (int64_t k = 0; k < H->kb_len[a]; ++k) used[c][idx_h[H->kb_off[a] + k]] = 1;
+                for (int64_t k = 0; k < H->kb_len[a]; ++k) {
+                    const int32_t e = (int32_t)(H->kb_off[a] + k);
+                    atom_of[e] = a;
+                    before[e] = mark[idx_h[e]];
+                    mark[idx_h[e]] = e;
+                }
             }
+            unmark();
             std::vector<int4> atoms(natoms);
             for (int a = 0; a < natoms; ++a) {
                 const int64_t padded = H->kb_off[a + 1] - H->kb_off[a];
@@ -561,8 +570,6 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
                 return fail("atom upload", e);
             k_to_float<<<nblocks_for(4 * total), 256>>>(H->kb_p, H->kb_p32, 4 * total);
             ScatterHost sc;
-            for (int a = 0; a < natoms; ++a)
-                for (int64_t k = 0; k < H->kb_len[a]; ++k) mark[idx_h[H->kb_off[a] + k]] = -1;
             build_scatter(idx_h, H->kb_off, H->kb_len, colour, mark, &sc);
             // one allocation and one copy for all of its tables
             const size_t nc = sc.entry.size();
