@@ -241,6 +241,20 @@ const TilePlan *Grid::plan(const TileShape &s, hipStream_t stream, int *err) {
     }
     TilePlan p;
     p.nitems = (int32_t)items.size();
+    // Dense: every tile spans the whole z-range and the list above is in its
+    // number order, so a workgroup computes its item instead of loading it;
+    // with the closed form of a full box's rows (KParams::row_slots), which
+    // saves the other dependent load, captured sequences go from 4.97 to 4.84
+    // us a launch on 32^3 x 4 orbitals, 13.3 to 12.5 on 48^3 x 8, 57.2 to 55.7
+    // on 96^3 x 8.  Spheres keep their lists: cut into dense plans with empty
+    // tiles they were no faster.
+    bool dense = (int)order.size() == ntx * nty && s.PT == 0 && (s.ZM == 0 || s.ZM == 2);
+    for (const int k : order) dense = dense && zlo[k] == 0 && zhi[k] == nz - 1;
+    if (dense) {
+        p.ntx = ntx;
+        p.nty = nty;
+        p.ZC = std::max(1, std::min(s.ZC, nz));
+    }
     if (p.nitems > 0) {
         hipError_t e = hipMalloc(&p.items, sizeof(int4) * items.size());
         if (e == hipSuccess)

@@ -86,6 +86,10 @@ struct TileShape {
 struct TilePlan {
     int4 *items = nullptr;  // device
     int32_t nitems = 0;
+    // Dense plans (full boxes) hold every (tx, ty) tile in every z-chunk in
+    // this order, so that a workgroup knows its item from its number: item =
+    // (c nty + ty) ntx + tx, planes [c ZC, (c + 1) ZC) within the box.
+    int32_t ntx = 0, nty = 0, ZC = 0;  // ntx = 0: not dense
 };
 
 // ------------------------------------------------------------------ grid --
@@ -228,6 +232,8 @@ struct KParams {
     int32_t ny, nz;
     int32_t axis;
     int32_t align;  // row alignment of the grid (1: compact rows, no dead slots)
+    int32_t ntx, nty, ZC;        // of a dense plan, else ntx = 0
+    int32_t row_slots, row_len;  // slots and points of every row of a full box, else 0
 };
 // Stage outputs of at least this many bytes (the size of the last-level
 // cache behind L2) are written with non-temporal stores.

@@ -30,46 +30,57 @@ std::vector<TileShape> tile_candidates(int compute) {
 // A tile wants to be wide (halo lines per column: 32 x 8 1.5, 16 x 16 1.5,
 // 32 x 16 1.0) but a launch also wants enough workgroups: below 4 M values
 // the widest tiles leave compute units idle or pay for empty columns, and
-// z is cut so that about `items` workgroups start (each chunk re-reads 8
-// planes, which such batches find in cache) but no chunk is shorter than
-// `zmin` planes.  Chunks are cut equal, at the same planes for every tile
-// (ZM = 2), and two orbitals of a tile run side by side (BO = 2, V shared).
+// z is cut so that about `items` workgroups start (768: the 256 units x 3
+// resident 32 x 8 workgroups, one round) with no chunk shorter than `zmin`
+// planes (each chunk re-reads 8 planes, which such batches find in
+// cache).  Chunks are cut equal, at the same planes for every tile (ZM = 2),
+// and two orbitals of a tile run side by side (BO = 2, V shared).
 // The lines come from timing every compiled tile with chunks of 1..96 planes
 // on 207 FP64 and 214 mixed systems (spheres 27 to 181 points across and
-// cubes of 20^3 to 120^3, 1..64 orbitals, both storages).  Time over that
-// system's best, geometric mean, FP64: this table 1.01-1.07 by size (worst
-// system 1.25), the fixed 32 x 16 / 32 x 8 / 16 x 8 choice before it
-// 1.03-1.26 (at 4-8 M values 16 x 8 tiles over the whole z-range 1.26); mixed
-// 1.01-1.05 against 1.02-1.39.
+// cubes of 20^3 to 120^3, 1..64 orbitals, both storages), below 2 M values in
+// captured graphs, so that the host does not hide in the figures.  Time over
+// that system's best, geometric mean, FP64: this table 1.01-1.08 by size (worst
+// system 1.25), the fixed 32 x 16 / 32 x 8 / 16 x 8 choice before it 1.03-1.26
+// (at 4-8 M values 16 x 8 tiles over the whole z-range 1.26); mixed 1.01-1.06
+// against 1.02-1.39.
 namespace {
 struct ShapeRule {
     double below;  // points x orbitals
     int TX, TY, PD, items, zmin;
+    double fill;  // share of a sphere's tile columns x chunks that hold points, as counted towards items
 };
 constexpr ShapeRule kRules64[] = {
-    {1e5, 32, 8, 1, 768, 1},    // latency: as many short marches as fit at once
-    {5e5, 32, 8, 1, 768, 2},
-    {4e6, 32, 8, 1, 1536, 6},   // enough chunks that the last round is full
-    {1e7, 16, 16, 1, 4096, 12}, // 3 workgroups a unit, still cache resident
-    {4e7, 32, 16, 1, 6144, 32}, // memory bound: least halo per column
-    {1e300, 32, 16, 1, 8192, 48},
+    {1e5, 32, 8, 1, 768, 1, 1.0},    // latency: as many short marches as fit at once
+    {2.5e5, 32, 8, 1, 768, 2, 1.0},
+    {1e6, 32, 8, 1, 768, 4, 0.75},
+    {4e6, 32, 8, 1, 1536, 6, 1.0},   // two rounds
+    {1e7, 16, 16, 1, 4096, 12, 1.0}, // 3 workgroups a unit, still cache resident
+    {4e7, 32, 16, 1, 6144, 32, 1.0}, // memory bound: least halo per column
+    {1e300, 32, 16, 1, 8192, 48, 1.0},
 };
+// FP32 below 1 M values: 16 x 8 tiles time alike (1.05), but their workgroups
+// are 128 threads and the projector gather that rides in the launch takes
+// twice as long on two waves (38^3 x 7, one atom, a step 93 us against 66).
 constexpr ShapeRule kRules32[] = {
-    {5e5, 32, 8, 2, 768, 1},
-    {1e7, 16, 8, 1, 6144, 8},
-    {4e7, 32, 8, 2, 8192, 24},
-    {1e300, 32, 16, 1, 4096, 64},
+    {1e5, 32, 8, 1, 768, 1, 1.0},
+    {2.5e5, 32, 8, 1, 768, 2, 1.0},
+    {1e6, 32, 8, 1, 1024, 2, 0.75},
+    {4e6, 16, 8, 1, 3072, 8, 1.0},
+    {1e7, 16, 8, 1, 6144, 8, 1.0},
+    {4e7, 32, 8, 2, 8192, 24, 1.0},
+    {1e300, 32, 16, 1, 4096, 64, 1.0},
 };
 }  // namespace
 
 TileShape default_shape(const Grid &g, int64_t nst, int compute) {
-    const double work = (double)g.npts * (double)std::max<int64_t>(nst, 1);
+    const double orbitals = (double)std::max<int64_t>(nst, 1), work = (double)g.npts * orbitals;
     const ShapeRule *r = compute == 0 ? kRules64 : kRules32;
     while (work >= r->below) ++r;
     TileShape sh{1, r->TX, r->TY, 0};
     sh.PD = r->PD;
     sh.BO = 2;
-    const double tiles = (double)((g.n[0] + r->TX - 1) / r->TX) * ((g.n[1] + r->TY - 1) / r->TY) * (double)std::max<int64_t>(nst, 1);
+    const double tiles = (double)((g.n[0] + r->TX - 1) / r->TX) * ((g.n[1] + r->TY - 1) / r->TY) * orbitals *
+                         (g.shape == RSG_BOX_SPHERE ? r->fill : 1.0);
     const double zc = std::max<double>(r->zmin, g.n[2] * tiles / r->items);
     const int chunks = std::max(1, (int)std::lround(g.n[2] / zc));
     sh.ZC = (g.n[2] + chunks - 1) / chunks;
@@ -122,6 +133,12 @@ KParams make_params(const Ham &H, const StageArgs &a, const TileShape &shape, co
     p.nz = g.n[2];
     p.axis = H.axis;
     p.align = g.align;
+    p.ntx = plan ? plan->ntx : 0;
+    p.nty = plan ? plan->nty : 0;
+    p.ZC = plan ? plan->ZC : 0;
+    const bool box = g.shape == RSG_BOX_CUBE;
+    p.row_slots = box ? (g.n[0] + g.align - 1) / g.align * g.align : 0;
+    p.row_len = box ? g.n[0] : 0;
     return p;
 }
 

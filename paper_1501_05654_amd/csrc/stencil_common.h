@@ -57,17 +57,11 @@ __device__ __forceinline__ void block_item(const KParams &a, int blk, int *n, in
 // compiler would place the select where the load is issued and wait there);
 // a masked-off lane issues its load at an out-of-range offset, which the
 // buffer hardware answers with zero.
-// SEL: the test as unsigned compares and selects, which keeps the march's
-// step free of branches.
-template <bool SEL>
+// The test is unsigned compares and a select, which keeps the march's step free
+// of branches.
 __device__ __forceinline__ int2 row_of(const KParams &a, int y, int z) {
-    if constexpr (SEL) {
-        const bool v = (unsigned)y < (unsigned)a.ny && (unsigned)z < (unsigned)a.nz;
-        return a.rows[v ? z * a.ny + y : a.ny * a.nz];
-    } else {
-        const bool v = y >= 0 && y < a.ny && z >= 0 && z < a.nz;
-        return a.rows[v ? z * a.ny + y : a.ny * a.nz];
-    }
+    const bool v = (unsigned)y < (unsigned)a.ny && (unsigned)z < (unsigned)a.nz;
+    return a.rows[v ? z * a.ny + y : a.ny * a.nz];
 }
 __device__ __forceinline__ int idx_in_row(int2 r, int x) {
     const int x0 = r.y & 0xffff, x1 = (r.y >> 16) & 0xffff;
@@ -77,7 +71,7 @@ __device__ __forceinline__ int idx_in_row(int2 r, int x) {
 // dead slot of a row-aligned grid (inside the row's x-range widened to
 // multiples of align, outside the box) gives -(index) - 2, which every load
 // treats as out of range and the store fills with zero; anything else -1.
-// SEL as for row_of: selects only.
+// SEL: selects only, which keeps the step free of branches.
 template <bool SEL>
 __device__ __forceinline__ int slot_in_row(int2 r, int x, int align) {
     const int x0 = r.y & 0xffff, x1 = (r.y >> 16) & 0xffff;

@@ -244,7 +244,13 @@ __device__ __forceinline__ void march_ring(const KParams &a, const int4 it, cons
             const int k = b * P + 4 + D + pl;
             const int yy = it.y * TY + r - 4, zz = zs + dir * k;
             const bool v = (unsigned)yy < (unsigned)a.ny && (unsigned)zz < (unsigned)a.nz && k < nk + 4 && pl < P;
-            seg[j] = a.rows[v ? zz * a.ny + yy : a.ny * a.nz];
+            // the rows of a full box need no table (FP64: the choice would
+            // take the first FP32 stage from 128 to 130 registers, 4 waves to
+            // 3: a mixed step of 500 k points x 32 orbitals 583 -> 602 us)
+            if (std::is_same<Tc, double>::value && a.row_slots)
+                seg[j] = v ? make_int2((zz * a.ny + yy) * a.row_slots, a.row_len << 16) : make_int2(0, 0);
+            else
+                seg[j] = a.rows[v ? zz * a.ny + yy : a.ny * a.nz];
         }
     };
     auto seg_store = [&](int slot) {
@@ -446,15 +452,15 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     // round trip, not one per entry)
     int2 rq[9];  // planes zs - 4 .. zs + 4
 #pragma unroll
-    for (int j = 0; j < 9; ++j) rq[j] = row_of<true>(a, y, zs + dir * (j - 4));
+    for (int j = 0; j < 9; ++j) rq[j] = row_of(a, y, zs + dir * (j - 4));
     int2 rh0[HPT];
 #pragma unroll
-    for (int j = 0; j < HPT; ++j) rh0[j] = row_of<true>(a, hl.y[j], zs);
-    int2 rf = row_of<true>(a, y, zs + dir * 5);  // rows for the loads of the first step
-    int2 ro = rq[5];                             // plane zs + 1
+    for (int j = 0; j < HPT; ++j) rh0[j] = row_of(a, hl.y[j], zs);
+    int2 rf = row_of(a, y, zs + dir * 5);  // rows for the loads of the first step
+    int2 ro = rq[5];                       // plane zs + 1
     int2 rh[HPT];
 #pragma unroll
-    for (int j = 0; j < HPT; ++j) rh[j] = row_of<true>(a, hl.y[j], zs + dir);
+    for (int j = 0; j < HPT; ++j) rh[j] = row_of(a, hl.y[j], zs + dir);
     C2 q[9];
 #pragma unroll
     for (int j = 0; j < 8; ++j) q[j] = fetch(idx_in_row(rq[j], x), true);
@@ -481,10 +487,10 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
             if (hl.ok[j]) pl[hl.l[j]] = hv[j];
         __syncthreads();
         // row entries for the next step, then this step's loads (plane k+1)
-        const int2 rf_n = row_of<true>(a, y, z + dir * 6), ro_n = row_of<true>(a, y, z + dir * 2);
+        const int2 rf_n = row_of(a, y, z + dir * 6), ro_n = row_of(a, y, z + dir * 2);
         int2 rh_n[HPT];
 #pragma unroll
-        for (int j = 0; j < HPT; ++j) rh_n[j] = row_of<true>(a, hl.y[j], z + dir * 2);
+        for (int j = 0; j < HPT; ++j) rh_n[j] = row_of(a, hl.y[j], z + dir * 2);
         const bool live = k + 1 < nk;
         nxt = fetch(live ? idx_in_row(rf, x) : -1, true);
 #pragma unroll
@@ -616,7 +622,14 @@ __global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST
     n = __builtin_amdgcn_readfirstlane(n);
     item = __builtin_amdgcn_readfirstlane(item);
     double2 pacc = make_double2(0.0, 0.0);
-    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, a.items[item], n, tile, rowl, pacc);
+    int4 it;
+    if (a.ntx) {  // dense plan
+        const int c = item / (a.ntx * a.nty), k = item - c * a.ntx * a.nty, ty = k / a.ntx;
+        it = make_int4(k - ty * a.ntx, ty, c * a.ZC, min(a.nz, (c + 1) * a.ZC));
+    } else {
+        it = a.items[item];
+    }
+    march<NTS, TX, TY, D, Tin, Tc, Tout, MODE, FIRST, MASK, CS, SUM>(a, it, n, tile, rowl, pacc);
     if constexpr (SUM != 0) {
         // this workgroup's part of the sum, at a fixed place (so the final
         // sum has a fixed order): its place in the launch order for the pair
@@ -663,6 +676,7 @@ __global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, !FIRST)),
             KParams a = sysp[__builtin_amdgcn_readfirstlane(bi.sys)];
             a.cre = cre;
             a.cim = cim;
+            a.row_slots = 0;  // rows from the table: the choice would cost registers here
             double2 unused = make_double2(0.0, 0.0);
             march<NTS, TX, TY, D, double2, double, double2, 1, FIRST, false, false>(
                 a, bi.tile, __builtin_amdgcn_readfirstlane(bi.ob), tile, rowl, unused);
