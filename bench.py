@@ -34,7 +34,7 @@ def log(msg: str):
 
 
 # the sources of the stencil kernels and their launch
-STENCIL_SOURCES = ("stencil.hip", "stencil_common.h", "stencil_inst.hip", "stencil_inst_nt.hip", "stencil_kernels.h")
+STENCIL_SOURCES = ("kb_gather.h", "stencil.hip", "stencil_common.h", "stencil_inst.hip", "stencil_inst_nt.hip", "stencil_kernels.h")
 
 
 def stencil_source_hash() -> str:
@@ -336,7 +336,7 @@ def bench_batch(args):
             tile, tms = b.autotune(reps=3)
             log(f"batch tile {tile}: {tms:.3f} ms per stage")
         # eager steps with per-launch HIP-event timing of the stencil kernel
-        # (one persistent launch per size class and stage)
+        # (one persistent launch per tile and stage)
         timed_steps = max(1, args.warmup)
         with rsg.kernel_timing() as kt:
             b.propagate(dt, timed_steps)
@@ -392,7 +392,7 @@ def bench_batch(args):
                                        "(rocprofv3 FETCH_SIZE and WRITE_SIZE on this stencil source and tile, "
                                        "scaled by a 1 GiB copy); not measured in this run")
                      if ctraffic else None,
-                     "kernel": "k_stencil_batch (persistent; one launch per size class and stage)",
+                     "kernel": "k_stencil_batch (persistent; one launch per tile and stage)",
                      "stage_ms": stage_ms, "kernel_mean_ms": kt.mean_ms, "launches_timed": kt.count},
         "per_system_eager_value": tot * 4 * per_steps / (t5 - t4),
         "cpu_baseline": None,
@@ -825,7 +825,7 @@ def bench_solve(args):
     # the slowest orbital sets the number of launched iterations; every
     # orbital's passes run until it stops
     pt_orb_iter = gg.npoints * float(np.sum(it))
-    alg = pt_orb_iter * 336 + float(np.max(it)) * gg.npoints * 8
+    alg = pt_orb_iter * 240 + float(np.max(it)) * gg.npoints * 8
     return {
         "metric": "QMR grid-pt·orbital iterations/s", "value": pt_orb_iter / el, "unit": "pt·orb·iter/s",
         "n_gpus": 1, "steps": reps, "warmup": args.warmup, "ms_per_step": el * 1e3,
@@ -836,8 +836,8 @@ def bench_solve(args):
                    "step": "one full solve from x = 0"},
         "roofline": {"bound": "hbm", "achieved": alg / el / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": alg / el / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "QMR iteration (H application + 3 fused passes)",
-                     "algorithmic_bytes": "336 B/pt·orb + 8 B/pt per iteration"},
+                     "kernel": "QMR iteration (H application + 2 fused passes)",
+                     "algorithmic_bytes": "240 B/pt·orb + 8 B/pt per iteration"},
         "iterations": {"max": int(np.max(it)), "mean": float(np.mean(it)), "min": int(np.min(it))},
         "true_rel_residual_max": float(rel.max()),
         "cpu_baseline": None,
@@ -988,12 +988,10 @@ def sub_results(args) -> dict:
                              "fd_rel_err": r["fd_rel_err"], "directional_derivative": r["directional_derivative"],
                              "central_fd": r["central_fd"],
                              "sweep_algorithmic_GBs": r["roofline"]["sweep_algorithmic_GBs"]}
-    # one tile per size class, timed per class on this workload: 16x16 at
-    # depth 2 for the narrowest and widest classes, 8x8 at depth 2 for the
-    # middle one (fixed, so that the line can carry the committed counter
-    # summary's traffic for exactly these tiles)
-    r = run("batch256", bench_batch, ns(steps=10, warmup=2, align=8,
-                                        tile="1,16,16,0,2,0,0,0;1,8,8,0,2,0,0,0;1,16,16,0,2,0,0,0"))
+    # every class on the tile a batch starts with (fixed, so that the line can
+    # carry the committed counter summary's traffic for exactly this tile);
+    # one launch per stage
+    r = run("batch256", bench_batch, ns(steps=10, warmup=2, align=8, tile="1,32,16,48,1,0,0,2"))
     out["batch256"] = {"value": r["value"], "unit": r["unit"], "ms_per_step": r["ms_per_step"],
                        "stencil_stage_ms": r["roofline"]["stage_ms"], "roofline_frac": r["roofline"]["frac"],
                        "traffic_per_stage": r["roofline"]["traffic"],
