@@ -11,10 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("align", [1, 8])
-@pytest.mark.parametrize("nst", [1, 6, 7, 50, 51, 128, 129])
+@pytest.mark.parametrize("nst", [1, 3, 4, 6, 7, 12, 13, 50, 51, 128, 129])
 def test_default_tiles_give_the_bits_of_a_fixed_one(nst, align):
     R = rsg()
-    g = R.Grid(0.25, R=6.6, align=align)  # 77 k points: lines at 1e5, 5e5, 4e6 and 1e7 values
+    g = R.Grid(0.25, R=6.6, align=align)  # 77 k points: lines at 1e5, 2.5e5, 1e6, 4e6 and 1e7 values
     gen = torch.Generator(device="cuda").manual_seed(5)
     live = torch.zeros(g.np, dtype=torch.float64, device="cuda")
     live[torch.from_numpy(g.live()).cuda()] = 1.0
