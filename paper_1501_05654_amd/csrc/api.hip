@@ -1144,7 +1144,7 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
         rest.first = true;
         int err = RSG_OK;
         // the work buffer read by the other stages holds a real stage output
-        if ((rc = launch_stencil(*H, first, default_shape(*H->g, nst, cmp), s))) {
+        if ((rc = launch_stencil(*H, first, default_shape(*H->g, nst, cmp, H->natoms > 0), s))) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return rc;
@@ -1227,7 +1227,7 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
         // phase 2: the few fastest again with more launches, so that shapes
         // within timing noise of each other are told apart
         double bt = 1e300;
-        TileShape bs = default_shape(*H->g, nst, cmp);
+        TileShape bs = default_shape(*H->g, nst, cmp, H->natoms > 0);
         if (!rc && !err) {
             std::stable_sort(timed.begin(), timed.end(),
                              [](const std::pair<double, TileShape> &p, const std::pair<double, TileShape> &q) {

@@ -113,6 +113,36 @@ Grid::~Grid() {
     if (ijk) (void)hipFree(ijk);
 }
 
+// A tile covers a row wherever the row owns slots: its x-range widened to
+// multiples of the alignment, so that the stencil writes the zeros of
+// every dead slot (the widened end may pass the box's last column).
+TileExtents Grid::extents(int TX, int TY) const {
+    const int nx = n[0], ny = n[1], nz = n[2], A = align;
+    int xend = nx;
+    for (const int2 &r : rows_host) {
+        const int a = r.y & 0xffff, b = (r.y >> 16) & 0xffff;
+        if (a < b) xend = std::max(xend, (b + A - 1) & -A);
+    }
+    TileExtents e;
+    e.ntx = (xend + TX - 1) / TX;
+    e.nty = (ny + TY - 1) / TY;
+    e.zlo.assign((size_t)e.ntx * e.nty, nz);
+    e.zhi.assign((size_t)e.ntx * e.nty, -1);
+    for (int z = 0; z < nz; ++z)
+        for (int y = 0; y < ny; ++y) {
+            const int2 r = rows_host[(size_t)z * ny + y];
+            const int a0 = r.y & 0xffff, b0 = (r.y >> 16) & 0xffff;
+            if (a0 >= b0) continue;
+            const int a = a0 & -A, b = (b0 + A - 1) & -A;
+            for (int tx = a / TX; tx <= (b - 1) / TX; ++tx) {
+                const size_t k = (size_t)(y / TY) * e.ntx + tx;
+                e.zlo[k] = std::min(e.zlo[k], z);
+                e.zhi[k] = std::max(e.zhi[k], z);
+            }
+        }
+    return e;
+}
+
 // Work items for one tile shape: every (tx, ty) tile that holds box points,
 // with its z-extent split into chunks of at most ZC planes.  Within a chunk
 // the tiles follow row order (PT = 0: ty, then tx) or the Morton (Z-curve)
@@ -140,31 +170,10 @@ const TilePlan *Grid::plan(const TileShape &s, hipStream_t stream, int *err) {
     key.ZM = s.ZM;
     auto it = plans.find(key);
     if (it != plans.end()) return &it->second;
-    const int nx = n[0], ny = n[1], nz = n[2];
-    // A tile covers a row wherever the row owns slots: its x-range widened to
-    // multiples of the alignment, so that the stencil writes the zeros of
-    // every dead slot (the widened end may pass the box's last column).
-    const int A = align;
-    int xend = nx;
-    for (const int2 &r : rows_host) {
-        const int a = r.y & 0xffff, b = (r.y >> 16) & 0xffff;
-        if (a < b) xend = std::max(xend, (b + A - 1) & -A);
-    }
-    const int ntx = (xend + s.TX - 1) / s.TX, nty = (ny + s.TY - 1) / s.TY;
-    std::vector<int> zlo((size_t)ntx * nty, nz), zhi((size_t)ntx * nty, -1);
-    for (int z = 0; z < nz; ++z)
-        for (int y = 0; y < ny; ++y) {
-            const int2 r = rows_host[(size_t)z * ny + y];
-            const int a0 = r.y & 0xffff, b0 = (r.y >> 16) & 0xffff;
-            if (a0 >= b0) continue;
-            const int a = a0 & -A, b = (b0 + A - 1) & -A;
-            const int ty = y / s.TY;
-            for (int tx = a / s.TX; tx <= (b - 1) / s.TX; ++tx) {
-                const size_t k = (size_t)ty * ntx + tx;
-                zlo[k] = std::min(zlo[k], z);
-                zhi[k] = std::max(zhi[k], z);
-            }
-        }
+    const int nz = n[2];
+    const TileExtents ext = extents(s.TX, s.TY);
+    const int ntx = ext.ntx, nty = ext.nty;
+    const std::vector<int> &zlo = ext.zlo, &zhi = ext.zhi;
     // non-empty tiles in the order used inside a z-chunk
     std::vector<int> order;
     for (int ty = 0; ty < nty; ++ty)

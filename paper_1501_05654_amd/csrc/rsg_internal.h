@@ -7,7 +7,9 @@
 #include <cstdint>
 #include <cstdio>
 #include <map>
+#include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "rsg.h"
@@ -94,6 +96,13 @@ struct TilePlan {
 
 // ------------------------------------------------------------------ grid --
 
+// Planes [zlo, zhi] of every (tx, ty) tile of a grid in which it covers slots,
+// at ty * ntx + tx (zhi < zlo: none).
+struct TileExtents {
+    int ntx = 0, nty = 0;
+    std::vector<int> zlo, zhi;
+};
+
 struct Grid {
     int32_t shape = 0;
     int32_t n[3] = {0, 0, 0};  // tight box x, y, z
@@ -109,7 +118,11 @@ struct Grid {
     std::vector<int2> rows_host;
     int32_t *ijk = nullptr;     // device [np][3]
     std::map<TileShape, TilePlan> plans;
+    // default_shape's results by {orbitals, compute, projectors}
+    mutable std::mutex defaults_mu;
+    mutable std::map<std::tuple<int64_t, int, bool>, TileShape> defaults;
     ~Grid();
+    TileExtents extents(int TX, int TY) const;
     const TilePlan *plan(const TileShape &s, hipStream_t stream, int *err);
 };
 
@@ -267,7 +280,8 @@ int launch_stencil_batch(const TileShape &shape, int mode, bool first, bool nt, 
                          int32_t *ctr, int grid, hipStream_t s);
 // Resident workgroups of the batched kernel for this shape (or an error code).
 int stencil_batch_grid(const TileShape &shape, bool first, bool nt);
-TileShape default_shape(const Grid &g, int64_t nst, int compute);
+// Tile of a launch that nobody tuned; projectors: its gather rides in the launch.
+TileShape default_shape(const Grid &g, int64_t nst, int compute, bool projectors);
 std::vector<TileShape> tile_candidates(int compute);
 
 // KB projectors.  gather: D[a][i][col] = h^3 sum_e p[e][i] in(idx[e], col)

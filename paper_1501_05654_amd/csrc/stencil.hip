@@ -29,69 +29,123 @@ std::vector<TileShape> tile_candidates(int compute) {
 // Tile and z-chunk of a launch nobody tuned, by its points times orbitals.
 // A tile wants to be wide (halo lines per column: 32 x 8 1.5, 16 x 16 1.5,
 // 32 x 16 1.0) but a launch also wants enough workgroups: below 4 M values
-// the widest tiles leave compute units idle or pay for empty columns, and
-// z is cut so that about `items` workgroups start (768: the 256 units x 3
-// resident 32 x 8 workgroups, one round) with no chunk shorter than `zmin`
-// planes (each chunk re-reads 8 planes, which such batches find in
-// cache).  Chunks are cut equal, at the same planes for every tile (ZM = 2),
-// and two orbitals of a tile run side by side (BO = 2, V shared).
-// The lines come from timing every compiled tile with chunks of 1..96 planes
-// on 207 FP64 and 214 mixed systems (spheres 27 to 181 points across and
-// cubes of 20^3 to 120^3, 1..64 orbitals, both storages), below 2 M values in
-// captured graphs, so that the host does not hide in the figures.  Time over
-// that system's best, geometric mean, FP64: this table 1.01-1.08 by size (worst
-// system 1.25), the fixed 32 x 16 / 32 x 8 / 16 x 8 choice before it 1.03-1.26
-// (at 4-8 M values 16 x 8 tiles over the whole z-range 1.26); mixed 1.01-1.06
-// against 1.02-1.39.
+// the widest tiles leave compute units idle or pay for empty columns, and z is
+// cut into as many equal chunks, at the same planes for every tile (ZM = 2), as
+// start at most `items` workgroups and hold at least `zmin` planes (each chunk
+// re-reads 8 planes, which such batches find in cache).  There the workgroups
+// are counted as the plan lists them: the best chunk of a small launch is
+// the shortest whose workgroups are all resident at once (3 of 256 threads or 6
+// of 128 on each of 256 units: 768, 1536), and one more round costs up to 1.2
+// times as long.  Larger launches take several rounds anyway; they count every
+// tile of the box in every chunk and round the number of chunks.
+// All tiles of an orbital run before the next orbital's (BO = 1) in these:
+// a pair of orbitals side by side reads V half as often, which batches that stay in
+// cache do not feel, but spreads an orbital's halos over more XCDs (45 points
+// across x 3 orbitals, 32 x 8: 6.97 us a stage in pairs, 6.2 without).
+// The lines come from timing every compiled tile, chunks of 1..64 planes and
+// both orders on 372 FP64 and 302 mixed systems of 1e4 to 3.5e7 values (spheres 27
+// to 149 points across, cubes of 20^3 to 118^3, 1..64 orbitals, both storages, with
+// and without projectors) in captured graphs.
 namespace {
 struct ShapeRule {
     double below;  // points x orbitals
-    int TX, TY, PD, items, zmin;
-    double fill;  // share of a sphere's tile columns x chunks that hold points, as counted towards items
+    int TX, TY, PD, items, zmin, BO;
+    bool counted;  // items: the plan's, else every tile of the box
 };
 constexpr ShapeRule kRules64[] = {
-    {1e5, 32, 8, 1, 768, 1, 1.0},    // latency: as many short marches as fit at once
-    {2.5e5, 32, 8, 1, 768, 2, 1.0},
-    {1e6, 32, 8, 1, 768, 4, 0.75},
-    {4e6, 32, 8, 1, 1536, 6, 1.0},   // two rounds
-    {1e7, 16, 16, 1, 4096, 12, 1.0}, // 3 workgroups a unit, still cache resident
-    {4e7, 32, 16, 1, 6144, 32, 1.0}, // memory bound: least halo per column
-    {1e300, 32, 16, 1, 8192, 48, 1.0},
+    {1e6, 32, 8, 1, 768, 1, 1, true},     // one round
+    {2e6, 32, 8, 1, 1536, 6, 1, true},
+    {4e6, 32, 8, 1, 2048, 8, 1, true},
+    {1e7, 16, 16, 1, 4096, 12, 2, false},  // 3 workgroups a unit, still cache resident
+    {4e7, 32, 16, 1, 6144, 32, 2, false},  // memory bound: least halo per column
+    {1e300, 32, 16, 1, 8192, 48, 2, false},
 };
-// FP32 below 1 M values: 16 x 8 tiles time alike (1.05), but their workgroups
-// are 128 threads and the projector gather that rides in the launch takes
-// twice as long on two waves (38^3 x 7, one atom, a step 93 us against 66).
+// Spheres without projectors: 16-wide tiles leave fewer columns of the rim
+// empty (45 points across x 13 orbitals 12.9 us a stage, 14.8 in 32 x 8; boxes
+// take 1.04 times as long in 16 x 8).
+constexpr ShapeRule kSphere64[] = {
+    {2.5e5, 32, 8, 1, 768, 1, 1, true},
+    {1e6, 16, 8, 1, 1536, 3, 1, true},
+    {2e6, 16, 8, 1, 3072, 4, 1, true},
+    {4e6, 16, 8, 1, 4096, 4, 1, true},
+    {1e7, 16, 16, 1, 4096, 12, 2, false},
+    {4e7, 32, 16, 1, 6144, 32, 2, false},
+    {1e300, 32, 16, 1, 8192, 48, 2, false},
+};
 constexpr ShapeRule kRules32[] = {
-    {1e5, 32, 8, 1, 768, 1, 1.0},
-    {2.5e5, 32, 8, 1, 768, 2, 1.0},
-    {1e6, 32, 8, 1, 1024, 2, 0.75},
-    {4e6, 16, 8, 1, 3072, 8, 1.0},
-    {1e7, 16, 8, 1, 6144, 8, 1.0},
-    {4e7, 32, 8, 2, 8192, 24, 1.0},
-    {1e300, 32, 16, 1, 4096, 64, 1.0},
+    {1e5, 32, 8, 1, 512, 1, 1, true},
+    {2.5e5, 16, 8, 1, 1024, 1, 1, true},
+    {1e6, 16, 8, 1, 2048, 3, 1, true},
+    {2e6, 16, 8, 1, 2048, 4, 1, true},
+    {1e7, 16, 8, 1, 4096, 8, 1, true},
+    {4e7, 32, 8, 2, 8192, 24, 2, false},
+    {1e300, 32, 16, 1, 4096, 64, 2, false},
 };
+// With projectors their gather rides in the launch with the tile's own threads,
+// and on the two waves of a 16 x 8 tile it takes twice as long (FP32, 41^3 x 18
+// orbitals, two atoms: a stage 25.8 us against 21.3), so that these take wider
+// tiles and longer chunks.
+constexpr ShapeRule kRules32p[] = {
+    {2.5e5, 32, 8, 1, 512, 1, 1, true},
+    {1e6, 32, 8, 1, 768, 4, 1, true},
+    {2e6, 32, 8, 1, 2048, 4, 1, true},
+    {4e6, 32, 8, 2, 2048, 6, 1, true},
+    {1e7, 32, 8, 2, 3072, 8, 1, true},
+    {4e7, 32, 8, 2, 8192, 24, 2, false},
+    {1e300, 32, 16, 1, 4096, 64, 2, false},
+};
+
+TileShape shape_by_rule(const Grid &g, int64_t nst, int compute, bool projectors) {
+    const int nz = g.n[2];
+    const double orbitals = (double)std::max<int64_t>(nst, 1), work = (double)g.npts * orbitals;
+    const ShapeRule *r = compute != 0 ? (projectors ? kRules32p : kRules32)
+                         : g.shape == RSG_BOX_SPHERE && !projectors ? kSphere64
+                                                                    : kRules64;
+    while (work >= r->below) ++r;
+    TileShape sh{1, r->TX, r->TY, nz};
+    sh.PD = r->PD;
+    sh.BO = r->BO;
+    if (r->counted) {
+        const TileExtents e = g.extents(r->TX, r->TY);
+        for (int chunks = 1; chunks <= nz; ++chunks) {
+            const int zc = (nz + chunks - 1) / chunks;
+            int64_t items = 0;
+            for (size_t k = 0; k < e.zlo.size(); ++k)
+                if (e.zhi[k] >= e.zlo[k]) items += e.zhi[k] / zc - e.zlo[k] / zc + 1;
+            if (zc < r->zmin || (double)items * orbitals > r->items) break;
+            sh.ZC = zc;
+        }
+    } else {
+        const double tiles = (double)((g.n[0] + r->TX - 1) / r->TX) * ((g.n[1] + r->TY - 1) / r->TY) * orbitals;
+        const double zc = std::max<double>(r->zmin, nz * tiles / r->items);
+        const int chunks = std::max(1, (int)std::lround(nz / zc));
+        sh.ZC = (nz + chunks - 1) / chunks;
+    }
+    sh.ZM = sh.ZC < nz ? 2 : 0;
+    return sh;
+}
 }  // namespace
 
-TileShape default_shape(const Grid &g, int64_t nst, int compute) {
-    const double orbitals = (double)std::max<int64_t>(nst, 1), work = (double)g.npts * orbitals;
-    const ShapeRule *r = compute == 0 ? kRules64 : kRules32;
-    while (work >= r->below) ++r;
-    TileShape sh{1, r->TX, r->TY, 0};
-    sh.PD = r->PD;
-    sh.BO = 2;
-    const double tiles = (double)((g.n[0] + r->TX - 1) / r->TX) * ((g.n[1] + r->TY - 1) / r->TY) * orbitals *
-                         (g.shape == RSG_BOX_SPHERE ? r->fill : 1.0);
-    const double zc = std::max<double>(r->zmin, g.n[2] * tiles / r->items);
-    const int chunks = std::max(1, (int)std::lround(g.n[2] / zc));
-    sh.ZC = (g.n[2] + chunks - 1) / chunks;
-    sh.ZM = chunks > 1 ? 2 : 0;
-    return sh;
+TileShape default_shape(const Grid &g, int64_t nst, int compute, bool projectors) {
+    const auto key = std::make_tuple(nst, compute, projectors);
+    try {
+        {
+            std::lock_guard<std::mutex> lk(g.defaults_mu);
+            const auto it = g.defaults.find(key);
+            if (it != g.defaults.end()) return it->second;
+        }
+        const TileShape sh = shape_by_rule(g, nst, compute, projectors);
+        std::lock_guard<std::mutex> lk(g.defaults_mu);
+        return g.defaults[key] = sh;
+    } catch (const std::bad_alloc &) {
+        return TileShape{1, 32, 8, g.n[2]};
+    }
 }
 
 TileShape Ham::tile_for(int64_t nst, int compute) const {
     auto it = tiles.find(std::make_pair(nst, compute));
     if (it != tiles.end()) return it->second;
-    return default_shape(*g, nst, compute);
+    return default_shape(*g, nst, compute, natoms > 0);
 }
 
 KParams make_params(const Ham &H, const StageArgs &a, const TileShape &shape, const TilePlan *plan) {
