@@ -363,11 +363,14 @@ int rsg_get_tile(rsg_ham_t H, int64_t nst, int32_t dtype, rsg_tile *t);
 
 /* Tile autotuner for the Taylor(4) step on psi (device [nst][ldp], left
  * unchanged).  Phase 1 times one of the middle Taylor stages (reads a work
- * buffer, writes the other) for every compiled tile
- * shape, z-chunk lengths {whole, 64, 32, and 16, 8, 4, 2, 1 when the batch
- * has few tiles}, PT {0, 1}, BO {0, 1, 2, 4} and ZM {0, 1} with HIP events (best of
+ * buffer, writes the other, and gathers the projectors as the stages of a step
+ * do) for every compiled tile
+ * shape, z-chunk lengths {whole, 96, 64, 32, and 16, 8, 4, 2, 1 when the batch
+ * has few tiles}, PT {0, 1}, BO {0, 1, 2, 4} and ZM {0, 1} (and 2 in row order
+ * with BO 1 or 2) with HIP events (best of
  * reps launches after a warm-up launch; a stage under 0.2 ms is timed as the
- * mean of 16 back-to-back launches).  Phase 2 re-times the six fastest
+ * mean of 16 back-to-back launches).  Phase 2 re-times the tile in use, the
+ * default tile and the six fastest
  * on the stencil work of a whole step (the first stage plus three later
  * ones, 3 reps launches each), keeps the fastest for (nst, dtype) and
  * returns it in *best and that step time in *best_ms (either may be NULL).
@@ -379,8 +382,9 @@ int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t ldp, int32_t
 /* rsg_autotune with a tile cache in the text file cache_path, one line per
  * tuned case: "<key> | B TX TY ZC PD PT BO ZM | ms".  The key names the box
  * shape, its dimensions, point and slot counts, the row alignment, nst, the
- * dtype, complex scaling and mask use, and the device (architecture name
- * and compute-unit count).  If the file holds the key (the last such line
+ * dtype, complex scaling and mask use, the projectors' atoms and support entries,
+ * the revision of the stencil kernels, and the device (architecture name
+ * and compute-unit count); entries of another revision are left alone.  If the file holds the key (the last such line
  * wins) the tile is set with no kernel launch and *cached = 1; otherwise
  * the autotuner runs as rsg_autotune does, its choice is appended to the
  * file and *cached = 0.  best, best_ms and cached may be NULL.  The file is

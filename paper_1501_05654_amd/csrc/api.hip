@@ -1083,8 +1083,9 @@ extern "C" int rsg_get_tile(rsg_ham_t H, int64_t nst, int32_t dtype, rsg_tile *t
 }
 
 // Times one Taylor stage (out = psi + c H psi into the workspace, psi
-// untouched) for every compiled tile shape, z-chunk length, tile order,
-// block order and z-march, re-times the six fastest with three times the
+// untouched, with the projector gather that rides in its launch) for every
+// compiled tile shape, z-chunk length, tile order, block order and z-march,
+// re-times the six fastest, the default and the tile in use with three times the
 // launches, keeps the fastest for (nst, dtype) and reports it.
 extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t ldp, int32_t dtype,
                             void *ws, size_t ws_bytes, int32_t reps, rsg_tile *best, double *best_ms,
@@ -1101,6 +1102,7 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
     Carve c(ws, ws_bytes);
     void *w1 = c.take(batch_bytes(nst, ldp, cmp ? 8 : 16));
     void *w2 = c.take(batch_bytes(nst, ldp, cmp ? 8 : 16));
+    void *D = c.take(kb_workspace_bytes(*H, nst));
     if (!c.ok) {
         set_error("rsg_autotune: workspace carve failed");
         return RSG_ENOMEM;
@@ -1135,6 +1137,7 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
         first.nst = nst;
         first.ldp = ldp;
         first.cim = -1e-3;
+        first.D = D;  // the gather takes the tile's own threads: its time is part of the tile's
         StageArgs rest = first;
         rest.in = w1;
         rest.in_t = wt;
@@ -1225,21 +1228,23 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
             if (rc || err) break;
         }
         // phase 2: the few fastest again with more launches, so that shapes
-        // within timing noise of each other are told apart
+        // within timing noise of each other are told apart; before them the
+        // tile in use and the default, whose chunks phase 1 need not hold
         double bt = 1e300;
-        TileShape bs = default_shape(*H->g, nst, cmp, H->natoms > 0);
+        TileShape bs = H->tile_for(nst, cmp);
         if (!rc && !err) {
             std::stable_sort(timed.begin(), timed.end(),
                              [](const std::pair<double, TileShape> &p, const std::pair<double, TileShape> &q) {
                                  return p.first < q.first;
                              });
-            const size_t keep = std::min<size_t>(6, timed.size());
-            for (size_t k = 0; k < keep && !rc; ++k) {
+            std::vector<TileShape> last = {bs, default_shape(*H->g, nst, cmp, H->natoms > 0)};
+            for (size_t k = 0; k < std::min<size_t>(6, timed.size()); ++k) last.push_back(timed[k].second);
+            for (const TileShape &sh : last) {
                 double t = 0;
-                if ((rc = time_step(timed[k].second, 3 * reps, &t))) break;
+                if ((rc = time_step(sh, 3 * reps, &t))) break;
                 if (t < bt) {
                     bt = t;
-                    bs = timed[k].second;
+                    bs = sh;
                 }
             }
         }
@@ -1257,7 +1262,8 @@ extern "C" int rsg_autotune(rsg_ham_t H, const void *psi, int64_t nst, int64_t l
 
 // Key of a tuned tile in the cache file: everything the choice depends on
 // (box shape and size, storage alignment, orbital count, precision, the
-// kernel family in use, and the device).
+// kernel family in use and its revision, the projectors whose gather rides in the
+// launch, and the device).
 static int tile_cache_key(const Ham &H, int64_t nst, int32_t dtype, std::string *key) {
     int dev = 0;
     hipDeviceProp_t prop;
@@ -1265,9 +1271,11 @@ static int tile_cache_key(const Ham &H, int64_t nst, int32_t dtype, std::string 
     RSG_CHECK_HIP(hipGetDeviceProperties(&prop, dev));
     const Grid &g = *H.g;
     char buf[512];
-    snprintf(buf, sizeof buf, "box=%d dims=%dx%dx%d points=%lld slots=%lld align=%d nst=%lld dtype=%d cs=%d mask=%d dev=%s/%d",
+    snprintf(buf, sizeof buf, "box=%d dims=%dx%dx%d points=%lld slots=%lld align=%d nst=%lld dtype=%d cs=%d mask=%d atoms=%d support=%lld "
+             "kernels=%d dev=%s/%d",
              g.shape, g.n[0], g.n[1], g.n[2], (long long)g.npts, (long long)g.np, g.align, (long long)nst, dtype,
-             H.complex_scaled() ? 1 : 0, H.mask ? 1 : 0, prop.gcnArchName, prop.multiProcessorCount);
+             H.complex_scaled() ? 1 : 0, H.mask ? 1 : 0, H.natoms, (long long)(H.natoms ? H.kb_off[H.natoms] : 0),
+             kStencilRevision, prop.gcnArchName, prop.multiProcessorCount);
     *key = buf;
     return RSG_OK;
 }

@@ -283,6 +283,9 @@ int stencil_batch_grid(const TileShape &shape, bool first, bool nt);
 // Tile of a launch that nobody tuned; projectors: its gather rides in the launch.
 TileShape default_shape(const Grid &g, int64_t nst, int compute, bool projectors);
 std::vector<TileShape> tile_candidates(int compute);
+// Part of a tuned tile's key: raised with every change of the stencil kernels that
+// may change which tile is the fastest.
+constexpr int kStencilRevision = 2;
 
 // KB projectors.  gather: D[a][i][col] = h^3 sum_e p[e][i] in(idx[e], col)
 // (col over the 2*nst real columns: re and im of each orbital), or its
