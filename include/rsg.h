@@ -451,8 +451,10 @@ int rsg_batch_get_tile(rsg_batch_t b, rsg_tile *t);
 int rsg_batch_get_class_tile(rsg_batch_t b, int32_t c, rsg_tile *t);
 
 /* Class c: its number of systems, its stencil work items per stage
- * (tiles x z-chunks x orbitals) and the workgroups its persistent launch
- * runs (at most nitems; each takes items until the list is exhausted). */
+ * (tiles x z-chunks x orbitals) and the workgroups of the persistent launch
+ * that runs them, together with those of the other classes on the same tile
+ * (at most that launch's items; each workgroup takes items until the list is
+ * exhausted). */
 int rsg_batch_class_info(rsg_batch_t b, int32_t c, int32_t *nsys, int64_t *nitems, int32_t *grid);
 
 /* At most max_workgroups persistent workgroups per stencil launch (0: as

@@ -16,28 +16,37 @@
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
+#include <memory>
 #include <tuple>
 
 namespace rsg {
 
-// Systems of one size class share a tile shape and a persistent launch per
-// stage; the classes of a stage run back to back on the caller's stream.
+// Systems of one size class share a tile shape.
 struct BatchClass {
     TileShape tile{1, 32, 16, 48};
-    std::vector<int32_t> sys;    // member systems
-    BatchItem *items = nullptr;  // device work list of this class
+    std::vector<int32_t> sys;  // member systems
+    int64_t nitems = 0;        // their work items per stage
+};
+
+// One persistent launch of a stage: classes on one tile run as one (its list over
+// all their systems), so a stage drains the chip once, not once per class.  The
+// launches of a stage run back to back on the caller's stream.
+struct BatchLaunch {
+    TileShape tile{1, 32, 16, 48};
+    std::vector<int32_t> sys;
+    BatchItem *items = nullptr;  // device work list
     int32_t *seg = nullptr;      // device bounds of the list's per-XCD segments
     int32_t nitems = 0;
-    int grid = 0;                // resident workgroups of the class's kernel
-    void free_list() {
+    int grid = 0;                // resident workgroups of the tile's kernel
+    BatchLaunch() = default;
+    BatchLaunch(const BatchLaunch &) = delete;
+    BatchLaunch &operator=(const BatchLaunch &) = delete;
+    ~BatchLaunch() {
         if (items) (void)hipFree(items);
         if (seg) (void)hipFree(seg);
-        items = nullptr;
-        seg = nullptr;
-        nitems = 0;
     }
 };
+using BatchLaunches = std::vector<std::unique_ptr<BatchLaunch>>;
 
 // Tile every class starts with: 32 x 16, two columns per thread, z in chunks
 // of 48 planes at common planes.  Of ten shapes x five chunk lengths per class
@@ -57,9 +66,7 @@ struct Batch {
     std::vector<rsg_system_desc> sys;
     std::vector<void *> w1, w2, D;  // per-system work buffers inside the caller's workspace
     std::vector<BatchClass> cls;
-    // Classes on one tile run as one launch (its list over all their systems),
-    // so a stage drains the chip once, not once per class.
-    std::vector<BatchClass> launches;
+    BatchLaunches launches;  // one per tile among the classes
     int32_t grid_cap = 0;  // at most this many persistent workgroups per launch (0: no cap)
     bool nt = false;       // stage outputs written with non-temporal stores
     KParams *sp[4] = {nullptr, nullptr, nullptr, nullptr};  // device, per stage, one per system
@@ -81,8 +88,6 @@ struct Batch {
             sp[k] = nullptr;
             kb[k] = nullptr;
         }
-        for (auto &c : cls) c.free_list();
-        for (auto &c : launches) c.free_list();
         launches.clear();
         if (ctr) (void)hipFree(ctr);
         ctr = nullptr;
@@ -133,87 +138,106 @@ void stage_buffers(const Batch &b, size_t i, int k, const void **in, const void 
     *base = *in;
 }
 
-// Stencil items of cl's systems for its tile: the systems with the most work
+// The launch of these systems on one tile: the systems with the most work
 // first (the small ones fill the tail of the persistent grid), each system
 // sweeping its tiles one orbital at a time so that neighbouring tiles are
-// resident together.  Replaces the device list.
-int build_list(Batch &b, BatchClass &cl, hipStream_t s) {
-    cl.free_list();
-    std::vector<int32_t> by_work = cl.sys;
-    std::stable_sort(by_work.begin(), by_work.end(), [&](int32_t p, int32_t q) {
-        return b.sys[p].ham->g->np * b.sys[p].nst > b.sys[q].ham->g->np * b.sys[q].nst;
-    });
-    std::vector<BatchItem> items;
-    int err = RSG_OK;
-    for (const int32_t i : by_work) {
-        const rsg_system_desc &d = b.sys[i];
-        TileShape sh = cl.tile;
-        sh.PT = 0;
-        sh.BO = 0;
-        sh.ZC = sh.ZC > 0 ? sh.ZC : d.ham->g->n[2];  // ZM as chosen for the class
-        const TilePlan *plan = d.ham->g->plan(sh, s, &err);
-        if (!plan) return err;
-        // copy the plan's items back to the host to expand them per orbital
-        std::vector<int4> pit(plan->nitems);
-        if (plan->nitems)
-            RSG_CHECK_HIP(hipMemcpy(pit.data(), plan->items, sizeof(int4) * plan->nitems, hipMemcpyDeviceToHost));
-        for (int n = 0; n < (int)d.nst; ++n)
-            for (const int4 &t : pit) items.push_back(BatchItem{t, i, n});
-    }
-    // per-XCD segments of about equal work: a march costs its z-planes plus
-    // the planes that fill the register ring
-    std::vector<int64_t> cum(items.size() + 1, 0);
-    for (size_t w = 0; w < items.size(); ++w)
-        cum[w + 1] = cum[w] + std::abs(items[w].tile.w - items[w].tile.z) + 8;
-    std::vector<int32_t> seg(kBatchQueues + 1, 0);
-    for (int q = 1; q < kBatchQueues; ++q)
-        seg[q] = (int32_t)(std::lower_bound(cum.begin(), cum.end(), cum.back() * q / kBatchQueues) - cum.begin());
-    seg[kBatchQueues] = (int32_t)items.size();
-    for (int q = 1; q <= kBatchQueues; ++q) seg[q] = std::max(seg[q], seg[q - 1]);
-    cl.grid = stencil_batch_grid(cl.tile, true, b.nt);
-    if (cl.grid <= 0) return cl.grid;
-    int rc = upload(&cl.items, items, s);
-    if (rc) return rc;
-    if ((rc = upload(&cl.seg, seg, s))) return rc;
-    cl.nitems = (int32_t)items.size();
-    RSG_CHECK_HIP(hipStreamSynchronize(s));
-    return RSG_OK;
-}
-
-// The device list of class c, after its tile changed.  The merged launches
-// are rebuilt by merge_classes.
-int build_class(Batch &b, size_t c, hipStream_t s) {
-    b.drop_graphs();
-    return build_list(b, b.cls[c], s);
-}
-
-// The launches of a stage from the classes' tiles.
-int merge_classes(Batch &b, hipStream_t s) {
-    b.drop_graphs();
-    for (auto &l : b.launches) l.free_list();
-    b.launches.clear();
-    for (const auto &c : b.cls) {
-        BatchClass *l = nullptr;
-        for (auto &k : b.launches)
-            if (same_tile(k.tile, c.tile)) l = &k;
-        if (!l) {
-            b.launches.emplace_back();
-            l = &b.launches.back();
-            l->tile = c.tile;
+// resident together.  Null, with the code in *rc, on failure.
+std::unique_ptr<BatchLaunch> build_launch(const Batch &b, const TileShape &tile, const std::vector<int32_t> &members,
+                                          hipStream_t s, int *rc) {
+    auto l = std::make_unique<BatchLaunch>();
+    l->tile = tile;
+    l->sys = members;
+    *rc = [&]() -> int {
+        std::vector<int32_t> by_work = members;
+        std::stable_sort(by_work.begin(), by_work.end(), [&](int32_t p, int32_t q) {
+            return b.sys[p].ham->g->np * b.sys[p].nst > b.sys[q].ham->g->np * b.sys[q].nst;
+        });
+        std::vector<BatchItem> items;
+        int err = RSG_OK;
+        for (const int32_t i : by_work) {
+            const rsg_system_desc &d = b.sys[i];
+            TileShape sh = tile;
+            sh.PT = 0;
+            sh.BO = 0;
+            sh.ZC = sh.ZC > 0 ? sh.ZC : d.ham->g->n[2];  // ZM as chosen for the class
+            const TilePlan *plan = d.ham->g->plan(sh, s, &err);
+            if (!plan) return err;
+            // copy the plan's items back to the host to expand them per orbital
+            std::vector<int4> pit(plan->nitems);
+            if (plan->nitems)
+                RSG_CHECK_HIP(hipMemcpy(pit.data(), plan->items, sizeof(int4) * plan->nitems, hipMemcpyDeviceToHost));
+            for (int n = 0; n < (int)d.nst; ++n)
+                for (const int4 &t : pit) items.push_back(BatchItem{t, i, n});
         }
-        l->sys.insert(l->sys.end(), c.sys.begin(), c.sys.end());
+        // per-XCD segments of about equal work: a march costs its z-planes plus
+        // the planes that fill the register ring
+        std::vector<int64_t> cum(items.size() + 1, 0);
+        for (size_t w = 0; w < items.size(); ++w)
+            cum[w + 1] = cum[w] + std::abs(items[w].tile.w - items[w].tile.z) + 8;
+        std::vector<int32_t> seg(kBatchQueues + 1, 0);
+        for (int q = 1; q < kBatchQueues; ++q)
+            seg[q] = (int32_t)(std::lower_bound(cum.begin(), cum.end(), cum.back() * q / kBatchQueues) - cum.begin());
+        seg[kBatchQueues] = (int32_t)items.size();
+        for (int q = 1; q <= kBatchQueues; ++q) seg[q] = std::max(seg[q], seg[q - 1]);
+        l->grid = stencil_batch_grid(tile, true, b.nt);
+        if (l->grid <= 0) return l->grid;
+        int r = upload(&l->items, items, s);
+        if (r) return r;
+        if ((r = upload(&l->seg, seg, s))) return r;
+        l->nitems = (int32_t)items.size();
+        RSG_CHECK_HIP(hipStreamSynchronize(s));
+        return RSG_OK;
+    }();
+    if (*rc) return nullptr;
+    return l;
+}
+
+// The launches of a stage with these classes, and the classes' items.
+int build_launches(const Batch &b, std::vector<BatchClass> &cls, hipStream_t s, BatchLaunches *out) {
+    std::vector<std::pair<TileShape, std::vector<int32_t>>> groups;
+    for (const auto &c : cls) {
+        auto g = std::find_if(groups.begin(), groups.end(), [&](const auto &k) { return same_tile(k.first, c.tile); });
+        if (g == groups.end()) g = groups.insert(g, {c.tile, {}});
+        g->second.insert(g->second.end(), c.sys.begin(), c.sys.end());
     }
-    for (auto &l : b.launches) {
-        const int rc = build_list(b, l, s);
-        if (rc) return rc;
+    for (const auto &g : groups) {
+        int rc;
+        auto l = build_launch(b, g.first, g.second, s, &rc);
+        if (!l) return rc;
+        out->push_back(std::move(l));
+    }
+    for (auto &c : cls) {
+        c.nitems = 0;
+        for (const int32_t i : c.sys) {
+            const rsg_system_desc &d = b.sys[i];
+            TileShape sh = c.tile;
+            sh.PT = 0;
+            sh.BO = 0;
+            sh.ZC = sh.ZC > 0 ? sh.ZC : d.ham->g->n[2];
+            int err = RSG_OK;
+            const TilePlan *plan = d.ham->g->plan(sh, s, &err);  // built above
+            if (!plan) return err;
+            c.nitems += (int64_t)plan->nitems * d.nst;
+        }
     }
     return RSG_OK;
 }
 
-// (Re)build the per-system parameter tables, the projector work lists and
-// every class's stencil items.
+// Gives the batch these classes: their launches are built first, so a failure
+// leaves the batch as it was.  Captured graphs hold the old lists.
+int set_batch_classes(Batch &b, std::vector<BatchClass> cls, hipStream_t s) {
+    BatchLaunches l;
+    const int rc = build_launches(b, cls, s, &l);
+    if (rc) return rc;
+    b.drop_graphs();
+    b.cls = std::move(cls);
+    b.launches = std::move(l);
+    return RSG_OK;
+}
+
+// Builds the per-system parameter tables, the projector work lists and the
+// launches of every stage.
 int build_tables(Batch &b, hipStream_t s) {
-    b.free_tables();
     std::vector<int4> gitems;
     std::vector<int4> sitems;
     std::vector<KParams> sp[4];
@@ -273,19 +297,23 @@ int build_tables(Batch &b, hipStream_t s) {
     b.ngitems = (int32_t)gitems.size();
     b.nsitems = (int32_t)sitems.size();
     RSG_CHECK_HIP(hipStreamSynchronize(s));
-    for (size_t c = 0; c < b.cls.size(); ++c)
-        if ((rc = build_class(b, c, s))) return rc;
-    return merge_classes(b, s);
+    return set_batch_classes(b, b.cls, s);
 }
 
-int class_grid(const Batch &b, const BatchClass &c) {
-    return b.grid_cap > 0 ? std::min(c.grid, (int)b.grid_cap) : c.grid;
+int launch_grid(const Batch &b, const BatchLaunch &l) {
+    return b.grid_cap > 0 ? std::min(l.grid, (int)b.grid_cap) : l.grid;
 }
 
-// The persistent stencil launch of one class for stage k with factor (cre, cim).
-int class_launch(const Batch &b, const BatchClass &c, int k, double cre, double cim, hipStream_t s) {
-    return launch_stencil_batch(c.tile, 1, true, b.nt, b.sp[k], c.items, c.seg, c.nitems, cre, cim, b.ctr,
-                                class_grid(b, c), s);
+// The persistent stencil launches of stage k with factor (cre, cim).  They share
+// the work counters: they run one after the other on this stream, and each leaves
+// the counters zero.
+int stencil_launches(const Batch &b, const BatchLaunches &launches, int k, double cre, double cim, hipStream_t s) {
+    for (const auto &l : launches) {
+        const int rc = launch_stencil_batch(l->tile, 1, true, b.nt, b.sp[k], l->items, l->seg, l->nitems, cre, cim, b.ctr,
+                                            launch_grid(b, *l), s);
+        if (rc) return rc;
+    }
+    return RSG_OK;
 }
 
 // Stage k of a step, the same product form as a single system's FP64 step:
@@ -295,10 +323,7 @@ int stage_launches(const Batch &b, int k, double dt, hipStream_t s) {
     const std::complex<double> c = std::complex<double>(0.0, dt) / taylor4_roots()[k];
     int rc;
     if ((rc = launch_kb_gather_batch(b.kb[k], b.gitems, b.ngitems, s))) return rc;
-    // the launches share the work counters: they run one after the other on
-    // this stream, and each leaves the counters zero
-    for (const auto &l : b.launches)
-        if ((rc = class_launch(b, l, k, c.real(), c.imag(), s))) return rc;
+    if ((rc = stencil_launches(b, b.launches, k, c.real(), c.imag(), s))) return rc;
     return launch_kb_scatter_batch(b.kb[k], b.sitems, b.nsitems, c.real(), c.imag(), s);
 }
 
@@ -446,18 +471,15 @@ extern "C" int rsg_batch_set_classes(rsg_batch_t b, const int32_t *class_of_sys,
         for (int32_t c = 0; c < ncl; ++c)
             RSG_REQUIRE(!cls[c].sys.empty(), RSG_EINVAL, "rsg_batch_set_classes: class %d has no system", c);
         for (auto &c : cls) c.tile = start_tile();
-        b->free_tables();
-        b->cls = cls;
-        return build_tables(*b, (hipStream_t)stream);
+        return set_batch_classes(*b, cls, (hipStream_t)stream);
     });
 }
 
-static int set_class_tile(rsg_batch_t b, int32_t c, const rsg_tile *t) {
-    BatchClass &cl = b->cls[c];
-    cl.tile = TileShape{t->B, t->TX, t->TY, t->ZC};
-    cl.tile.PD = t->PD;
-    cl.tile.ZM = t->ZM;
-    return RSG_OK;
+static TileShape batch_tile(const rsg_tile *t) {
+    TileShape sh{t->B, t->TX, t->TY, t->ZC};
+    sh.PD = t->PD;
+    sh.ZM = t->ZM;
+    return sh;
 }
 
 static int check_batch_tile(const rsg_tile *t, const char *who) {
@@ -473,12 +495,9 @@ extern "C" int rsg_batch_set_tile(rsg_batch_t b, const rsg_tile *t, void *stream
     int rc = check_batch_tile(t, "rsg_batch_set_tile");
     if (rc) return rc;
     return guarded([&]() -> int {
-        for (int32_t c = 0; c < (int32_t)b->cls.size(); ++c) {
-            set_class_tile(b, c, t);
-            const int r = build_class(*b, (size_t)c, (hipStream_t)stream);
-            if (r) return r;
-        }
-        return merge_classes(*b, (hipStream_t)stream);
+        std::vector<BatchClass> cls = b->cls;
+        for (auto &c : cls) c.tile = batch_tile(t);
+        return set_batch_classes(*b, cls, (hipStream_t)stream);
     });
 }
 
@@ -488,10 +507,10 @@ extern "C" int rsg_batch_set_class_tile(rsg_batch_t b, int32_t c, const rsg_tile
     RSG_REQUIRE(c >= 0 && c < (int32_t)b->cls.size(), RSG_EINVAL, "rsg_batch_set_class_tile: no class %d", c);
     int rc = check_batch_tile(t, "rsg_batch_set_class_tile");
     if (rc) return rc;
-    set_class_tile(b, c, t);
-    return guarded([&]() {
-        const int r = build_class(*b, (size_t)c, (hipStream_t)stream);
-        return r ? r : merge_classes(*b, (hipStream_t)stream);
+    return guarded([&]() -> int {
+        std::vector<BatchClass> cls = b->cls;
+        cls[c].tile = batch_tile(t);
+        return set_batch_classes(*b, cls, (hipStream_t)stream);
     });
 }
 
@@ -530,7 +549,11 @@ extern "C" int rsg_batch_class_info(rsg_batch_t b, int32_t c, int32_t *nsys, int
     const BatchClass &cl = b->cls[c];
     if (nsys) *nsys = (int32_t)cl.sys.size();
     if (nitems) *nitems = cl.nitems;
-    if (grid) *grid = std::min<int64_t>(cl.nitems, class_grid(*b, cl));
+    if (grid) {
+        *grid = 0;
+        for (const auto &l : b->launches)
+            if (same_tile(l->tile, cl.tile)) *grid = std::min<int32_t>(l->nitems, launch_grid(*b, *l));
+    }
     return RSG_OK;
 }
 
@@ -544,61 +567,65 @@ extern "C" int rsg_batch_set_grid(rsg_batch_t b, int32_t max_workgroups) {
 }
 
 // Per class: every compiled tile x z-chunk {whole, 32} x z-march {upward,
-// centre-out}, timed on that class's persistent launch of a middle stage
-// (w1 -> w2, the orbitals untouched), best of reps after a warm-up; the
-// fastest per class is kept.
+// centre-out}, timed on a launch of that class for a middle stage (w1 -> w2,
+// the orbitals untouched), best of reps after a warm-up; the fastest per class
+// is kept.
 extern "C" int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, double *best_ms, void *stream) {
     clear_error();
     RSG_REQUIRE(b && reps > 0, RSG_EINVAL, "rsg_batch_autotune: bad argument");
     hipStream_t s = (hipStream_t)stream;
     return guarded([&]() -> int {
-        hipEvent_t e0, e1;
-        RSG_CHECK_HIP(hipEventCreate(&e0));
-        RSG_CHECK_HIP(hipEventCreate(&e1));
-        int rc = RSG_OK;
-        double total = 0.0;
-        std::vector<TileShape> chosen;
-        for (auto &c : b->cls) chosen.push_back(c.tile);
-        for (size_t ci = 0; ci < b->cls.size() && !rc; ++ci) {
-            double bt = 1e300;
-            for (const auto &cand : tile_candidates(0)) {
-                for (int zv = 0; zv < 4; ++zv) {
-                    TileShape sh = cand;
-                    sh.ZC = (zv & 1) ? 32 : 0;
-                    sh.ZM = zv >> 1;
-                    b->cls[ci].tile = sh;
-                    if ((rc = build_class(*b, ci, s))) break;
-                    double tmin = 1e300;
-                    for (int r = 0; r <= reps; ++r) {
-                        RSG_CHECK_HIP(hipEventRecord(e0, s));
-                        if ((rc = class_launch(*b, b->cls[ci], 1, 0.0, -1e-3, s))) break;
-                        RSG_CHECK_HIP(hipEventRecord(e1, s));
-                        RSG_CHECK_HIP(hipEventSynchronize(e1));
-                        float ms = 0.f;
-                        RSG_CHECK_HIP(hipEventElapsedTime(&ms, e0, e1));
-                        if (r > 0) tmin = std::min(tmin, (double)ms);
-                    }
-                    if (rc) break;
-                    if (tmin < bt) {
-                        bt = tmin;
-                        chosen[ci] = sh;
-                    }
-                }
-                if (rc) break;
+        struct Events {
+            hipEvent_t e[2] = {nullptr, nullptr};
+            ~Events() {
+                for (auto v : e)
+                    if (v) (void)hipEventDestroy(v);
             }
-            b->cls[ci].tile = chosen[ci];
+        } ev;
+        for (auto &v : ev.e) RSG_CHECK_HIP(hipEventCreate(&v));
+        auto time_stage = [&](const BatchLaunches &l, int n, double *tmin) -> int {
+            *tmin = 1e300;
+            for (int r = 0; r <= n; ++r) {
+                RSG_CHECK_HIP(hipEventRecord(ev.e[0], s));
+                const int q = stencil_launches(*b, l, 1, 0.0, -1e-3, s);
+                if (q) return q;
+                RSG_CHECK_HIP(hipEventRecord(ev.e[1], s));
+                RSG_CHECK_HIP(hipEventSynchronize(ev.e[1]));
+                float ms = 0.f;
+                RSG_CHECK_HIP(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+                if (r > 0) *tmin = std::min(*tmin, (double)ms);
+            }
+            return RSG_OK;
+        };
+        std::vector<TileShape> cand;
+        for (const auto &t : tile_candidates(0)) {
+            TileShape sh = t;
+            for (const auto &[zc, zm] : {std::pair<int, int>{0, 0}, {32, 0}, {0, 1}, {32, 1}}) {
+                sh.ZC = zc;
+                sh.ZM = zm;
+                cand.push_back(sh);
+            }
+        }
+        std::vector<BatchClass> own = b->cls;  // every class on its fastest tile
+        double total = 0;
+        for (auto &c : own) {
+            double bt = 1e300;
+            for (const auto &sh : cand) {
+                int rc;
+                BatchLaunches l;
+                l.push_back(build_launch(*b, sh, c.sys, s, &rc));
+                if (rc) return rc;
+                double t = 0;
+                if ((rc = time_stage(l, reps, &t))) return rc;
+                if (t < bt) {
+                    bt = t;
+                    c.tile = sh;
+                }
+            }
             total += bt;
-            if (!rc) rc = build_class(*b, ci, s);
         }
-        if (!rc) rc = merge_classes(*b, s);
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        if (rc) {
-            // leave a consistent batch behind: every class on its chosen tile
-            for (size_t ci = 0; ci < b->cls.size(); ++ci) b->cls[ci].tile = chosen[ci];
-            (void)build_tables(*b, s);
-            return rc;
-        }
+        const int rc = set_batch_classes(*b, own, s);
+        if (rc) return rc;
         if (best) rsg_batch_get_tile(b, best);
         if (best_ms) *best_ms = total;
         return RSG_OK;
