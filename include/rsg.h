@@ -462,12 +462,15 @@ int rsg_batch_class_info(rsg_batch_t b, int32_t c, int32_t *nsys, int64_t *nitem
  * more items each; the results do not change.  Drops captured graphs. */
 int rsg_batch_set_grid(rsg_batch_t b, int32_t max_workgroups);
 
-/* Autotuner over the size classes: for each class, every compiled FP64 tile
- * shape x z-chunk {whole, 32} x z-march {upward, centre-out}, timed on that
- * class's persistent launch of a middle Taylor stage (best of reps after a
- * warm-up); the fastest per class is kept.  *best: the tile of the class
- * with the most work; *best_ms: the sum over classes of their best stage
- * times.  The orbitals are not modified.  Synchronises the stream. */
+/* Autotuner over the size classes: for each class, its present tile and every
+ * compiled FP64 tile shape x z-chunk {whole, 32} x z-march {upward, centre-out}
+ * and common chunks of {32, 48, 64}, timed on a persistent launch of that
+ * class for a middle Taylor stage (best of reps after a warm-up).  Then whole
+ * stages as a step runs them (3 reps): the present tiles, the fastest of each
+ * class, and each of these tiles for all classes; the present tiles stay unless
+ * another choice is faster.  *best: the tile of the class with the most work;
+ * *best_ms: the stencil time of a stage with the tiles kept.  The orbitals are not
+ * modified.  Synchronises the stream. */
 int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, double *best_ms, void *stream);
 
 /* nsteps Taylor(4) steps of every system at time step dt, zero field.

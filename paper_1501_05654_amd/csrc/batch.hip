@@ -567,9 +567,12 @@ extern "C" int rsg_batch_set_grid(rsg_batch_t b, int32_t max_workgroups) {
 }
 
 // Per class: every compiled tile x z-chunk {whole, 32} x z-march {upward,
-// centre-out}, timed on a launch of that class for a middle stage (w1 -> w2,
-// the orbitals untouched), best of reps after a warm-up; the fastest per class
-// is kept.
+// centre-out}, common chunks of 32, 48 and 64 planes, and the class's own tile,
+// timed on a launch of that class for a middle stage (w1 -> w2, the orbitals
+// untouched), best of reps after a warm-up.  A step does not run its classes
+// one by one, so the last word is between whole stages as they run: the present
+// tiles, the classes' fastest, and each of these tiles for all classes (one
+// launch, one drain).  The present tiles stay unless another choice is faster.
 extern "C" int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, double *best_ms, void *stream) {
     clear_error();
     RSG_REQUIRE(b && reps > 0, RSG_EINVAL, "rsg_batch_autotune: bad argument");
@@ -600,17 +603,18 @@ extern "C" int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, d
         std::vector<TileShape> cand;
         for (const auto &t : tile_candidates(0)) {
             TileShape sh = t;
-            for (const auto &[zc, zm] : {std::pair<int, int>{0, 0}, {32, 0}, {0, 1}, {32, 1}}) {
+            for (const auto &[zc, zm] : {std::pair<int, int>{0, 0}, {32, 0}, {0, 1}, {32, 1}, {32, 2}, {48, 2}, {64, 2}}) {
                 sh.ZC = zc;
                 sh.ZM = zm;
                 cand.push_back(sh);
             }
         }
         std::vector<BatchClass> own = b->cls;  // every class on its fastest tile
-        double total = 0;
         for (auto &c : own) {
+            std::vector<TileShape> tiles = cand;
+            tiles.insert(tiles.begin(), c.tile);
             double bt = 1e300;
-            for (const auto &sh : cand) {
+            for (const auto &sh : tiles) {
                 int rc;
                 BatchLaunches l;
                 l.push_back(build_launch(*b, sh, c.sys, s, &rc));
@@ -622,12 +626,41 @@ extern "C" int rsg_batch_autotune(rsg_batch_t b, int32_t reps, rsg_tile *best, d
                     c.tile = sh;
                 }
             }
-            total += bt;
         }
-        const int rc = set_batch_classes(*b, own, s);
-        if (rc) return rc;
+        std::vector<std::vector<BatchClass>> sets = {b->cls};
+        auto add = [&](const std::vector<BatchClass> &v) {
+            auto same = [&](const std::vector<BatchClass> &u) {
+                return std::equal(u.begin(), u.end(), v.begin(),
+                                  [](const BatchClass &p, const BatchClass &q) { return same_tile(p.tile, q.tile); });
+            };
+            if (std::none_of(sets.begin(), sets.end(), same)) sets.push_back(v);
+        };
+        add(own);
+        for (const auto *v : {&b->cls, &own})
+            for (const auto &c : *v) {
+                std::vector<BatchClass> common = b->cls;
+                for (auto &k : common) k.tile = c.tile;
+                add(common);
+            }
+        double bt = 1e300;
+        size_t pick = 0;
+        for (size_t k = 0; k < sets.size(); ++k) {
+            BatchLaunches l;
+            int rc = build_launches(*b, sets[k], s, &l);
+            double t = 0;
+            if (!rc) rc = time_stage(l, 3 * reps, &t);
+            if (rc) return rc;
+            if (t < bt) {
+                bt = t;
+                pick = k;
+            }
+        }
+        if (pick > 0) {
+            const int rc = set_batch_classes(*b, sets[pick], s);
+            if (rc) return rc;
+        }
         if (best) rsg_batch_get_tile(b, best);
-        if (best_ms) *best_ms = total;
+        if (best_ms) *best_ms = bt;
         return RSG_OK;
     });
 }
