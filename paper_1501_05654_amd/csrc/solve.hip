@@ -416,7 +416,8 @@ __global__ void __launch_bounds__(SB) k_sv_scal(PassArgs a) {
         const double2 num = make_double2(-q.eta.x * f, -q.eta.y * f);
         q.eta = cdiv(num, q.beta);
         q.cd = (q.theta * ga) * (q.theta * ga);
-        q.cr = (th * ga) * (th * ga);  // 1 - gamma^2 without cancellation
+        // 1 - gamma^2 without cancellation; theta^2 may overflow, gamma is 0 then
+        q.cr = ga > 0 ? (th * ga) * (th * ga) : 1.0;
         q.theta = th;
         q.gamma = ga;
         if (rho1 > 0) {
