@@ -164,6 +164,17 @@ TileExtents Grid::extents(int TX, int TY) const {
 //     of a patch march over the patch's common z-extent, and items are ordered
 //     patch-major, then chunk, then tile.
 const TilePlan *Grid::plan(const TileShape &s, hipStream_t stream, int *err) {
+    // reached from C entries outside any try block: host allocation fails by code
+    try {
+        return build_plan(s, stream, err);
+    } catch (const std::bad_alloc &) {
+        set_error("tile plan: host allocation failed");
+        *err = RSG_ENOMEM;
+        return nullptr;
+    }
+}
+
+const TilePlan *Grid::build_plan(const TileShape &s, hipStream_t stream, int *err) {
     TileShape key{0, s.TX, s.TY, s.ZC};
     key.PD = 0;
     key.PT = s.PT;
@@ -278,7 +289,12 @@ const TilePlan *Grid::plan(const TileShape &s, hipStream_t stream, int *err) {
         }
     }
     *err = RSG_OK;
-    return &(plans[key] = p);
+    try {
+        return &(plans[key] = p);
+    } catch (...) {
+        if (p.items) (void)hipFree(p.items);
+        throw;
+    }
 }
 
 }  // namespace rsg

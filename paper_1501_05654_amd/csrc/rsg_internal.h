@@ -123,7 +123,12 @@ struct Grid {
     mutable std::map<std::tuple<int64_t, int, bool>, TileShape> defaults;
     ~Grid();
     TileExtents extents(int TX, int TY) const;
+    // The plan of a tile shape, built and kept at its first use; null with a code in
+    // *err on failure.
     const TilePlan *plan(const TileShape &s, hipStream_t stream, int *err);
+
+  private:
+    const TilePlan *build_plan(const TileShape &s, hipStream_t stream, int *err);
 };
 
 // ----------------------------------------------------------- Hamiltonian --
