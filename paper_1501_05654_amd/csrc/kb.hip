@@ -158,7 +158,17 @@ __global__ void __launch_bounds__(SP * 8) k_kb_scatter(Tout *__restrict__ out, i
                              mask, sF);
 }
 
-constexpr int GW = 16;  // waves of a batched gather workgroup
+constexpr int GW = 16;  // waves of a gather workgroup in a launch of its own
+
+// blockIdx.x = {atom, column tile, chunk}, as in the stencil's launch.
+template <class Tin, class Tc>
+__global__ void __launch_bounds__(GW * 64) k_kb_gather(const Tin *__restrict__ in, GatherArgs g) {
+    __shared__ Tc red[kGatherSlots * 64];
+    const int j = blockIdx.x, chunk = j % g.nchunk, q = j / g.nchunk, atom = q / g.nct;
+    gather_tile<GW, Tin, Tc>(in, g.ldo, g.ncols, g.atoms[atom], atom, q - atom * g.nct, g.idx,
+                             static_cast<const Tc *>(g.p), (Tc)g.h3, static_cast<Tc *>(g.D), red, chunk, g.nchunk,
+                             static_cast<Tc *>(g.P));
+}
 
 // Batched forms over many systems (FP64): item {system, atom, column tile}
 // for the gather, {system, scatter item, orbital tile} for the scatter.
@@ -240,6 +250,18 @@ GatherArgs gather_args(const Ham &H, int compute, int64_t nst, int64_t ldp, void
     g.nblk = H.natoms * g.nct * g.nchunk;
     g.h3 = H.g->h * H.g->h * H.g->h;
     return g;
+}
+
+int launch_kb_gather(const GatherArgs &g, const void *in, int in_t, int compute, hipStream_t s) {
+    if (g.nblk == 0) return RSG_OK;
+    if (compute == 0)
+        k_kb_gather<double, double><<<(unsigned)g.nblk, GW * 64, 0, s>>>((const double *)in, g);
+    else if (in_t == 0)
+        k_kb_gather<double, float><<<(unsigned)g.nblk, GW * 64, 0, s>>>((const double *)in, g);
+    else
+        k_kb_gather<float, float><<<(unsigned)g.nblk, GW * 64, 0, s>>>((const float *)in, g);
+    RSG_CHECK_HIP(hipGetLastError());
+    return RSG_OK;
 }
 
 int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t nst, int64_t ldp,

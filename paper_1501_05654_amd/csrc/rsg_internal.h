@@ -311,6 +311,8 @@ struct GatherArgs {
     double h3 = 0;
 };
 GatherArgs gather_args(const Ham &H, int compute, int64_t nst, int64_t ldp, void *D);
+// The gather as a launch of its own (same bits), for tiles of few threads.
+int launch_kb_gather(const GatherArgs &g, const void *in, int in_t, int compute, hipStream_t s);
 int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t nst, int64_t ldp,
                       const void *D, double cre, double cim, const double *mask, hipStream_t s);
 size_t kb_workspace_bytes(const Ham &H, int64_t nst);

@@ -220,6 +220,15 @@ int64_t stencil_blocks(const Ham &H, int64_t nst, int compute, hipStream_t s) {
     return (int64_t)plan->nitems * nst;
 }
 
+// Whether the projector gather rides in the launch of a tile: a workgroup of few
+// waves takes long for its part (19 us on two, 32 on one, for two atoms of 1,200
+// points), which hides only behind marches that last as long.  23^3 x 2 orbitals, a
+// stage in 8 x 8 tiles with chunks of 2 planes: 32.4 us riding, 14.6 with a gather
+// launch of 16 waves before it, with chunks of 8 17.2; 16 x 8 with 2 planes 19.7 and
+// 14.4.  With marches of 49 planes and more riding leads in 8 x 8 (34.3 and 40.6
+// us), of 23 and more in 16 x 8 (19.4 and 24.8).
+bool gather_rides(const TileShape &s) { return s.TX * s.TY >= 256 || s.TX * s.TY * s.ZC >= 2048; }
+
 int launch_stencil(const Ham &H, const StageArgs &a, const TileShape &tile, hipStream_t s) {
     const Grid &g = *H.g;
     int err = RSG_OK;
@@ -253,6 +262,11 @@ int launch_stencil(const Ham &H, const StageArgs &a, const TileShape &tile, hipS
     if ((int64_t)nb + ga.nblk > INT32_MAX) {
         set_error("stencil launch too large");
         return RSG_EUNSUPPORTED;
+    }
+    if (!gather_rides(shape) && a.in_t <= a.compute) {
+        const int rc = launch_kb_gather(ga, a.in, a.in_t, a.compute, s);
+        if (rc) return rc;
+        ga = GatherArgs{};
     }
     timing_before(s);
     const int rc =
