@@ -179,7 +179,7 @@ std::unique_ptr<BatchLaunch> build_launch(const Batch &b, const TileShape &tile,
             seg[q] = (int32_t)(std::lower_bound(cum.begin(), cum.end(), cum.back() * q / kBatchQueues) - cum.begin());
         seg[kBatchQueues] = (int32_t)items.size();
         for (int q = 1; q <= kBatchQueues; ++q) seg[q] = std::max(seg[q], seg[q - 1]);
-        l->grid = stencil_batch_grid(tile, true, b.nt);
+        l->grid = stencil_batch_grid(tile, b.nt);
         if (l->grid <= 0) return l->grid;
         int r = upload(&l->items, items, s);
         if (r) return r;
@@ -251,7 +251,6 @@ int build_tables(Batch &b, hipStream_t s) {
             a.mode = 1;
             a.nst = d.nst;
             a.ldp = d.ldp;
-            a.first = k == 0;
             // the persistent kernel takes its tiles from the class's list,
             // not from a plan
             sp[k].push_back(make_params(H, a, TileShape{1, 32, 8, 0}, nullptr));
@@ -309,7 +308,7 @@ int launch_grid(const Batch &b, const BatchLaunch &l) {
 // the counters zero.
 int stencil_launches(const Batch &b, const BatchLaunches &launches, int k, double cre, double cim, hipStream_t s) {
     for (const auto &l : launches) {
-        const int rc = launch_stencil_batch(l->tile, 1, true, b.nt, b.sp[k], l->items, l->seg, l->nitems, cre, cim, b.ctr,
+        const int rc = launch_stencil_batch(l->tile, b.nt, b.sp[k], l->items, l->seg, l->nitems, cre, cim, b.ctr,
                                             launch_grid(b, *l), s);
         if (rc) return rc;
     }

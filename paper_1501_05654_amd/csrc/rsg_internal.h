@@ -280,11 +280,11 @@ constexpr int kBatchQueues = 8;
 // ctr: kBatchQueues + 1 device int32 work counters, zero before the first
 // launch (each launch leaves them zero again); launches sharing them must
 // not overlap.  nt: the kernel set with non-temporal output stores.
-int launch_stencil_batch(const TileShape &shape, int mode, bool first, bool nt, const KParams *sysp,
-                         const BatchItem *items, const int32_t *seg, int32_t nitems, double cre, double cim,
-                         int32_t *ctr, int grid, hipStream_t s);
+int launch_stencil_batch(const TileShape &shape, bool nt, const KParams *sysp, const BatchItem *items,
+                         const int32_t *seg, int32_t nitems, double cre, double cim, int32_t *ctr, int grid,
+                         hipStream_t s);
 // Resident workgroups of the batched kernel for this shape (or an error code).
-int stencil_batch_grid(const TileShape &shape, bool first, bool nt);
+int stencil_batch_grid(const TileShape &shape, bool nt);
 // Tile of a launch that nobody tuned; projectors: its gather rides in the launch.
 TileShape default_shape(const Grid &g, int64_t nst, int compute, bool projectors);
 std::vector<TileShape> tile_candidates(int compute);

@@ -281,26 +281,22 @@ int launch_stencil(const Ham &H, const StageArgs &a, const TileShape &tile, hipS
     return RSG_OK;
 }
 
-int stencil_batch_grid(const TileShape &shape, bool first, bool nt) {
-    return nt ? batch_dispatch<true>(shape, first, nullptr, nullptr, nullptr, 0, 0.0, 0.0, nullptr, -1, nullptr)
-              : batch_dispatch<false>(shape, first, nullptr, nullptr, nullptr, 0, 0.0, 0.0, nullptr, -1, nullptr);
+int stencil_batch_grid(const TileShape &shape, bool nt) {
+    return nt ? batch_dispatch<true>(shape, nullptr, nullptr, nullptr, 0, 0.0, 0.0, nullptr, -1, nullptr)
+              : batch_dispatch<false>(shape, nullptr, nullptr, nullptr, 0, 0.0, 0.0, nullptr, -1, nullptr);
 }
 
-int launch_stencil_batch(const TileShape &shape, int mode, bool first, bool nt, const KParams *sysp,
-                         const BatchItem *items, const int32_t *seg, int32_t nitems, double cre, double cim,
-                         int32_t *ctr, int grid, hipStream_t s) {
+int launch_stencil_batch(const TileShape &shape, bool nt, const KParams *sysp, const BatchItem *items,
+                         const int32_t *seg, int32_t nitems, double cre, double cim, int32_t *ctr, int grid,
+                         hipStream_t s) {
     if (nitems == 0) return RSG_OK;
-    if (mode != 1) {
-        set_error("batched stencil: only Horner stages are batched");
-        return RSG_EUNSUPPORTED;
-    }
     if (grid <= 0 || !ctr || !seg) {
         set_error("batched stencil: need a persistent grid size > 0, work counters and segment bounds");
         return RSG_EINVAL;
     }
     timing_before(s);
-    const int rc = nt ? batch_dispatch<true>(shape, first, sysp, items, seg, nitems, cre, cim, ctr, grid, s)
-                      : batch_dispatch<false>(shape, first, sysp, items, seg, nitems, cre, cim, ctr, grid, s);
+    const int rc = nt ? batch_dispatch<true>(shape, sysp, items, seg, nitems, cre, cim, ctr, grid, s)
+                      : batch_dispatch<false>(shape, sysp, items, seg, nitems, cre, cim, ctr, grid, s);
     timing_after(s);
     if (rc != RSG_OK) {
         if (rc == RSG_EUNSUPPORTED)

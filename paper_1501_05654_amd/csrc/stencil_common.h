@@ -71,19 +71,13 @@ __device__ __forceinline__ int idx_in_row(int2 r, int x) {
 // dead slot of a row-aligned grid (inside the row's x-range widened to
 // multiples of align, outside the box) gives -(index) - 2, which every load
 // treats as out of range and the store fills with zero; anything else -1.
-// SEL: selects only, which keeps the step free of branches.
-template <bool SEL>
+// Selects only, which keeps the step free of branches.
 __device__ __forceinline__ int slot_in_row(int2 r, int x, int align) {
     const int x0 = r.y & 0xffff, x1 = (r.y >> 16) & 0xffff;
     const int a0 = x0 & -align, a1 = (x1 + align - 1) & -align;
-    if constexpr (SEL) {
-        const int v = r.x + x;
-        const bool in = x >= x0 && x < x1, dead = x0 < x1 && x >= a0 && x < a1;
-        return in ? v : (dead ? -v - 2 : -1);
-    } else {
-        if (x >= x0 && x < x1) return r.x + x;
-        return (x0 < x1 && x >= a0 && x < a1) ? -(r.x + x) - 2 : -1;
-    }
+    const int v = r.x + x;
+    const bool in = x >= x0 && x < x1, dead = x0 < x1 && x >= a0 && x < a1;
+    return in ? v : (dead ? -v - 2 : -1);
 }
 
 // The same as a code that addresses every operand without a further test.

@@ -418,10 +418,6 @@ template <bool NTS, int TX, int TY, class Tin, class Tc, class Tout, int MODE, b
 __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, const int n,
                                            typename CT<Tc>::c2 *tile, double2 &pacc) {
     using C2 = typename CT<Tc>::c2;
-    // selects instead of branches in the row lookups: the row index always,
-    // the slot in the row in the FP64 kernels (in the FP32 ones that select
-    // costs registers at the 4-wave occupancy limit)
-    constexpr bool SEL = std::is_same<Tc, double>::value;
     constexpr int NT = TX * TY, LX = TX + 8;
     constexpr int HPT = (8 * TX + 8 * TY + NT - 1) / NT;
     constexpr int PLANE = (TY + 8) * LX;  // one plane buffer; tile holds two
@@ -464,7 +460,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
     C2 q[9];
 #pragma unroll
     for (int j = 0; j < 8; ++j) q[j] = fetch(idx_in_row(rq[j], x), true);
-    int idx_c = slot_in_row<SEL>(rq[4], x, a.align);
+    int idx_c = slot_in_row(rq[4], x, a.align);
     C2 nxt = fetch(idx_in_row(rq[8], x), true);
     C2 hv[HPT];
 #pragma unroll
@@ -495,7 +491,7 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
         nxt = fetch(live ? idx_in_row(rf, x) : -1, true);
 #pragma unroll
         for (int j = 0; j < HPT; ++j) hv[j] = fetch(idx_in_row(rh[j], hl.x[j]), hl.ok[j] && live);
-        const int idx_n = live ? slot_in_row<SEL>(ro, x, a.align) : -1;
+        const int idx_n = live ? slot_in_row(ro, x, a.align) : -1;
         const Tc v_n = fetch_v(idx_n);
         const Tc vi_n = fetch_vi(idx_n);
         const double2 b_n = fetch_b(idx_n);
@@ -653,14 +649,14 @@ __global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST
 // workgroups done; the last workgroup out sets them all back to zero for
 // the next launch (every workgroup has found every segment used up before
 // it counts itself done, so no item is taken after the reset).
-template <bool NTS, int TX, int TY, int D, bool FIRST>
-__global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, !FIRST)),
-                                         TX == 16 && TY == 16 && D == 1 && FIRST ? 3 : 2) k_stencil_batch(const KParams *__restrict__ sysp,
-                                                           const BatchItem *__restrict__ items,
-                                                           const int32_t *__restrict__ seg, double cre,
-                                                           double cim, int32_t *ctr) {
+// Every stage of a product-form step is its own base (a first-type stage).
+template <bool NTS, int TX, int TY, int D>
+__global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, false)),
+                                  TX == 16 && TY == 16 && D == 1 ? 3 : 2)
+    k_stencil_batch(const KParams *__restrict__ sysp, const BatchItem *__restrict__ items,
+                    const int32_t *__restrict__ seg, double cre, double cim, int32_t *ctr) {
     __shared__ double2 tile[2 * (TY + 8) * (TX + 8)];  // two plane buffers
-    __shared__ int4 rowl[march_rows<TX, TY, D, tile_cy(TX, TY, D, true, !FIRST), !FIRST>()];
+    __shared__ int4 rowl[march_rows<TX, TY, D, tile_cy(TX, TY, D, true, false), false>()];
     __shared__ int32_t next;
     const int home = blockIdx.x % kBatchQueues;
     for (int j = 0; j < kBatchQueues; ++j) {
@@ -678,7 +674,7 @@ __global__ void __launch_bounds__((TX * TY / tile_cy(TX, TY, D, true, !FIRST)),
             a.cim = cim;
             a.row_slots = 0;  // rows from the table: the choice would cost registers here
             double2 unused = make_double2(0.0, 0.0);
-            march<NTS, TX, TY, D, double2, double, double2, 1, FIRST, false, false>(
+            march<NTS, TX, TY, D, double2, double, double2, 1, true, false, false>(
                 a, bi.tile, __builtin_amdgcn_readfirstlane(bi.ob), tile, rowl, unused);
             __syncthreads();  // the next item reuses the plane buffer
         }
@@ -761,11 +757,11 @@ int launch_fp32(const StageArgs &a, const KParams &p, const GatherArgs &g, int n
 // grid < 0: return the number of resident workgroups of this kernel on the
 // device (occupancy query, not allowed during graph capture); grid > 0:
 // launch with that many persistent workgroups.
-template <bool NTS, int TX, int TY, int D, bool FIRST>
+template <bool NTS, int TX, int TY, int D>
 int launch_batch_inst(const KParams *sysp, const BatchItem *items, const int32_t *seg, int32_t nitems, double cre,
                       double cim, int32_t *ctr, int grid, hipStream_t s) {
-    constexpr int NT = TX * TY / tile_cy(TX, TY, D, true, !FIRST);
-    auto kern = k_stencil_batch<NTS, TX, TY, D, FIRST>;
+    constexpr int NT = TX * TY / tile_cy(TX, TY, D, true, false);
+    auto kern = k_stencil_batch<NTS, TX, TY, D>;
     if (grid < 0) {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
@@ -776,13 +772,6 @@ int launch_batch_inst(const KParams *sysp, const BatchItem *items, const int32_t
     }
     kern<<<(int)std::min<int64_t>(nitems, grid), NT, 0, s>>>(sysp, items, seg, cre, cim, ctr);
     return RSG_OK;
-}
-
-template <bool NTS, int TX, int TY, int D>
-int launch_batch_shape(bool first, const KParams *sysp, const BatchItem *items, const int32_t *seg, int32_t nitems,
-                       double cre, double cim, int32_t *ctr, int grid, hipStream_t s) {
-    if (first) return launch_batch_inst<NTS, TX, TY, D, true>(sysp, items, seg, nitems, cre, cim, ctr, grid, s);
-    return launch_batch_inst<NTS, TX, TY, D, false>(sysp, items, seg, nitems, cre, cim, ctr, grid, s);
 }
 
 }  // namespace sk
@@ -832,14 +821,14 @@ int stencil_dispatch(const StageArgs &a, const KParams &p, const GatherArgs &g, 
 // resident workgroups on the device, grid > 0 launches it with that many
 // (RSG_EUNSUPPORTED if the shape is not compiled).
 template <bool NTS>
-int batch_dispatch(const TileShape &shape, bool first, const KParams *sysp, const BatchItem *items,
-                   const int32_t *seg, int32_t nitems, double cre, double cim, int32_t *ctr, int grid, hipStream_t s) {
+int batch_dispatch(const TileShape &shape, const KParams *sysp, const BatchItem *items, const int32_t *seg,
+                   int32_t nitems, double cre, double cim, int32_t *ctr, int grid, hipStream_t s) {
     int rc = RSG_EUNSUPPORTED;
     bool found = false;
 #define RSG_TRY_B(X_, Y_, D_)                                                                             \
     if (!found && shape.TX == X_ && shape.TY == Y_ && shape.PD == D_) {                                   \
         found = true;                                                                                     \
-        rc = sk::launch_batch_shape<NTS, X_, Y_, D_>(first, sysp, items, seg, nitems, cre, cim, ctr, grid, s); \
+        rc = sk::launch_batch_inst<NTS, X_, Y_, D_>(sysp, items, seg, nitems, cre, cim, ctr, grid, s);    \
     }
     if (shape.B == 1) { RSG_FP64_SHAPES(RSG_TRY_B) }
 #undef RSG_TRY_B
@@ -850,7 +839,7 @@ int batch_dispatch(const TileShape &shape, bool first, const KParams *sysp, cons
 #define RSG_STENCIL_INST(EXT, NTS_)                                                                           \
     EXT template int stencil_dispatch<NTS_>(const StageArgs &, const KParams &, const GatherArgs &,            \
                                             const TileShape &, bool, int, hipStream_t);                       \
-    EXT template int batch_dispatch<NTS_>(const TileShape &, bool, const KParams *, const BatchItem *,         \
+    EXT template int batch_dispatch<NTS_>(const TileShape &, const KParams *, const BatchItem *,               \
                                           const int32_t *, int32_t, double, double, int32_t *, int, hipStream_t);
 RSG_STENCIL_INST(extern, false)
 RSG_STENCIL_INST(extern, true)
