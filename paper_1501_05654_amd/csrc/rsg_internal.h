@@ -118,11 +118,13 @@ struct Grid {
     std::vector<int2> rows_host;
     int32_t *ijk = nullptr;     // device [np][3]
     std::map<TileShape, TilePlan> plans;
-    // default_shape's results by {orbitals, compute, projectors}
-    mutable std::mutex defaults_mu;
+    // Kept under lazy_mu: the extents of TX x TY tiles, and default_shape's results
+    // by {orbitals, compute, projectors}.
+    mutable std::mutex lazy_mu;
+    mutable std::map<std::pair<int, int>, TileExtents> tile_extents;
     mutable std::map<std::tuple<int64_t, int, bool>, TileShape> defaults;
     ~Grid();
-    TileExtents extents(int TX, int TY) const;
+    const TileExtents &extents(int TX, int TY) const;
     // The plan of a tile shape, built and kept at its first use; null with a code in
     // *err on failure.
     const TilePlan *plan(const TileShape &s, hipStream_t stream, int *err);

@@ -106,11 +106,13 @@ TileShape shape_by_rule(const Grid &g, int64_t nst, int compute, bool projectors
     sh.PD = r->PD;
     sh.BO = r->BO;
     if (r->counted) {
-        const TileExtents e = g.extents(r->TX, r->TY);
+        const TileExtents &e = g.extents(r->TX, r->TY);
+        // (a tile has at most one item a chunk: so many chunks fit uncounted)
+        const int sure = (int)std::min<double>(nz, r->items / (orbitals * (double)e.zlo.size()));
         for (int chunks = 1; chunks <= nz; ++chunks) {
             const int zc = (nz + chunks - 1) / chunks;
             int64_t items = 0;
-            for (size_t k = 0; k < e.zlo.size(); ++k)
+            for (size_t k = 0; chunks > sure && k < e.zlo.size(); ++k)
                 if (e.zhi[k] >= e.zlo[k]) items += e.zhi[k] / zc - e.zlo[k] / zc + 1;
             if (zc < r->zmin || (double)items * orbitals > r->items) break;
             sh.ZC = zc;
@@ -130,12 +132,12 @@ TileShape default_shape(const Grid &g, int64_t nst, int compute, bool projectors
     const auto key = std::make_tuple(nst, compute, projectors);
     try {
         {
-            std::lock_guard<std::mutex> lk(g.defaults_mu);
+            std::lock_guard<std::mutex> lk(g.lazy_mu);
             const auto it = g.defaults.find(key);
             if (it != g.defaults.end()) return it->second;
         }
         const TileShape sh = shape_by_rule(g, nst, compute, projectors);
-        std::lock_guard<std::mutex> lk(g.defaults_mu);
+        std::lock_guard<std::mutex> lk(g.lazy_mu);
         return g.defaults[key] = sh;
     } catch (const std::bad_alloc &) {
         return TileShape{1, 32, 8, g.n[2]};
