@@ -119,6 +119,15 @@ __global__ void k_to_float(const double *src, float *dst, int64_t n) {
         dst[i] = (float)src[i];
 }
 
+// The scatter's projector values: entry[k] of the supports' at place k, and in FP32.
+__global__ void k_scatter_values(const int32_t *entry, const double *src, double *dst, float *dst32, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 4 * n; i += (int64_t)gridDim.x * blockDim.x) {
+        const double v = src[4 * (int64_t)entry[i >> 2] + (i & 3)];
+        dst[i] = v;
+        dst32[i] = (float)v;
+    }
+}
+
 // Plain copy, four 16-byte loads in flight per thread per iteration.
 __global__ void __launch_bounds__(256) k_copy16(const int4 *src, int4 *dst, int64_t n16) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -491,87 +500,76 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
             }
             const int64_t total = H->kb_off[natoms];
             std::vector<int32_t> idx_h(total, 0);
-            std::vector<double> p_h((size_t)total * 4, 0.0);
             std::vector<double> E_h((size_t)natoms * 4);
+            // the projector values stay on the device
+            if ((e = hipMalloc(&H->kb_p, sizeof(double) * 4 * total)) != hipSuccess) return fail("p", e);
+            if ((e = hipMemset(H->kb_p, 0, sizeof(double) * 4 * total)) != hipSuccess) return fail("p clear", e);
             for (int a = 0; a < natoms; ++a) {
                 const int64_t n = proj[a].n_support;
                 if (n > 0) {
                     if ((e = hipMemcpy(idx_h.data() + H->kb_off[a], proj[a].idx, sizeof(int32_t) * n,
                                        hipMemcpyDeviceToHost)) != hipSuccess)
                         return fail("projector index copy", e);
-                    if ((e = hipMemcpy(p_h.data() + 4 * H->kb_off[a], proj[a].p, sizeof(double) * 4 * n,
-                                       hipMemcpyDeviceToHost)) != hipSuccess)
+                    if ((e = hipMemcpy(H->kb_p + 4 * H->kb_off[a], proj[a].p, sizeof(double) * 4 * n,
+                                       hipMemcpyDefault)) != hipSuccess)
                         return fail("projector value copy", e);
                 }
                 for (int64_t k = n; k < H->kb_off[a + 1] - H->kb_off[a]; ++k)
                     idx_h[H->kb_off[a] + k] = n > 0 ? idx_h[H->kb_off[a]] : 0;
                 for (int i = 0; i < 4; ++i) E_h[4 * a + i] = proj[a].E[i];
             }
-            // validate indices: in range and distinct within an atom
+            // one pass over the entries: indices in range and distinct within an
+            // atom; greedy colours: atoms whose supports overlap get different
+            // ones (a point adds its atoms in colour order).  mark[r] heads the
+            // list of the entries at point r so far, latest atom first.
             std::vector<int32_t> mark(np > 0 ? np : 1, -1);
-            for (int a = 0; a < natoms; ++a)
+            std::vector<int> colour(natoms, -1);
+            std::vector<int32_t> before(total), atom_of(total);
+            std::vector<char> taken(natoms + 1);
+            for (int a = 0; a < natoms; ++a) {
+                std::fill(taken.begin(), taken.begin() + a + 1, 0);
                 for (int64_t k = 0; k < H->kb_len[a]; ++k) {
-                    const int32_t r = idx_h[H->kb_off[a] + k];
+                    const int32_t q = (int32_t)(H->kb_off[a] + k), r = idx_h[q];
                     if (r < 0 || r >= np) {
                         set_error("rsg_ham_create: atom %d projector index %d outside [0, %lld)", a, r,
                                   (long long)np);
                         delete H;
                         return RSG_EINVAL;
                     }
-                    if (mark[r] == a) {
+                    if (mark[r] >= 0 && atom_of[mark[r]] == a) {
                         set_error("rsg_ham_create: atom %d lists point %d twice", a, r);
                         delete H;
                         return RSG_EINVAL;
                     }
-                    mark[r] = a;
+                    for (int32_t o = mark[r]; o >= 0; o = before[o]) taken[colour[atom_of[o]]] = 1;
+                    atom_of[q] = a;
+                    before[q] = mark[r];
+                    mark[r] = q;
                 }
-            // greedy colouring: atoms whose supports overlap get different
-            // colours; a point adds its atoms in colour order.  mark[r]
-            // heads the list of the entries at point r so far.
-            auto unmark = [&] {
-                for (int a = 0; a < natoms; ++a)
-                    for (int64_t k = 0; k < H->kb_len[a]; ++k) mark[idx_h[H->kb_off[a] + k]] = -1;
-            };
-            unmark();
-            std::vector<int> colour(natoms, -1);
-            std::vector<int32_t> before(total, -1), atom_of(total, 0);
-            for (int a = 0; a < natoms; ++a) {
-                std::vector<char> taken(a + 1, 0);
-                for (int64_t k = 0; k < H->kb_len[a]; ++k)
-                    for (int32_t e = mark[idx_h[H->kb_off[a] + k]]; e >= 0; e = before[e]) taken[colour[atom_of[e]]] = 1;
                 int c = 0;
                 while (taken[c]) ++c;
                 colour[a] = c;
-                for (int64_t k = 0; k < H->kb_len[a]; ++k) {
-                    const int32_t e = (int32_t)(H->kb_off[a] + k);
-                    atom_of[e] = a;
-                    before[e] = mark[idx_h[e]];
-                    mark[idx_h[e]] = e;
-                }
             }
-            unmark();
             std::vector<int4> atoms(natoms);
             for (int a = 0; a < natoms; ++a) {
                 const int64_t padded = H->kb_off[a + 1] - H->kb_off[a];
                 atoms[a] = make_int4((int)H->kb_off[a], (int)padded, (int)H->kb_len[a], a);
             }
             if ((e = hipMalloc(&H->kb_idx, sizeof(int32_t) * total)) != hipSuccess) return fail("idx", e);
-            if ((e = hipMalloc(&H->kb_p, sizeof(double) * 4 * total)) != hipSuccess) return fail("p", e);
             if ((e = hipMalloc(&H->kb_p32, sizeof(float) * 4 * total)) != hipSuccess) return fail("p32", e);
             if ((e = hipMalloc(&H->kb_E, sizeof(double) * 4 * natoms)) != hipSuccess) return fail("E", e);
             if ((e = hipMalloc(&H->gather_items, sizeof(int4) * natoms)) != hipSuccess) return fail("atoms", e);
             if ((e = hipMemcpy(H->kb_idx, idx_h.data(), sizeof(int32_t) * total, hipMemcpyHostToDevice)) != hipSuccess)
                 return fail("idx upload", e);
-            if ((e = hipMemcpy(H->kb_p, p_h.data(), sizeof(double) * 4 * total, hipMemcpyHostToDevice)) != hipSuccess)
-                return fail("p upload", e);
             if ((e = hipMemcpy(H->kb_E, E_h.data(), sizeof(double) * 4 * natoms, hipMemcpyHostToDevice)) != hipSuccess)
                 return fail("E upload", e);
             if ((e = hipMemcpy(H->gather_items, atoms.data(), sizeof(int4) * natoms, hipMemcpyHostToDevice)) != hipSuccess)
                 return fail("atom upload", e);
             k_to_float<<<nblocks_for(4 * total), 256>>>(H->kb_p, H->kb_p32, 4 * total);
             ScatterHost sc;
-            build_scatter(idx_h, H->kb_off, H->kb_len, colour, mark, &sc);
-            // one allocation and one copy for all of its tables
+            build_scatter(idx_h, H->kb_off, H->kb_len, colour, atom_of, mark, &sc);
+            // one allocation and one copy for all of its tables; its projector
+            // values are gathered on the device
             const size_t nc = sc.entry.size();
             size_t used_bytes = 0;
             auto place_at = [&](size_t bytes) {
@@ -581,8 +579,9 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
             };
             const size_t o_items = place_at(sizeof(int4) * sc.items.size()), o_pt = place_at(4 * sc.pt.size()),
                          o_more = place_at(4 * sc.more.size()), o_place = place_at(4 * nc),
-                         o_atoms = place_at(4 * sc.atoms.size()), o_p = place_at(32 * nc), o_p32 = place_at(16 * nc);
+                         o_atoms = place_at(4 * sc.atoms.size()), o_entry = place_at(4 * nc);
             std::vector<char> img(used_bytes, 0);
+            const size_t o_p = place_at(32 * nc), o_p32 = place_at(16 * nc);
             auto put = [&](size_t at, const auto &v) {
                 if (!v.empty()) std::memcpy(img.data() + at, v.data(), sizeof(v[0]) * v.size());
             };
@@ -591,17 +590,9 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
             put(o_more, sc.more);
             put(o_place, sc.place);
             put(o_atoms, sc.atoms);
-            for (size_t k = 0; k < nc; ++k) {
-                const double *p = &p_h[4 * (size_t)sc.entry[k]];
-                double *d = reinterpret_cast<double *>(img.data() + o_p) + 4 * k;
-                float *f = reinterpret_cast<float *>(img.data() + o_p32) + 4 * k;
-                for (int i = 0; i < 4; ++i) {
-                    d[i] = p[i];
-                    f[i] = (float)p[i];
-                }
-            }
+            put(o_entry, sc.entry);
             if ((e = hipMalloc(&H->scatter_mem, used_bytes)) != hipSuccess) return fail("scatter", e);
-            if ((e = hipMemcpy(H->scatter_mem, img.data(), used_bytes, hipMemcpyHostToDevice)) != hipSuccess)
+            if ((e = hipMemcpy(H->scatter_mem, img.data(), img.size(), hipMemcpyHostToDevice)) != hipSuccess)
                 return fail("scatter upload", e);
             H->scatter.items = (int4 *)(H->scatter_mem + o_items);
             H->scatter.pt = (int32_t *)(H->scatter_mem + o_pt);
@@ -611,6 +602,10 @@ extern "C" int rsg_ham_create(rsg_grid_t g, const double *vloc_dev, double kin, 
             H->scatter_p = (double *)(H->scatter_mem + o_p);
             H->scatter_p32 = (float *)(H->scatter_mem + o_p32);
             H->scatter_n = (int32_t)sc.items.size();
+            if (nc > 0)
+                k_scatter_values<<<nblocks_for(4 * (int64_t)nc), 256>>>((int32_t *)(H->scatter_mem + o_entry), H->kb_p,
+                                                                        (double *)(H->scatter_mem + o_p),
+                                                                        (float *)(H->scatter_mem + o_p32), (int64_t)nc);
         }
         if ((e = hipGetLastError()) != hipSuccess) return fail("conversion", e);
         if ((e = hipDeviceSynchronize()) != hipSuccess) return fail("sync", e);

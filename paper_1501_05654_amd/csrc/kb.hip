@@ -293,48 +293,56 @@ int launch_kb_scatter(const Ham &H, void *out, int out_t, int compute, int64_t n
 // The scatter's tables (ScatterTab) from the padded supports and the atoms'
 // colours: the points of the union of all supports grouped by the first atom
 // in colour order that covers them, each with its atoms in colour order.
-// place: scratch of one entry per slot, all -1.
+// atom_of: the atom of every entry.  mark: one value per slot, not negative at
+// every covered one; holds ~(place of the slot's point) there on return.
 void build_scatter(const std::vector<int32_t> &idx, const std::vector<int64_t> &off, const std::vector<int64_t> &len,
-                   const std::vector<int> &colour, std::vector<int32_t> &place, ScatterHost *t) {
+                   const std::vector<int> &colour, const std::vector<int32_t> &atom_of, std::vector<int32_t> &mark,
+                   ScatterHost *t) {
     const int natoms = (int)len.size();
     std::vector<int> ord(natoms);
     for (int a = 0; a < natoms; ++a) ord[a] = a;
     std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return colour[a] < colour[b]; });
-    std::vector<int32_t> owner, extra;
-    for (auto *v : {&t->pt, &t->entry, &owner, &extra}) v->reserve(idx.size());
+    int64_t nc = 0;
+    for (const int64_t l : len) nc += l;
+    t->pt.resize(nc);
+    t->entry.resize(nc);
+    t->more.assign(nc + 1, 0);
+    size_t n = 0;  // points so far; more[u + 1] counts point u's atoms beyond its owner
     for (const int a : ord)
         for (int64_t k = 0; k < len[a]; ++k) {
-            const int32_t r = idx[off[a] + k];
-            if (place[r] < 0) {
-                place[r] = (int32_t)t->pt.size();
-                t->pt.push_back(r);
-                owner.push_back(a);
-                extra.push_back(0);
-                t->entry.push_back((int32_t)(off[a] + k));
+            const int32_t e = (int32_t)(off[a] + k);
+            int32_t &m = mark[idx[e]];
+            if (m >= 0) {
+                m = ~(int32_t)n;
+                t->pt[n] = idx[e];
+                t->entry[n++] = e;
             } else {
-                ++extra[place[r]];
+                ++t->more[~m + 1];
             }
         }
-    const size_t n = t->pt.size();
-    t->more.assign(n + 1, (int32_t)n);
-    for (size_t u = 0; u < n; ++u) t->more[u + 1] = t->more[u] + extra[u];
-    t->entry.resize(t->more[n]);
-    t->place.assign(t->more[n], 0);
-    std::vector<int32_t> fill(t->more.begin(), t->more.end() - 1);
-    for (const int a : ord)
-        for (int64_t k = 0; k < len[a]; ++k) {
-            const int32_t u = place[idx[off[a] + k]];
-            if (owner[u] == a) continue;
-            t->entry[fill[u]] = (int32_t)(off[a] + k);
-            t->place[fill[u]++] = a;  // the atom for now
-        }
-    std::vector<int> rank(natoms), seen(natoms, -1);
+    t->pt.resize(n);
+    t->more.resize(n + 1);
+    t->more[0] = (int32_t)n;
+    for (size_t u = 0; u < n; ++u) t->more[u + 1] += t->more[u];
+    t->place.assign(nc, 0);
+    if ((size_t)nc > n) {
+        std::vector<int32_t> fill(t->more.begin(), t->more.end() - 1);
+        for (const int a : ord)
+            for (int64_t k = 0; k < len[a]; ++k) {
+                const int32_t e = (int32_t)(off[a] + k), u = ~mark[idx[e]];
+                if (t->entry[u] == e) continue;
+                t->entry[fill[u]] = e;
+                t->place[fill[u]++] = a;  // the atom for now
+            }
+    }
+    std::vector<int> rank(natoms), seen(natoms, -1), list;
     for (int j = 0; j < natoms; ++j) rank[ord[j]] = j;
     for (size_t u = 0; u < n;) {
+        const int owner = atom_of[t->entry[u]];
         size_t v = u + 1;
-        while (v < n && v - u < (size_t)kScatterPoints && owner[v] == owner[u]) ++v;
-        std::vector<int> list(1, owner[u]);  // the item's atoms in colour order, the owner first
-        seen[owner[u]] = (int)t->items.size();
+        while (v < n && v - u < (size_t)kScatterPoints && atom_of[t->entry[v]] == owner) ++v;
+        list.assign(1, owner);  // the item's atoms in colour order, the owner first
+        seen[owner] = (int)t->items.size();
         for (int32_t c = t->more[u]; c < t->more[v]; ++c) {
             const int a = t->place[c];
             if (seen[a] != (int)t->items.size()) {

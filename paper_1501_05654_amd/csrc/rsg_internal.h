@@ -153,7 +153,8 @@ struct ScatterHost {
     std::vector<int32_t> pt, more, place, atoms, entry;
 };
 void build_scatter(const std::vector<int32_t> &idx, const std::vector<int64_t> &off, const std::vector<int64_t> &len,
-                   const std::vector<int> &colour, std::vector<int32_t> &place, ScatterHost *t);
+                   const std::vector<int> &colour, const std::vector<int32_t> &atom_of, std::vector<int32_t> &mark,
+                   ScatterHost *t);
 
 struct Ham {
     Grid *g = nullptr;
