@@ -41,16 +41,24 @@ constexpr int MB = 256;  // threads per workgroup
 // (x, y, z pairs), then weighted.
 //
 // Bound by the latency of its gathers: all 24 table entries are requested,
-// then all 24 neighbours (a point without one reads itself and adds zero, so
-// no load hides behind a branch; with a branch each, the loads ran one after
-// another, 48 round trips deep).  500,199 points in Hilbert order: 16 orbitals
-// 277 -> 196 us, 64 orbitals 1.03 -> 0.88 ms, 4 orbitals 62 -> 51 us.  What is
-// left is the L1's rate (25 values of 16 B in for one out).  Workgroups of 1024
-// threads (265 us) and orbitals in groups of 4, 8 or 32 per workgroup
-// (200-211 us) were slower.
-__global__ void __launch_bounds__(MB) k_map_lap(const double2 *__restrict__ psi, double2 *__restrict__ out,
-                                                const int32_t *__restrict__ nbr, int32_t np, int32_t nst,
-                                                int64_t ld, double scale) {
+// then the neighbours, twelve at a time (a point without one reads itself and
+// adds zero, so no load hides behind a branch; with a branch each, the loads ran
+// one after another, 48 round trips deep).  All 24 together take 148 registers and 3
+// waves a SIMD; twelve take 126 and 4, which is worth more and leaves no second round
+// of workgroups at 2-4 e5 values.  Values (points x orbitals), Hilbert order, with
+// branches, 24 together, twelve:
+//   9,459 x 23 (2.2 e5)    9.0    9.6   7.7 us
+//   9,459 x 40 (3.8 e5)   10.6   12.9  10.3 us
+//   500,199 x 4             62     51    36 us
+//   500,199 x 16           279    191   160 us
+//   500,199 x 64          1027    882   726 us
+// Eight at a time measures the same within 3 %.  What is left is the L1's rate (25
+// values of 16 B in for one out).  With 24 together, workgroups of 1024 threads and
+// orbitals in groups of 4, 8 or 32 per workgroup were slower.
+constexpr int MG = 12;  // neighbours in flight
+__global__ void __launch_bounds__(MB, 4) k_map_lap(const double2 *__restrict__ psi, double2 *__restrict__ out,
+                                                   const int32_t *__restrict__ nbr, int32_t np, int32_t nst,
+                                                   int64_t ld, double scale) {
     const int blk = xcd_contiguous(blockIdx.x, gridDim.x);
     const int g = blk * MB + (int)threadIdx.x;
     const int p = g / nst;
@@ -60,15 +68,18 @@ __global__ void __launch_bounds__(MB) k_map_lap(const double2 *__restrict__ psi,
 #pragma unroll
     for (int j = 0; j < 24; ++j) q[j] = nbr[(int64_t)j * np + p];
     const double2 c = psi[(int64_t)p * ld + n];
-    double2 v[24];
-#pragma unroll
-    for (int j = 0; j < 24; ++j) v[j] = psi[(int64_t)(q[j] >= 0 ? q[j] : p) * ld + n];
     double sr[4] = {0, 0, 0, 0}, si[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < 24; ++j) {
-        const int k = j & 7, dm = k < 4 ? 3 - k : k - 4;  // |m| - 1
-        sr[dm] += q[j] >= 0 ? v[j].x : 0.0;
-        si[dm] += q[j] >= 0 ? v[j].y : 0.0;
+    for (int b = 0; b < 24; b += MG) {
+        double2 v[MG];
+#pragma unroll
+        for (int j = 0; j < MG; ++j) v[j] = psi[(int64_t)(q[b + j] >= 0 ? q[b + j] : p) * ld + n];
+#pragma unroll
+        for (int j = 0; j < MG; ++j) {
+            const int k = (b + j) & 7, dm = k < 4 ? 3 - k : k - 4;  // |m| - 1
+            sr[dm] += q[b + j] >= 0 ? v[j].x : 0.0;
+            si[dm] += q[b + j] >= 0 ? v[j].y : 0.0;
+        }
     }
     const double c0 = -205.0 / 72.0, c1 = 8.0 / 5.0, c2 = -1.0 / 5.0, c3 = 8.0 / 315.0, c4 = -1.0 / 560.0;
     const double lr = 3.0 * c0 * c.x + c1 * sr[0] + c2 * sr[1] + c3 * sr[2] + c4 * sr[3];
