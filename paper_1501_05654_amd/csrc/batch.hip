@@ -4,12 +4,13 @@
 // (section "Parallelization, optimizations and graphics processing units");
 // here the group extends across systems.  The systems are grouped into size
 // classes (by the width of their box), each class with its own stencil tile
-// shape; every stage of a Taylor(4) step runs, per tile shape in use, as one persistent
-// stencil launch over a list of (system, tile, z-range, orbital) items
-// (largest systems first, each sweeping its tiles orbital by orbital; the
-// list is cut into one contiguous segment per XCD, so that each XCD's L2
-// holds the halos its neighbouring tiles share), preceded by one projector gather launch and followed by one scatter launch, all systems at once.  A step sequence can be captured once into
-// a HIP graph and replayed.  Each output point is computed by the same
+// shape; every stage of a Taylor(4) step runs, per tile shape in use, as one
+// persistent stencil launch over a list of (system, tile, z-range, orbital)
+// items (largest systems first, each sweeping its tiles orbital by orbital;
+// the list is cut into one contiguous segment per XCD, so that each XCD's L2
+// holds the halos its neighbouring tiles share).  One projector gather launch
+// precedes them and one scatter launch follows, all systems at once.  A step
+// sequence can be captured once into a HIP graph and replayed.  Each output point is computed by the same
 // arithmetic as the single-system path, so the results are bitwise equal to
 // propagating each system alone with its class's tile shape.
 #include "rsg_internal.h"
@@ -103,9 +104,10 @@ struct Batch {
 
 // Default size classes: systems whose tight box is narrower than 48 points,
 // 48 to 79 points, and 80 points or more (the spheres of radius 4 to 12 bohr
-// at h = 0.25 span 33 to 97 points).  A tile that suits the widest spheres
-// leaves most lanes of a narrow sphere's tiles idle, and the other way round
-// narrow tiles re-read more halo per output on wide spheres.
+// at h = 0.25 span 33 to 97 points).  A class is what a caller or the tuner
+// may give a tile of its own: wide tiles leave more lanes of a narrow sphere
+// idle, narrow ones re-read more halo on a wide sphere.  One tile starts in
+// all of them (start_tile), and classes on one tile share their launches.
 constexpr int kClassEdges[] = {48, 80};
 
 namespace {

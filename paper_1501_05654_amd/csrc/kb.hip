@@ -61,10 +61,11 @@ __device__ __forceinline__ typename cpx<Tc>::type scatter_coef(const Tc *__restr
     return f;
 }
 
-// Scatter for one item (up to SP points of one owner atom) and 8 orbitals:
-// lane e of 32 takes points e, e + 32, ..., so that a half-wave covers runs of
-// consecutive points of one orbital.  The coefficients of the item's atoms (its owner and
-// the atoms that overlap it there) are staged in LDS, SA atoms at a time.
+// Scatter for one item (up to kScatterPoints points of one owner atom) and 8
+// orbitals: lane e of SP takes points e and e + SP, so that a half-wave covers
+// runs of consecutive points of one orbital.  The coefficients of the item's
+// atoms (its owner and the atoms that overlap it there) are staged in LDS, SA
+// atoms at a time.
 // Latency bound on small systems, where the chunk sums and every colour were
 // launches of their own: 2.0 + 2 x 3.6 us -> 5.0 us (2 atoms x 5 orbitals, 17 k
 // points), 4.8 + 2 x 4.9 -> 7.2 us (3 x 7, 500 k); 16 atoms x 64 orbitals
@@ -193,11 +194,11 @@ __global__ void __launch_bounds__(SP * 8) k_kb_scatter_batch(const KbSys *__rest
 }  // namespace
 
 // Support chunks per (atom, column tile): enough workgroups to fill the chip
-// when there are few atoms or few orbitals, each chunk at least 8 groups a slot
-// of 4 support entries of the smallest support (8 groups per wave: with
-// fewer, a batch of many small systems ran tens of thousands of nearly
-// empty gather workgroups).  The count depends on the system alone, so a
-// system gives the same bits alone or in a batch.
+// when there are few atoms or few orbitals.  Of the smallest support every chunk
+// keeps at least 8 groups (of 4 entries) for each of its kGatherSlots running
+// sums: with fewer, a batch of many small systems ran tens of thousands of
+// nearly empty gather workgroups.  The count depends on the system alone, so
+// a system gives the same bits alone or in a batch.
 int gather_chunks(const Ham &H, int64_t nst) {
     if (H.natoms == 0 || nst == 0) return 1;
     int64_t min_groups = INT64_MAX;

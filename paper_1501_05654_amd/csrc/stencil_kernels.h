@@ -538,7 +538,8 @@ __device__ __forceinline__ void march_lean(const KParams &a, const int4 it, cons
 // they keep one column per thread at 32 x 16, and fit at 32 x 32 (512
 // threads, one halo value each).  Measured per stage:
 // 3.05 M-point sphere x 64 orbitals 1.65 (16 x 16) and 1.71 ms (32 x 16, one
-// column) -> 1.59 ms (32 x 16, two), 96^3 cube x 8 57 -> 52 us (32 x 32).
+// column) -> 1.59 ms (32 x 16, two), 96^3 cube x 8 57 -> 52 us (32 x 32; a
+// candidate of the tuner, no default).
 constexpr int tile_cy(int TX, int TY, int D, bool fp64, bool heavy) {
     return fp64 && D == 1 && (TX * TY == 1024 || (TX * TY == 512 && TX == 32 && !heavy)) ? 2 : 1;
 }
@@ -599,10 +600,13 @@ __global__ void __launch_bounds__((TX * TY / stage_cy<TX, TY, D, Tc, MODE, FIRST
     using Real = decltype(Tin{}.x);
     if ((unsigned)((int)blockIdx.x - g.at) < (unsigned)g.nblk) {
         // the projector gather of the same input, with the plane buffer as
-        // its LDS.  A launch of its own before the stencil cost 6-7 us on
-        // small and middle systems and 20 us on 16 atoms x 64 orbitals, all
-        // latency; here it hides under the stencil (masked step of 500 k
-        // points x 7 orbitals x 3 atoms 272 -> 245 us).
+        // its LDS: the first workgroups of a launch that is resident at once,
+        // the last of a larger one.  A launch of its own before the stencil
+        // cost 6-7 us on small and middle systems and 20 us on 16 atoms x 64
+        // orbitals, all latency; here it hides under the marches (masked step
+        // of 500 k points x 7 orbitals x 3 atoms 272 -> 245 us).  Short
+        // marches in tiles of one or two waves don't hide it: there it stays
+        // a launch of its own and nblk is 0.
         static_assert(sizeof(tile) >= kGatherSlots * 64 * sizeof(Tc), "gather sums fit the plane buffer");
         const int j = (int)blockIdx.x - g.at, chunk = j % g.nchunk, q = j / g.nchunk, atom = q / g.nct;
         gather_tile<NW, Real, Tc>(static_cast<const Real *>(a.in), g.ldo, g.ncols, g.atoms[atom], atom, q - atom * g.nct,
