@@ -54,7 +54,8 @@ using BatchLaunches = std::vector<std::unique_ptr<BatchLaunch>>;
 // on four sets of systems (48 spheres of 1..32 and 1..5 orbitals on both
 // storages, 6 spheres) it is within 3 % of the best in every class; the 32 x 8
 // depth-2 tile over the whole z-range before it took 9-13 % longer a stage
-// (48 spheres, 1.6e8 values: 1.98 -> 1.75 ms).
+// (48 spheres, 1.6e8 values: 1.98 -> 1.75 ms).  On 256 spheres x 1..32 orbitals (6.9e8
+// values) whole columns of the same tile take 6.78 ms against 7.14: the tuner's to find.
 static TileShape start_tile() {
     TileShape t{1, 32, 16, 48};
     t.PD = 1;
